@@ -82,8 +82,11 @@ lrqo_status lrqo_shutdown(void);
  * g[2j+1] = sqrt(-2 ln u[2j]) sin(2 pi u[2j+1]); c_j = (g[2j] + i g[2j+1])/||g||.
  * The device evaluates this stream in FP32.
  *
- * Scoring: every candidate is scored in FP32; the best `rescore_topk` FP32
- * scores (ties to the lower index) are re-evaluated in FP64 from the same
+ * Scoring: every candidate is scored in FP32 (for K = 2, 3, 4, 2 <= r <= 4 and
+ * n >= 2,048, where the assignments far outnumber the candidates, on the
+ * matrix core from split FP32 values: w to the grade of an FP32 dot product,
+ * s = V^H z from exact integer sums of V rounded to 2^-30 of its largest
+ * entry); the best `rescore_topk` FP32 scores (ties to the lower index) are re-evaluated in FP64 from the same
  * FP32 direction widened to FP64; the FP64 arg-max (ties to the lower index)
  * is the result.  Labels and objective are therefore exactly those of the
  * FP64 decision rule at the returned direction.
@@ -106,7 +109,9 @@ typedef struct lrqo_sampled_options {
                                 |V_ij||c_j| of a decision boundary, u = 2^-24);
                                 other K: V c on BF16 MFMA with hi + lo parts,
                                 rows inside the BF16 error margin recomputed in
-                                FP32.  The FP64 rescore is the same in both.
+                                FP32.  The FP64 rescore is the same in both,
+                                and so is the scorer where the matrix-core
+                                form above applies.
                                 LRQO_BF16_FORM=w4 (read once per process)
                                 selects the second form for every K */
     int32_t rescore_topk;    /* 1..64; 0 means 64 */

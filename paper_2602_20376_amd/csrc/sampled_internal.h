@@ -87,7 +87,12 @@ struct SampledJob {
     hipEvent_t ev_score1;
 };
 
+// The scorer of a call: FP32 on the vector ALU, the precision form, or both
+// products on the matrix core from split FP32 values (sampled_split.h).
+enum ScoreForm { kFormFp32 = 0, kFormPrecision = 1, kFormSplit = 2 };
+
 struct ScratchPlan {
+    ScoreForm form = kFormFp32;
     int slices = 1;
     int64_t rows_per_slice = 0;
     int topk = 64;
@@ -102,6 +107,7 @@ struct Scratch {
     double2* roots64;
     float* f32;
     float* partial;
+    ScoreForm form;
     int slices;
     int64_t rows_per_slice;
     int topk;
@@ -120,7 +126,7 @@ constexpr int kCheckBlocks = 256;   // blocks of the prologue's finiteness check
 void plan_sampled(const SampledJob& job, ScratchPlan& plan);
 // The scorers with per-row label output for p.probe_count candidates
 // (sampled_probe.hip); same arithmetic as the plain launches.
-void launch_score_probe(const ScoreParams& p, dim3 grid, hipStream_t st, int r, bool real, int precision);
+void launch_score_probe(const ScoreParams& p, dim3 grid, hipStream_t st, int r, bool real, ScoreForm form);
 
 // Layout of the precision form's scorer: 0 = both products on MFMA
 // (k_score_bf16x; K = 2, 3, 4, other K take 1), 1 = V c on 4x4x4 MFMA tiles

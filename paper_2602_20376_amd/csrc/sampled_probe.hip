@@ -9,6 +9,7 @@
 #include "sampled_internal.h"
 #include "sampled_kernels.h"
 #include "sampled_bf16.h"
+#include "sampled_split.h"
 
 namespace lrqo {
 
@@ -38,9 +39,23 @@ void probe_bf16(const ScoreParams& p, dim3 grid, hipStream_t st) {
     }
 }
 
+template <int R, bool REAL, int KS>
+void probe_split(const ScoreParams& p, dim3 grid, hipStream_t st) {
+    if constexpr (R >= 2 && R <= 4 && !(REAL && KS == 2))
+        hipLaunchKernelGGL((k_score_split<R, REAL, KS, true>), grid, dim3(kSplitBlock), 0, st, p);
+}
+
 template <int R, bool REAL>
-void probe_k(const ScoreParams& p, dim3 grid, hipStream_t st, int precision) {
-    if (precision == 1) {
+void probe_k(const ScoreParams& p, dim3 grid, hipStream_t st, ScoreForm form) {
+    if (form == kFormSplit) {
+        switch (p.K) {
+            case 2: probe_split<R, REAL, 2>(p, grid, st); break;
+            case 3: probe_split<R, REAL, 3>(p, grid, st); break;
+            default: probe_split<R, REAL, 4>(p, grid, st); break;
+        }
+        return;
+    }
+    if (form == kFormPrecision) {
         switch (p.K) {
             case 2: probe_bf16<R, REAL, 2>(p, grid, st); break;
             case 3: probe_bf16<R, REAL, 3>(p, grid, st); break;
@@ -60,16 +75,16 @@ void probe_k(const ScoreParams& p, dim3 grid, hipStream_t st, int precision) {
 }
 
 template <bool REAL>
-void probe_r(const ScoreParams& p, dim3 grid, hipStream_t st, int r, int precision) {
+void probe_r(const ScoreParams& p, dim3 grid, hipStream_t st, int r, ScoreForm form) {
     switch (r) {
-        case 1: probe_k<1, REAL>(p, grid, st, precision); break;
-        case 2: probe_k<2, REAL>(p, grid, st, precision); break;
-        case 3: probe_k<3, REAL>(p, grid, st, precision); break;
-        case 4: probe_k<4, REAL>(p, grid, st, precision); break;
-        case 5: probe_k<5, REAL>(p, grid, st, precision); break;
-        case 6: probe_k<6, REAL>(p, grid, st, precision); break;
-        case 7: probe_k<7, REAL>(p, grid, st, precision); break;
-        case 8: probe_k<8, REAL>(p, grid, st, precision); break;
+        case 1: probe_k<1, REAL>(p, grid, st, form); break;
+        case 2: probe_k<2, REAL>(p, grid, st, form); break;
+        case 3: probe_k<3, REAL>(p, grid, st, form); break;
+        case 4: probe_k<4, REAL>(p, grid, st, form); break;
+        case 5: probe_k<5, REAL>(p, grid, st, form); break;
+        case 6: probe_k<6, REAL>(p, grid, st, form); break;
+        case 7: probe_k<7, REAL>(p, grid, st, form); break;
+        case 8: probe_k<8, REAL>(p, grid, st, form); break;
         default: break;
     }
 }
@@ -84,9 +99,9 @@ int bf16_form() {
     return form;
 }
 
-void launch_score_probe(const ScoreParams& p, dim3 grid, hipStream_t st, int r, bool real, int precision) {
-    if (real) probe_r<true>(p, grid, st, r, precision);
-    else probe_r<false>(p, grid, st, r, precision);
+void launch_score_probe(const ScoreParams& p, dim3 grid, hipStream_t st, int r, bool real, ScoreForm form) {
+    if (real) probe_r<true>(p, grid, st, r, form);
+    else probe_r<false>(p, grid, st, r, form);
 }
 
 }  // namespace lrqo
