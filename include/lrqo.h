@@ -82,12 +82,12 @@ lrqo_status lrqo_shutdown(void);
  * g[2j+1] = sqrt(-2 ln u[2j]) sin(2 pi u[2j+1]); c_j = (g[2j] + i g[2j+1])/||g||.
  * The device evaluates this stream in FP32.
  *
- * Scoring: every candidate is scored in FP32 (for K = 2, 3, 4, 2 <= r <= 4 and
- * n >= 2,048, where the assignments far outnumber the candidates, on the
- * matrix core from split FP32 values: w to the grade of an FP32 dot product,
- * s = V^H z from exact integer sums of V rounded to 2^-30 of its largest
- * entry); the best `rescore_topk` FP32 scores (ties to the lower index) are re-evaluated in FP64 from the same
- * FP32 direction widened to FP64; the FP64 arg-max (ties to the lower index)
+ * Scoring: every candidate is scored in FP32 (for K = 2, 3, 4, 8, 16,
+ * 2 <= r <= 4 and n >= 2,048, where the assignments far outnumber the
+ * candidates, on the matrix core from split FP32 values: w to the grade of an
+ * FP32 dot product, s = V^H z from exact integer sums of V rounded to 2^-30 of
+ * its largest entry); the best `rescore_topk` FP32 scores (ties to the lower
+ * index) are re-evaluated in FP64 from the same FP32 direction widened to FP64; the FP64 arg-max (ties to the lower index)
  * is the result.  Labels and objective are therefore exactly those of the
  * FP64 decision rule at the returned direction.
  *
@@ -138,7 +138,8 @@ typedef struct lrqo_sampled_result {
     double fp32_obj;         /* the FP32 scorer's value for the same direction */
     double best_c[2 * LRQO_MAX_R]; /* winner's direction, FP64 copy of the FP32 values, (re, im) pairs */
     int64_t flagged_rows;    /* precision 1: row-candidates recomputed in FP32
-                                (always 0 for K = 2, 3, 4, which recompute none) */
+                                (always 0 for K = 2, 3, 4 and in the matrix-core
+                                form, which recompute none) */
     float device_ms;         /* device time of the call, from stream events */
     float score_ms;          /* device time of the fused scoring kernel alone */
     int32_t rescored;        /* candidates that went through the FP64 rescore */

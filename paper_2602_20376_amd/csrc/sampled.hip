@@ -298,21 +298,23 @@ int cands_per_block(const SampledJob& job, ScoreForm form) {
     return mfma ? kBf16xCands : cands_per_block(job.r);
 }
 
-// The scorer of a call.  k_score_split takes K = 2, 3, 4 and 2 <= r <= 4 in
-// both precisions: it is 1.9 to 3.9 times as fast as the FP32 scorer at every
-// n tried (5,000 rows: 0.049 against 0.155 ms for 4,096 candidates; 10^6 rows,
-// r = 3: 14.5 against 34.8 ms for 131,072) and its scores lie 4 to 70 times
-// closer to FP64.  It is kept to problems whose assignments far outnumber the
-// candidates: where many candidates round to one assignment up to a rotation
-// their objectives are equal, only the rounding of the score orders them, and
-// the scorers that served such sizes before keep doing so.  The count is the
-// order of the arrangement's vertices, n^(2r-1); for real V and K = 4 the
-// quadrants of the turned w depend on Re c and Im c apart (n^(2r-2)), and for
-// real V and K = 2 on Re c alone (few assignments, not taken).
+// The scorer of a call.  k_score_split takes K = 2, 3, 4, 8, 16 and
+// 2 <= r <= 4 in both precisions: it is 1.8 to 3.9 times as fast as the FP32
+// scorer at every n tried (5,000 rows, r = 3 real, K = 3: 0.049 against
+// 0.155 ms for 4,096 candidates; 10^6 rows: 14.7 against 35.0 ms for 131,072;
+// r = 3 complex, K = 16, 200,000 rows: 4.7 against 14.9 ms for 65,536) and its
+// scores lie 4 to 70 times closer to FP64.  It is kept to problems whose
+// assignments far outnumber the candidates: where many candidates round to one
+// assignment up to a rotation their objectives are equal, only the rounding of
+// the score orders them, and the scorers that served such sizes before keep
+// doing so.  The count is the order of the arrangement's vertices, n^(2r-1);
+// for real V and K = 4 the quadrants of the turned w depend on Re c and Im c
+// apart (n^(2r-2)), and for real V and K = 2 on Re c alone (few assignments,
+// not taken).
 ScoreForm score_form(const SampledJob& job) {
     const ScoreForm plain = job.precision == 1 ? kFormPrecision : kFormFp32;
-    if (job.K < 2 || job.K > 4 || job.r < 2 || job.r > 4 || (job.real && job.K == 2)) return plain;
-    if (job.n < 2048 || job.n > kSplitMaxRows || (plain == kFormPrecision && bf16_form() == 1)) return plain;
+    if (k_special(job.K) == 0 || job.r < 2 || job.r > 4 || (job.real && job.K == 2)) return plain;
+    if (job.n < 2048 || job.n > split_rows(2) || (plain == kFormPrecision && bf16_form() == 1)) return plain;
     const double vertices = std::pow((double)job.n, job.real && job.K == 4 ? 2 * job.r - 2 : 2 * job.r - 1);
     return vertices >= 4096.0 * (double)job.S ? kFormSplit : plain;
 }
@@ -357,7 +359,9 @@ void launch_score_k(const ScoreParams& p, dim3 grid, hipStream_t st, ScoreForm f
         switch (p.K) {
             case 2: launch_score_split<R, REAL, 2>(p, grid, st); break;
             case 3: launch_score_split<R, REAL, 3>(p, grid, st); break;
-            default: launch_score_split<R, REAL, 4>(p, grid, st); break;
+            case 4: launch_score_split<R, REAL, 4>(p, grid, st); break;
+            case 8: launch_score_split<R, REAL, 8>(p, grid, st); break;
+            default: launch_score_split<R, REAL, 16>(p, grid, st); break;
         }
         return;
     }
@@ -483,11 +487,11 @@ void plan_sampled(const SampledJob& job, ScratchPlan& plan) {
     int64_t slices = std::max<int64_t>(1, (LRQO_SCORE_BLOCKS + cand_blocks - 1) / cand_blocks);
     slices = std::min<int64_t>(slices, std::max<int64_t>(1, job.n / 1024));
     if (plan.form == kFormSplit) {
-        // two blocks fit a CU (four waves a SIMD): of the slice counts up to
+        // two blocks fit a CU, one for K = 8 and 16: of the slice counts up to
         // that of the other scorers (so no call needs more scratch than it
         // did), the smallest whose last round of blocks is nearly full, or
         // the one that fills it best (the finer split among equals)
-        const int64_t blocks = (job.S + kSplitCands - 1) / kSplitCands, slots = 2 * 256;
+        const int64_t blocks = (job.S + kSplitCands - 1) / kSplitCands, slots = 256 * split_waves(job.K) / 2;
         int64_t best = slices;
         double best_fill = 0.0;
         for (int64_t s = 1; s <= slices; ++s) {

@@ -51,7 +51,9 @@ void probe_k(const ScoreParams& p, dim3 grid, hipStream_t st, ScoreForm form) {
         switch (p.K) {
             case 2: probe_split<R, REAL, 2>(p, grid, st); break;
             case 3: probe_split<R, REAL, 3>(p, grid, st); break;
-            default: probe_split<R, REAL, 4>(p, grid, st); break;
+            case 4: probe_split<R, REAL, 4>(p, grid, st); break;
+            case 8: probe_split<R, REAL, 8>(p, grid, st); break;
+            default: probe_split<R, REAL, 16>(p, grid, st); break;
         }
         return;
     }

@@ -1,5 +1,5 @@
-// Fused scorer on the matrix core from split FP32 values, K = 2, 3, 4 and
-// 2 <= r <= 4: both w = V c and s = V^H z are matrix products whose operands
+// Fused scorer on the matrix core from split FP32 values, K = 2, 3, 4, 8, 16
+// and 2 <= r <= 4: both w = V c and s = V^H z are matrix products whose operands
 // hold V, c and z without loss of FP32 grade.  Internal header, included
 // after sampled_kernels.h by sampled.hip and sampled_probe.hip.
 #pragma once
@@ -26,11 +26,17 @@ namespace {
 //              about 0.55u.  Five are used where they fill the k-slots of a
 //              chunk that six would not fit, the others get six or more.
 //   labels     sign bits only.  K = 3: u = |Im w| - sqrt(3) Re w (label 0 iff
-//              u < 0) and Im w; K = 4: the direction is turned by
-//              e^{-i pi/4}, so the labels are the quadrants; K = 2: Re w.
-//              v_perm_b32 spreads the signs of four rows over the bytes of a
-//              dword as 0 / -1.
-//   s = V^H z  v_mfma_i32_32x32x32_i8 of those masks against V in 30-bit
+//              u < 0) and Im w; K = 2: Re w; K = 4, 8, 16: the direction is
+//              turned by e^{-i pi/K}, so the boundaries are the axes and
+//              lines |b| = tan(phi) |a| of w = a + ib.  v_perm_b32 spreads the
+//              signs of four rows over the bytes of a dword as 0 / -1.
+//   z          label planes of one byte per row: masks of label sets
+//              (K = 2, 3, 4), sign(a), sign(b) within each half of a quadrant
+//              (K = 8), or for K = 16, whose roots have four magnitudes, Re z
+//              and Im z in 23-bit fixed point, three balanced base-256 digits
+//              each, looked up by v_perm_b32 (eight-byte tables: sector and
+//              sign select the byte)
+//   s = V^H z  v_mfma_i32_32x32x32_i8 of those planes against V in 30-bit
 //              fixed point (one scale for the whole factor, four balanced
 //              base-256 digits per value: 4C <= 32 rows of the operand).  The
 //              sums are exact integers, so the only error is the rounding of
@@ -50,7 +56,25 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 constexpr int kSplitBlock = 512;                           // eight waves of 32 candidates
 constexpr int kSplitCands = kSplitBlock / kWave * 32;      // candidates of a block
 constexpr int kSplitTile = 256;                            // rows staged at a time
-constexpr int64_t kSplitMaxRows = (int64_t)1 << 23;        // rows of a slice: |digit| <= 128 keeps I32 sums exact
+
+// Rows whose I32 sums stay exact: digits of V are at most 128 in size, plane
+// entries 1 (K = 16: 128; its sums are folded after as many rows).
+__host__ __device__ constexpr int64_t split_rows(int KS) { return (int64_t)1 << (KS == 16 ? 16 : 23); }
+
+// K = 16 planes.  Entry e of a table: bits 0 and 1 name the sector of the
+// quadrant, bit 2 is the sign; entries hold digit k of round(mag * kRoot16).
+constexpr double kRoot16 = 8200000.0;                      // top digit stays below 128
+constexpr double root16_mag(int e) {
+    return (e & 3) == 3 ? 0.98078528040323043 : (e & 3) == 1 ? 0.83146961230254524 : (e & 3) == 0 ? 0.55557023301960218 : 0.19509032201612826;
+}
+constexpr uint32_t root16_digit(int e, int k) {
+    const long long x = (long long)(root16_mag(e) * kRoot16 + 0.5) * (e & 4 ? -1 : 1);
+    return (uint32_t)(((((unsigned long long)(x + 0x808080)) >> (8 * k)) & 255u) ^ 0x80u);
+}
+constexpr uint32_t root16_table(int half, int k) {
+    return root16_digit(4 * half, k) | root16_digit(4 * half + 1, k) << 8 | root16_digit(4 * half + 2, k) << 16 |
+           root16_digit(4 * half + 3, k) << 24;
+}
 
 template <int R, bool REAL>
 struct SplitShape {
@@ -86,13 +110,15 @@ __device__ __forceinline__ void split3(float x, _Float16 (&p)[3]) {
     }
 }
 
-// Signs of a[i .. i+3] as bytes 0 / -1, as two halves to be or-ed.
+// Signs of two values as bytes 0 / -1 in the low or high half of a dword.
 __device__ __forceinline__ uint32_t signs_lo(float a, float b) {
     return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x0c0c0b09u);
 }
 __device__ __forceinline__ uint32_t signs_hi(float a, float b) {
     return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x0b090c0cu);
 }
+
+__device__ __forceinline__ uint32_t signs4(float a, float b, float c, float d) { return signs_lo(a, b) | signs_hi(c, d); }
 
 // Exponent e of the largest |V| entry (prologue's per-block maxima): V enters
 // the I8 operand as round(V 2^(29-e)), below 2^30 in size.
@@ -104,12 +130,19 @@ __device__ __forceinline__ int split_exponent(const float* vmax, int count) {
     return m > 0.0f && isfinite(m) ? ilogbf(m) : 0;
 }
 
+// Label planes of a K.
+__host__ __device__ constexpr int split_planes(int KS) { return KS == 2 ? 1 : (KS == 8 ? 4 : (KS == 16 ? 6 : 2)); }
+// Waves per SIMD asked of the compiler: K = 8 and 16 hold 64 and 96
+// accumulators (K = 8 at four waves spills: r = 3 complex 3.7 against 3.1 ms
+// for n = 100,000 and 131,072 candidates).
+__host__ __device__ constexpr int split_waves(int KS) { return KS >= 8 ? 2 : 4; }
+
 template <int R, bool REAL, int KS, bool PROBE>
-__global__ __launch_bounds__(kSplitBlock, 4) void k_score_split(ScoreParams p) {
+__global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(ScoreParams p) {
     using Sh = SplitShape<R, REAL>;
     constexpr int C = Sh::C, NCH = Sh::NCH, NP = Sh::NP;
     constexpr int NB = kSplitTile / 32;                  // 32-row blocks of a tile
-    constexpr int NPL = KS == 2 ? 1 : 2;                 // label planes
+    constexpr int NPL = split_planes(KS);
     __shared__ __align__(16) v8h aw[2][NB][NCH][64];     // F16 operand of w: [buffer][block][chunk][lane]
     __shared__ __align__(16) signed char as[2][NB][64][16];   // I8 operand of s: [buffer][block][lane][k-slot]
     __shared__ long long tot[kSplitTile / kWave][C];
@@ -127,13 +160,20 @@ __global__ __launch_bounds__(kSplitBlock, 4) void k_score_split(ScoreParams p) {
     {
         float c[1][2 * R];
         lane_directions<R, 1, PROBE>(p, idx, 0, blockIdx.y == 0 && h == 0, c, slot);
+        // scaled like a row (a caller's list need not hold unit directions)
+        float m = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 2 * R; ++j) m = fmaxf(m, fabsf(c[0][j]));
+        const int e = m > 0.0f ? 13 - ilogbf(m) : 0;
         double x[C], y[C];                               // factors of the components in Re w, Im w
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            double cr = c[0][2 * j] * 0x1p14, ci = c[0][2 * j + 1] * 0x1p14;
-            if constexpr (KS == 4) {                     // c e^{-i pi/4}
-                const double t = 0.70710678118654752 * (cr + ci);
-                ci = 0.70710678118654752 * (ci - cr);
+            double cr = ldexp((double)c[0][2 * j], e), ci = ldexp((double)c[0][2 * j + 1], e);
+            if constexpr (KS == 4 || KS == 8 || KS == 16) {   // c e^{-i pi/K}
+                constexpr double co = KS == 4 ? 0.70710678118654752 : (KS == 8 ? 0.92387953251128676 : 0.98078528040323043);
+                constexpr double sn = KS == 4 ? 0.70710678118654752 : (KS == 8 ? 0.38268343236508977 : 0.19509032201612826);
+                const double t = cr * co + ci * sn;
+                ci = ci * co - cr * sn;
                 cr = t;
             }
             const double sr = KS == 3 ? -1.7320508075688772 : 1.0;   // K = 3: -sqrt(3) Re w
@@ -171,6 +211,50 @@ __global__ __launch_bounds__(kSplitBlock, 4) void k_score_split(ScoreParams p) {
     for (int q = 0; q < NPL; ++q)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[q][i] = 0;
+
+    // ---- s of the lane's columns j = 2g + h from the accumulators, in units of V's fixed point
+    constexpr int NG = (R + 1) / 2;
+    double sum[NG][2];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) sum[g][0] = sum[g][1] = 0.0;
+    auto fold = [&]() {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int j = 2 * g + h;
+            double zr[2] = {0.0, 0.0}, zi[2] = {0.0, 0.0};   // sums of Re z, Im z times Re V_j and times Im V_j
+#pragma unroll
+            for (int q = 0; q < (REAL ? 1 : 2); ++q) {
+                const int i0 = REAL ? 4 * g : 8 * g + 4 * q;
+                auto plane = [&](int k) {
+                    return (((long long)acc[k][i0 + 3] * 256 + acc[k][i0 + 2]) * 256 + acc[k][i0 + 1]) * 256 + acc[k][i0];
+                };
+                if constexpr (KS <= 4) {
+                    long long t = 0;
+                    if (j < R) {
+                        for (int w = 0; w < kSplitTile / kWave; ++w) t += tot[w][q * R + j];
+                    }
+                    const long long n0 = -plane(0), n1 = -plane(NPL - 1);   // masks are 0 / -1
+                    if constexpr (KS == 2) {             // n0: rows with z = -1
+                        zr[q] = (double)(t - 2 * n0);
+                    } else if constexpr (KS == 3) {      // n0, n1: rows with label 0, 2
+                        zr[q] = 0.5 * (double)(3 * n0 - t);
+                        zi[q] = 0.86602540378443865 * (double)(t - n0 - 2 * n1);
+                    } else {                             // n0, n1: rows with negative real, imaginary part
+                        zr[q] = 0.70710678118654752 * (double)(t - 2 * n0);
+                        zi[q] = 0.70710678118654752 * (double)(t - 2 * n1);
+                    }
+                } else if constexpr (KS == 8) {
+                    zr[q] = 0.92387953251128676 * (double)plane(0) + 0.38268343236508977 * (double)plane(1);
+                    zi[q] = 0.38268343236508977 * (double)plane(2) + 0.92387953251128676 * (double)plane(3);
+                } else {
+                    zr[q] = (((double)plane(2) * 256.0 + (double)plane(1)) * 256.0 + (double)plane(0)) * (1.0 / kRoot16);
+                    zi[q] = (((double)plane(5) * 256.0 + (double)plane(4)) * 256.0 + (double)plane(3)) * (1.0 / kRoot16);
+                }
+            }
+            sum[g][0] += REAL ? zr[0] : zr[0] + zi[1];
+            sum[g][1] += REAL ? zi[0] : zi[0] - zr[1];
+        }
+    };
 
     // ---- tiles: threads 0..255 write the F16 operand of a row, 256..511 its I8 operand
     const int64_t r0 = (int64_t)blockIdx.y * p.rows_per_slice;
@@ -217,7 +301,7 @@ __global__ __launch_bounds__(kSplitBlock, 4) void k_score_split(ScoreParams p) {
 #pragma unroll
             for (int k = 0; k < C; ++k) {
                 const int q = __float2int_rn(ldexpf(v[k], 29 - ev));
-                ts[k] += q;
+                if constexpr (KS <= 4) ts[k] += q;
                 const uint32_t dig = ((uint32_t)q + 0x00808080u) ^ 0x00808080u;   // balanced digits, lowest first
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
@@ -249,37 +333,100 @@ __global__ __launch_bounds__(kSplitBlock, 4) void k_score_split(ScoreParams p) {
                 if constexpr (KS != 2) wi = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bim[ch], wi, 0, 0, 0);
             }
             const v4i a8 = *reinterpret_cast<const v4i*>(as[buf][blk][lane]);
-            v4i m0, m1;
+            v4i m[NPL];
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                float x[4];
+                float a[4], c[4];
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    x[b] = KS == 3 ? fabsf(wi[4 * d + b]) + wr[4 * d + b] : wr[4 * d + b];
-                m0[d] = (int)(signs_lo(x[0], x[1]) | signs_hi(x[2], x[3]));
+                for (int b = 0; b < 4; ++b) {
+                    a[b] = wr[4 * d + b];
+                    c[b] = wi[4 * d + b];
+                }
+                if constexpr (KS == 3) {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) a[b] += fabsf(c[b]);
+                }
+                const uint32_t sa = signs4(a[0], a[1], a[2], a[3]);
+                m[0][d] = (int)sa;
                 if constexpr (KS != 2) {
-                    const uint32_t si = signs_lo(wi[4 * d], wi[4 * d + 1]) | signs_hi(wi[4 * d + 2], wi[4 * d + 3]);
-                    m1[d] = (int)(KS == 3 ? si & ~(uint32_t)m0[d] : si);
+                    const uint32_t sb = signs4(c[0], c[1], c[2], c[3]);
+                    if constexpr (KS == 3) m[1][d] = (int)(sb & ~sa);
+                    else m[1][d] = (int)sb;
+                    if constexpr (KS == 8) {             // halves of the quadrant: |a| >= |b| or not
+                        float t[4];
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) t[b] = fabsf(a[b]) - fabsf(c[b]);
+                        const uint32_t st = signs4(t[0], t[1], t[2], t[3]);
+                        m[0][d] = (int)((sa | 0x01010101u) & ~st);
+                        m[1][d] = (int)((sa | 0x01010101u) & st);
+                        m[2][d] = (int)((sb | 0x01010101u) & ~st);
+                        m[3][d] = (int)((sb | 0x01010101u) & st);
+                    }
+                    if constexpr (KS == 16) {            // |b| against tan(pi/8), 1, tan(3 pi/8) times |a|
+                        float t[3][4];
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            t[0][b] = fmaf(-0.41421356237309505f, fabsf(a[b]), fabsf(c[b]));
+                            t[1][b] = fabsf(c[b]) - fabsf(a[b]);
+                            t[2][b] = fmaf(-2.41421356237309505f, fabsf(a[b]), fabsf(c[b]));
+                        }
+                        const uint32_t s0 = signs4(t[0][0], t[0][1], t[0][2], t[0][3]);
+                        const uint32_t s1 = signs4(t[1][0], t[1][1], t[1][2], t[1][3]);
+                        const uint32_t s2 = signs4(t[2][0], t[2][1], t[2][2], t[2][3]);
+                        // sector code: bit 0 below the diagonal, bit 1 next to an axis; Im z has
+                        // the magnitudes of Re z mirrored on the diagonal
+                        const uint32_t axis = (s0 | ~s2) & 0x02020202u;
+                        const uint32_t er = (axis | (s1 & 0x01010101u)) | (sa & 0x04040404u);
+                        const uint32_t ei = (axis | (~s1 & 0x01010101u)) | (sb & 0x04040404u);
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) {
+                            m[k][d] = (int)__builtin_amdgcn_perm(root16_table(1, k), root16_table(0, k), er);
+                            m[3 + k][d] = (int)__builtin_amdgcn_perm(root16_table(1, k), root16_table(0, k), ei);
+                        }
+                    }
                 }
             }
-            acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a8, m0, acc[0], 0, 0, 0);
-            if constexpr (KS != 2) acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a8, m1, acc[1], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) acc[q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a8, m[q], acc[q], 0, 0, 0);
             if constexpr (PROBE) {
                 if (slot[0] >= 0) {
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const int64_t at = t0 + 32 * blk + 8 * (i / 4) + 4 * h + i % 4;
-                        const bool f0 = (m0[i / 4] >> (8 * (i % 4))) & 1, f1 = KS != 2 && ((m1[i / 4] >> (8 * (i % 4))) & 1);
                         int lab;
-                        if constexpr (KS == 2) lab = f0 ? 1 : 0;
-                        else if constexpr (KS == 3) lab = f0 ? 0 : (f1 ? 2 : 1);
-                        else lab = f0 ? (f1 ? 3 : 2) : (f1 ? 0 : 1);
+                        if constexpr (KS <= 4) {
+                            const bool f0 = (m[0][i / 4] >> (8 * (i % 4))) & 1, f1 = (m[NPL - 1][i / 4] >> (8 * (i % 4))) & 1;
+                            if constexpr (KS == 2) lab = f0 ? 1 : 0;
+                            else if constexpr (KS == 3) lab = f0 ? 0 : (f1 ? 2 : 1);
+                            else lab = f0 ? (f1 ? 3 : 2) : (f1 ? 0 : 1);
+                        } else {                         // the root the planes hold, turned back
+                            auto at_byte = [&](int q) { return (float)(signed char)(m[q][i / 4] >> (8 * (i % 4))); };
+                            float zr, zi;
+                            if constexpr (KS == 8) {
+                                zr = kCos8 * at_byte(0) + kSin8 * at_byte(1);
+                                zi = kSin8 * at_byte(2) + kCos8 * at_byte(3);
+                            } else {
+                                zr = (at_byte(2) * 256.0f + at_byte(1)) * 256.0f + at_byte(0);
+                                zi = (at_byte(5) * 256.0f + at_byte(4)) * 256.0f + at_byte(3);
+                            }
+                            constexpr float co = KS == 8 ? kCos8 : kCos16, sn = KS == 8 ? kSin8 : kSin16;
+                            lab = root_index(zr * co - zi * sn, zr * sn + zi * co, KS);
+                        }
                         if (at < r1) p.probe_out[(size_t)slot[0] * p.n + at] = (uint16_t)lab;
                     }
                 }
             }
         }
         __syncthreads();
+        if constexpr (KS == 16) {                        // before the sums could pass 31 bits
+            if ((t0 - r0) % split_rows(KS) == split_rows(KS) - kSplitTile && t0 + kSplitTile < r1) {
+                fold();
+#pragma unroll
+                for (int q = 0; q < NPL; ++q)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[q][i] = 0;
+            }
+        }
     }
 
     // ---- sum_i V_i over the slice (exact), then s of each candidate
@@ -291,38 +438,14 @@ __global__ __launch_bounds__(kSplitBlock, 4) void k_score_split(ScoreParams p) {
         if (fixed && lane == 0) tot[wave - kSplitTile / kWave][k] = t;
     }
     __syncthreads();
+    fold();
     const double unit = ldexp(1.0, ev - 29);
     float f = 0.0f;
 #pragma unroll
-    for (int g = 0; g < (REAL ? 4 : 2); ++g) {           // the columns this lane's registers hold
-        const int j = REAL ? 2 * g + h : 2 * g + h;
-        if (2 * g >= R) break;
-        double zr[2], zi[2];                             // sums of Re z and Im z against Re V_j and Im V_j
-#pragma unroll
-        for (int q = 0; q < (REAL ? 1 : 2); ++q) {
-            const int i0 = REAL ? 4 * g : 8 * g + 4 * q;
-            long long t = 0, n0, n1 = 0;
-            if (j < R) {
-                for (int w = 0; w < kSplitTile / kWave; ++w) t += tot[w][q * R + j];
-            }
-            n0 = -((((long long)acc[0][i0 + 3] * 256 + acc[0][i0 + 2]) * 256 + acc[0][i0 + 1]) * 256 + acc[0][i0]);
-            if constexpr (KS != 2)
-                n1 = -((((long long)acc[NPL - 1][i0 + 3] * 256 + acc[NPL - 1][i0 + 2]) * 256 + acc[NPL - 1][i0 + 1]) * 256 +
-                       acc[NPL - 1][i0]);
-            if constexpr (KS == 2) {                     // n0: rows with z = -1
-                zr[q] = unit * (double)(t - 2 * n0);
-                zi[q] = 0.0;
-            } else if constexpr (KS == 3) {              // n0, n1: rows with label 0, 2
-                zr[q] = unit * 0.5 * (double)(3 * n0 - t);
-                zi[q] = unit * 0.86602540378443865 * (double)(t - n0 - 2 * n1);
-            } else {                                     // n0, n1: rows with negative real, imaginary part
-                zr[q] = unit * 0.70710678118654752 * (double)(t - 2 * n0);
-                zi[q] = unit * 0.70710678118654752 * (double)(t - 2 * n1);
-            }
-        }
-        const float sr = REAL ? (float)zr[0] : (float)(zr[0] + zi[1]);
-        const float si = REAL ? (float)zi[0] : (float)(zi[0] - zr[1]);
+    for (int g = 0; g < NG; ++g) {
+        const int j = 2 * g + h;
         if (j >= R) continue;
+        const float sr = (float)(unit * sum[g][0]), si = (float)(unit * sum[g][1]);
         f = fmaf(sr, sr, fmaf(si, si, f));
         if (gridDim.y > 1 && idx < p.S) {
             float* out = p.partial + ((size_t)blockIdx.y * (2 * R) + 2 * j) * p.S + idx;
