@@ -39,8 +39,7 @@ constexpr int NP = H * DIN + H + H * H + H + OUT * H + OUT;   // 21,248 paramete
 constexpr int OFF_W1 = 0, OFF_B1 = H * DIN, OFF_W2 = OFF_B1 + H, OFF_B2 = OFF_W2 + H * H,
               OFF_W3 = OFF_B2 + H, OFF_B3 = OFF_W3 + OUT * H;
 constexpr int kBlock = 256;
-constexpr int kRowTile = 64;   // rows per backward tile (one per lane)
-static_assert(kRowTile == kWave, "the backward maps lane l to row l of the tile");
+constexpr int kRowTile = 32;   // rows per backward tile (columns of its products)
 constexpr int kMaxRetry = 32;  // rejection-sampler attempts before falling back to the mean
 
 struct Frame {                 // canonical gauge of one instance
@@ -83,141 +82,105 @@ __device__ float mean_resultant(float k) {   // I_3 / I_2 = -d log C_6 / d kappa
 }
 
 // ---------------------------------------------------------------- gauge
-// Eigenvectors of a 3x3 Hermitian M through the 6x6 real symmetric form
-// [[Re M, -Im M], [Im M, Re M]] (cyclic Jacobi), each eigenvalue appearing
-// twice; complex vectors are taken in descending eigenvalue order and
-// orthogonalised (complex Gram-Schmidt), keeping three.
+// Eigenvectors of a 3x3 Hermitian M in descending eigenvalue order, by
+// cyclic complex Jacobi: rotation (p, q) turns column q by e^{-i alpha},
+// alpha = arg M_pq, and then zeroes the real off-diagonal entry.  One thread;
+// every index is a constant, so M and U stay in registers.  Three rotations a
+// sweep with three-entry updates, where the 6x6 real form of M took fifteen
+// with six (k_frame_eig, 64 instances: 71 -> 12 us).
 __device__ void hermitian_eig3(const double (&Mr)[3][3], const double (&Mi)[3][3],
                                double (&Ur)[3][3], double (&Ui)[3][3]) {
-    double A[6][6], Q[6][6];
-    for (int i = 0; i < 3; ++i)
+    double d[3], ar[3][3], ai[3][3];           // diagonal; entries above it
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        d[i] = Mr[i][i];
+#pragma unroll
         for (int j = 0; j < 3; ++j) {
-            A[i][j] = Mr[i][j];
-            A[i + 3][j + 3] = Mr[i][j];
-            A[i][j + 3] = -Mi[i][j];
-            A[i + 3][j] = Mi[i][j];
+            ar[i][j] = Mr[i][j];
+            ai[i][j] = Mi[i][j];
+            Ur[i][j] = i == j ? 1.0 : 0.0;
+            Ui[i][j] = 0.0;
         }
-    for (int i = 0; i < 6; ++i)
-        for (int j = 0; j < 6; ++j) Q[i][j] = i == j ? 1.0 : 0.0;
+    }
     for (int sweep = 0; sweep < 30; ++sweep) {
-        double off = 0.0, dia = 0.0;
+        double off = 0.0;
+        const double dia = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            dia += A[i][i] * A[i][i];
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = i + 1; j < 6; ++j) off += A[i][j] * A[i][j];
-        }
+            for (int j = i + 1; j < 3; ++j) off += ar[i][j] * ar[i][j] + ai[i][j] * ai[i][j];
         // converged when the off-diagonal part is at FP64 rounding of the
         // diagonal (an absolute bound would never be met for large M)
         if (off <= 1e-32 * dia || off < 1e-300) break;
-        // fully unrolled: every index is a constant, so A and Q stay in registers
 #pragma unroll
-        for (int p = 0; p < 6; ++p)
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
-            for (int q = p + 1; q < 6; ++q) {
-                if (fabs(A[p][q]) < 1e-300) continue;
-                const double th = (A[q][q] - A[p][p]) / (2.0 * A[p][q]);
+            for (int q = p + 1; q < 3; ++q) {
+                const double m = sqrt(ar[p][q] * ar[p][q] + ai[p][q] * ai[p][q]);
+                if (m < 1e-300) continue;
+                const double er = ar[p][q] / m, ei = -ai[p][q] / m;           // e^{-i alpha}
+                const double th = (d[q] - d[p]) / (2.0 * m);
                 const double t = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
                 const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
+                d[p] -= t * m;
+                d[q] += t * m;
+                ar[p][q] = ai[p][q] = 0.0;
+                const int k = 3 - p - q;                                       // the third index
+                // M_kp and M_kq from the entries above the diagonal
+                double pr = k < p ? ar[k][p] : ar[p][k], pi = k < p ? ai[k][p] : -ai[p][k];
+                double qr = k < q ? ar[k][q] : ar[q][k], qi = k < q ? ai[k][q] : -ai[q][k];
+                double tr = qr * er - qi * ei;
+                qi = qr * ei + qi * er;
+                qr = tr;
+                const double npr = c * pr - s * qr, npi = c * pi - s * qi;
+                const double nqr = s * pr + c * qr, nqi = s * pi + c * qi;
+                if (k < p) { ar[k][p] = npr; ai[k][p] = npi; } else { ar[p][k] = npr; ai[p][k] = -npi; }
+                if (k < q) { ar[k][q] = nqr; ai[k][q] = nqi; } else { ar[q][k] = nqr; ai[q][k] = -nqi; }
 #pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                    const double akp = A[k][p], akq = A[k][q];
-                    A[k][p] = c * akp - s * akq;
-                    A[k][q] = s * akp + c * akq;
-                }
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                    const double apk = A[p][k], aqk = A[q][k];
-                    A[p][k] = c * apk - s * aqk;
-                    A[q][k] = s * apk + c * aqk;
-                }
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                    const double qkp = Q[k][p], qkq = Q[k][q];
-                    Q[k][p] = c * qkp - s * qkq;
-                    Q[k][q] = s * qkp + c * qkq;
+                for (int i = 0; i < 3; ++i) {
+                    const double upr = Ur[i][p], upi = Ui[i][p];
+                    const double uqr = Ur[i][q] * er - Ui[i][q] * ei, uqi = Ur[i][q] * ei + Ui[i][q] * er;
+                    Ur[i][p] = c * upr - s * uqr;
+                    Ui[i][p] = c * upi - s * uqi;
+                    Ur[i][q] = s * upr + c * uqr;
+                    Ui[i][q] = s * upi + c * uqi;
                 }
             }
     }
-    // Everything below indexes A, Q, U only with constants (unrolled loops
-    // and selects), so that they stay in registers.
-    double ev[6];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) ev[c] = A[c][c];
-    auto pick6 = [](const double (&a)[6], int idx) {
-        double v = a[0];
+    for (int pass = 0; pass < 3; ++pass) {     // compare-exchange (0,1), (1,2), (0,1)
+        const int p = pass == 1 ? 1 : 0, q = p + 1;
+        const bool sw = d[q] > d[p];
+        const double dp = d[p];
+        d[p] = sw ? d[q] : d[p];
+        d[q] = sw ? dp : d[q];
 #pragma unroll
-        for (int c = 1; c < 6; ++c) v = idx == c ? a[c] : v;
-        return v;
-    };
-    int order[6] = {0, 1, 2, 3, 4, 5};
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int j = i + 1; j < 6; ++j)
-            if (pick6(ev, order[j]) > pick6(ev, order[i])) {
-                const int t = order[i];
-                order[i] = order[j];
-                order[j] = t;
-            }
-    int got = 0;
-#pragma unroll
-    for (int oi = 0; oi < 6; ++oi) {
-        if (got >= 3) break;
-        const int col = order[oi];
-        double ur[3], ui[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            ur[k] = Q[k][0];
-            ui[k] = Q[k + 3][0];
-#pragma unroll
-            for (int c = 1; c < 6; ++c) {
-                ur[k] = col == c ? Q[k][c] : ur[k];
-                ui[k] = col == c ? Q[k + 3][c] : ui[k];
-            }
+        for (int i = 0; i < 3; ++i) {
+            const double xr = Ur[i][p], xi = Ui[i][p];
+            Ur[i][p] = sw ? Ur[i][q] : xr;
+            Ui[i][p] = sw ? Ui[i][q] : xi;
+            Ur[i][q] = sw ? xr : Ur[i][q];
+            Ui[i][q] = sw ? xi : Ui[i][q];
         }
-#pragma unroll
-        for (int prev = 0; prev < 3; ++prev) {     // remove <u_prev, u> u_prev
-            if (prev >= got) break;
-            double dr = 0.0, di = 0.0;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                dr += Ur[k][prev] * ur[k] + Ui[k][prev] * ui[k];
-                di += Ur[k][prev] * ui[k] - Ui[k][prev] * ur[k];
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                ur[k] -= dr * Ur[k][prev] - di * Ui[k][prev];
-                ui[k] -= dr * Ui[k][prev] + di * Ur[k][prev];
-            }
-        }
-        double nrm = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) nrm += ur[k] * ur[k] + ui[k] * ui[k];
-        nrm = sqrt(nrm);
-        if (nrm < 0.5) continue;                   // the i * u twin of an earlier vector
-#pragma unroll
-        for (int g = 0; g < 3; ++g)
-            if (g == got) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    Ur[k][g] = ur[k] / nrm;
-                    Ui[k][g] = ui[k] / nrm;
-                }
-            }
-        ++got;
     }
 }
 
-__device__ double block_sum(double x, double* red) {
-    x = wave_sum_f64(x);
+// Block sums of N values: each wave's sum (butterfly), then the waves in
+// order; out[e] is written by thread e.
+template <int N>
+__device__ __forceinline__ void block_sums(const double (&x)[N], double (*red)[kBlock / kWave], double* out) {
     const int w = threadIdx.x / kWave;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        const double v = wave_sum_f64(x[e]);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[e][w] = v;
+    }
     __syncthreads();
-    if ((threadIdx.x & (kWave - 1)) == 0) red[w] = x;
-    __syncthreads();
-    double t = 0.0;
-    for (int i = 0; i < kBlock / kWave; ++i) t += red[i];
-    return t;
+    if (threadIdx.x < N) {
+        double t = 0.0;
+        for (int i = 0; i < kBlock / kWave; ++i) t += red[threadIdx.x][i];
+        out[threadIdx.x] = t;
+    }
 }
 
 // Canonical frame of each instance in four stages, the two row passes split
@@ -238,7 +201,7 @@ __device__ __forceinline__ void split_rows(int64_t n, int q, int splits, int64_t
 
 __global__ __launch_bounds__(kBlock) void k_frame_m(const float* __restrict__ V, const int64_t* voff,
                                                    const int64_t* nrows, int splits, double* __restrict__ work) {
-    __shared__ double red[kBlock / kWave];
+    __shared__ double red[kFrameM][kBlock / kWave];
     const int t = blockIdx.x, q = blockIdx.y;
     const float* Vt = V + voff[t];
     int64_t r0, r1;
@@ -258,10 +221,7 @@ __global__ __launch_bounds__(kBlock) void k_frame_m(const float* __restrict__ V,
             }
         acc[18] += w;
     }
-    for (int e = 0; e < kFrameM; ++e) {
-        const double v = block_sum(acc[e], red);
-        if (threadIdx.x == 0) work[((size_t)t * splits + q) * kFrameM + e] = v;
-    }
+    block_sums<kFrameM>(acc, red, work + ((size_t)t * splits + q) * kFrameM);
 }
 
 // One wave sums each entry e < W of instance t over the splits into tot[e]:
@@ -332,7 +292,7 @@ __device__ __forceinline__ void cpow_int(double wr, double wi, int K, double& pr
 __global__ __launch_bounds__(kBlock) void k_frame_p(const float* __restrict__ V, const int64_t* voff,
                                                    const int64_t* nrows, int splits, int K,
                                                    const Frame* __restrict__ frames, double* __restrict__ work) {
-    __shared__ double red[kBlock / kWave];
+    __shared__ double red[kFrameP][kBlock / kWave];
     __shared__ double Us[18];
     const int t = blockIdx.x, q = blockIdx.y;
     if (threadIdx.x < 18) Us[threadIdx.x] = frames[t].g[threadIdx.x];
@@ -341,7 +301,7 @@ __global__ __launch_bounds__(kBlock) void k_frame_p(const float* __restrict__ V,
     const float* Vt = V + voff[t];
     int64_t r0, r1;
     split_rows(nrows[t], q, splits, r0, r1);
-    double pk[6] = {0}, p1[6] = {0};
+    double sums[kFrameP] = {0};   // K-th moments, then first moments
     for (int64_t i = r0 + threadIdx.x; i < r1; i += kBlock) {
         double vr[3], vi[3];
         for (int j = 0; j < 3; ++j) {
@@ -355,22 +315,15 @@ __global__ __launch_bounds__(kBlock) void k_frame_p(const float* __restrict__ V,
                 wr += vr[a] * ur - vi[a] * ui;
                 wi += vr[a] * ui + vi[a] * ur;
             }
-            p1[2 * b] += wr;
-            p1[2 * b + 1] += wi;
+            sums[6 + 2 * b] += wr;
+            sums[6 + 2 * b + 1] += wi;
             double pr, pim;
             cpow_int(wr, wi, K, pr, pim);
-            pk[2 * b] += pr;
-            pk[2 * b + 1] += pim;
+            sums[2 * b] += pr;
+            sums[2 * b + 1] += pim;
         }
     }
-    for (int e = 0; e < 6; ++e) {
-        const double a = block_sum(pk[e], red);
-        const double b = block_sum(p1[e], red);
-        if (threadIdx.x == 0) {
-            work[((size_t)t * splits + q) * kFrameP + e] = a;
-            work[((size_t)t * splits + q) * kFrameP + 6 + e] = b;
-        }
-    }
+    block_sums<kFrameP>(sums, red, work + ((size_t)t * splits + q) * kFrameP);
 }
 
 __global__ __launch_bounds__(kWave) void k_frame_fin(const double* __restrict__ work, int splits, int K, Frame* __restrict__ frames) {
@@ -453,50 +406,134 @@ struct RowItems {
     int32_t count;
 };
 
-__global__ __launch_bounds__(kBlock) void k_mlp_fwd(const float* __restrict__ V, const int64_t* voff,
-                                                   const int64_t* nrows, const Frame* frames,
-                                                   const float* __restrict__ theta, RowItems items,
-                                                   float* __restrict__ partial /*[items][H]*/) {
-    __shared__ float W1[H * DIN], b1[H], W2[H * H], b2[H];
+// The row network on the matrix core, in FP32 (v_mfma_f32_32x32x2_f32, which
+// adds its two products to the accumulator as two FMAs in k order, so a sum
+// over k is the same FP32 chain as on the vector ALU, bit for bit).  The
+// vector form read every weight from LDS once per row and FMA and was bound by
+// those reads (262,144 rows: 68 us, 354,000 rows of a mini-batch 107 us; now
+// 33 and 46, against 15 and 21 us of matrix-core time).  A wave takes 32 rows as the columns of the products:
+// neurons are rows of the result, and its row 8j + 4h + c (held by lane half
+// h) is neuron 2 (16 m + 4 j + c) + h of block m.  Result register 4j + c of
+// block m is then neuron k = 2s + h, s = 16 m + 4 j + c: exactly the operand
+// that k-step s of the next layer takes from that lane.
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ int neuron_of(int row, int m) {
+    return 2 * (16 * m + 4 * (row >> 3) + (row & 3)) + ((row >> 2) & 1);
+}
+
+// Operands of the first layer: lane l holds row l % 32, k = 2s + l / 32.
+__device__ __forceinline__ void load_w1(const float* __restrict__ theta, int lane, float (&w1)[2][3]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            w1[m][s] = theta[OFF_W1 + neuron_of(lane & 31, m) * DIN + 2 * s + (lane >> 5)];
+}
+
+// Bias of this lane's result registers (b: 64 floats in LDS).
+__device__ __forceinline__ v16f bias_regs(const float* b, int m, int h) {
+    v16f v;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = b[2 * (16 * m + i) + h];
+    return v;
+}
+
+// First layer of 32 rows: h1[m][i] = relu of neuron 2 (16 m + i) + h.
+__device__ __forceinline__ void layer1(const float (&x)[DIN], const float (&w1)[2][3], const float* b1, int h,
+                                       v16f (&h1)[2]) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        v16f a = bias_regs(b1, m, h);
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            a = __builtin_amdgcn_mfma_f32_32x32x2f32(w1[m][s], h ? x[2 * s + 1] : x[2 * s], a, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) h1[m][i] = fmaxf(a[i], 0.0f);
+    }
+}
+
+// Sums of v[q] over each half-wave's 32 lanes; lane l returns that of
+// register l % 32.  At every level a lane keeps the registers whose index has
+// its lane bit and adds the partner's.
+template <int N>
+__device__ __forceinline__ float half_wave_sums(const float (&v)[N], int lane) {
+    if constexpr (N == 1) {
+        return v[0];
+    } else {
+        float u[N / 2];
+#pragma unroll
+        for (int q = 0; q < N / 2; ++q) {
+            const float lo = v[q], hi = v[q + N / 2];
+            const bool up = (lane & (N / 2)) != 0;
+            u[q] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, N / 2, kWave);
+        }
+        return half_wave_sums(u, lane);
+    }
+}
+
+__global__ __launch_bounds__(kBlock, 2) void k_mlp_fwd(const float* __restrict__ V, const int64_t* voff,
+                                                      const int64_t* nrows, const Frame* frames,
+                                                      const float* __restrict__ theta, RowItems items,
+                                                      float* __restrict__ partial /*[items][H]*/) {
+    __shared__ float b1[H], b2[H];
     __shared__ float hs[kBlock / kWave][H];
-    for (int e = threadIdx.x; e < H * DIN; e += kBlock) W1[e] = theta[OFF_W1 + e];
-    for (int e = threadIdx.x; e < H * H; e += kBlock) W2[e] = theta[OFF_W2 + e];
-    for (int e = threadIdx.x; e < H; e += kBlock) {
-        b1[e] = theta[OFF_B1 + e];
-        b2[e] = theta[OFF_B2 + e];
-    }
-    __syncthreads();
-    const int it = blockIdx.x;
-    const int t = items.inst[it];
-    const int64_t i = items.start[it] + threadIdx.x;
-    const int64_t n = nrows[t];
-    const bool live = i < n;
-    float x[DIN], h1[H];
-#pragma unroll
-    for (int k = 0; k < DIN; ++k) x[k] = 0.0f;
-    if (live) feature_row(V + voff[t], i, frames[t], x);
-#pragma unroll
-    for (int o = 0; o < H; ++o) {
-        float a = b1[o];
-#pragma unroll
-        for (int k = 0; k < DIN; ++k) a = fmaf(W1[o * DIN + k], x[k], a);
-        h1[o] = fmaxf(a, 0.0f);
-    }
-    // each output of the second layer is summed over the block as it is made
-    const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    for (int o = 0; o < H; ++o) {
-        float a = b2[o];
-#pragma unroll
-        for (int k = 0; k < H; ++k) a = fmaf(W2[o * H + k], h1[k], a);
-        float v = live ? fmaxf(a, 0.0f) : 0.0f;
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-        if (lane == 0) hs[w][o] = v;
-    }
-    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, h = lane >> 5;
     if (threadIdx.x < H) {
-        float v = 0.0f;
-        for (int q = 0; q < kBlock / kWave; ++q) v += hs[q][threadIdx.x];
-        partial[(size_t)it * H + threadIdx.x] = v;
+        b1[threadIdx.x] = theta[OFF_B1 + threadIdx.x];
+        b2[threadIdx.x] = theta[OFF_B2 + threadIdx.x];
+    }
+    float w1[2][3], w2[2][32];
+    load_w1(theta, lane, w1);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const float4* row = reinterpret_cast<const float4*>(theta + OFF_W2 + neuron_of(lane & 31, m) * H);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const float4 v = row[q];
+            w2[m][2 * q] = h ? v.y : v.x;
+            w2[m][2 * q + 1] = h ? v.w : v.z;
+        }
+    }
+    __syncthreads();
+    for (int it = blockIdx.x; it < items.count; it += gridDim.x) {
+        const int t = items.inst[it];
+        const int64_t n = nrows[t];
+        // a wave's 64 rows in two halves; their sums are added as a butterfly over
+        // 64 lanes would add them (the halves first)
+        float sum[32];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int64_t i = items.start[it] + kWave * w + 32 * half + (lane & 31);
+            const bool live = i < n;
+            float x[DIN];
+#pragma unroll
+            for (int k = 0; k < DIN; ++k) x[k] = 0.0f;
+            if (live) feature_row(V + voff[t], i, frames[t], x);
+            v16f h1[2];
+            layer1(x, w1, b1, h, h1);
+            v16f a[2] = {bias_regs(b2, 0, h), bias_regs(b2, 1, h)};
+#pragma unroll
+            for (int s = 0; s < 32; ++s)
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    a[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(w2[m][s], h1[s / 16][s % 16], a[m], 0, 0, 0);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const float v = live ? fmaxf(a[m][q], 0.0f) : 0.0f;
+                    sum[16 * m + q] = half ? sum[16 * m + q] + v : v;
+                }
+        }
+        hs[w][2 * (lane & 31) + h] = half_wave_sums(sum, lane);
+        __syncthreads();
+        if (threadIdx.x < H) {
+            float v = 0.0f;
+            for (int q = 0; q < kBlock / kWave; ++q) v += hs[q][threadIdx.x];
+            partial[(size_t)it * H + threadIdx.x] = v;
+        }
+        __syncthreads();
     }
 }
 
@@ -546,7 +583,15 @@ struct Mixture {
 __device__ void head(const float* theta, const float* m, Mixture& mx, float* y /*[OUT]*/) {
     for (int o = threadIdx.x; o < OUT; o += blockDim.x) {
         float a = theta[OFF_B3 + o];
-        for (int k = 0; k < H; ++k) a = fmaf(theta[OFF_W3 + o * H + k], m[k], a);
+        const float4* row = reinterpret_cast<const float4*>(theta + OFF_W3 + o * H);
+#pragma unroll 8
+        for (int q = 0; q < H / 4; ++q) {
+            const float4 v = row[q];
+            a = fmaf(v.x, m[4 * q], a);
+            a = fmaf(v.y, m[4 * q + 1], a);
+            a = fmaf(v.z, m[4 * q + 2], a);
+            a = fmaf(v.w, m[4 * q + 3], a);
+        }
         y[o] = a;
     }
     __syncthreads();
@@ -562,13 +607,16 @@ __device__ void head(const float* theta, const float* m, Mixture& mx, float* y /
         mx.logc[k] = log_vmf_norm(kap);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float amax = -INFINITY;
-        for (int k = 0; k < NC; ++k) amax = fmaxf(amax, y[k * (DIN + 2) + DIN]);
+    if (threadIdx.x < kWave) {   // log-softmax of the logits, terms added in component order
+        const float a = threadIdx.x < NC ? y[threadIdx.x * (DIN + 2) + DIN] : -INFINITY;
+        float amax = a;
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, kWave));
+        const float e = expf(a - amax);
         float se = 0.0f;
-        for (int k = 0; k < NC; ++k) se += expf(y[k * (DIN + 2) + DIN] - amax);
-        const float lse = amax + logf(se);
-        for (int k = 0; k < NC; ++k) mx.logpi[k] = y[k * (DIN + 2) + DIN] - lse;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) se += __shfl(e, k, kWave);
+        if (threadIdx.x < NC) mx.logpi[threadIdx.x] = a - (amax + logf(se));
     }
     __syncthreads();
 }
@@ -603,15 +651,28 @@ __global__ __launch_bounds__(kBlock) void k_head_loss(const float* __restrict__ 
         lg[r][k] = mx.logpi[k] + mx.logc[k] + mx.kappa[k] * dot;
     }
     __syncthreads();
-    __shared__ float lse_s;
+    // log-sum-exp over all entries: thread maxima and sums, then over the block
+    __shared__ float lse_s, wred[kBlock / kWave];
+    const int wv = threadIdx.x / kWave;
+    float mxv = -INFINITY;
+    for (int e = threadIdx.x; e < K * NC; e += kBlock) mxv = fmaxf(mxv, lg[e / NC][e % NC]);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) mxv = fmaxf(mxv, __shfl_xor(mxv, off, kWave));
+    if ((threadIdx.x & (kWave - 1)) == 0) wred[wv] = mxv;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kBlock / kWave; ++q) mxv = fmaxf(mxv, wred[q]);
+    __syncthreads();
+    float se = 0.0f;
+    for (int e = threadIdx.x; e < K * NC; e += kBlock) se += expf(lg[e / NC][e % NC] - mxv);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) se += __shfl_xor(se, off, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) wred[wv] = se;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        float mxv = -INFINITY;
-        for (int r = 0; r < K; ++r)
-            for (int k = 0; k < NC; ++k) mxv = fmaxf(mxv, lg[r][k]);
-        float se = 0.0f;
-        for (int r = 0; r < K; ++r)
-            for (int k = 0; k < NC; ++k) se += expf(lg[r][k] - mxv);
-        lse_s = mxv + logf(se);
+        float tot = 0.0f;
+        for (int q = 0; q < kBlock / kWave; ++q) tot += wred[q];
+        lse_s = mxv + logf(tot);
         loss[t] = -(lse_s - logf((float)K));
     }
     __syncthreads();
@@ -659,118 +720,215 @@ __global__ __launch_bounds__(kBlock) void k_head_loss(const float* __restrict__ 
     }
 }
 
-// Row backward: item j covers kRowTile rows of one instance; gradients of
-// W1, b1, W2, b2 over those rows into partial[j][...] (H*DIN + H + H*H + H).
-__global__ __launch_bounds__(kBlock) void k_mlp_bwd(const float* __restrict__ V, const int64_t* voff,
-                                                   const int64_t* nrows, const Frame* frames,
-                                                   const float* __restrict__ theta,
-                                                   const float* __restrict__ dmvec, RowItems items,
-                                                   float* __restrict__ partial) {
-    constexpr int NG = H * DIN + H + H * H + H;
-    __shared__ float W1[H * DIN], b1[H], W2[H * H], b2[H];
-    // rows padded to H + 1 floats: lanes that hold different rows of one
-    // column fall in different LDS banks
-    __shared__ float X[kRowTile][DIN + 1], A1[kRowTile][H + 1], D2[kRowTile][H + 1], D1[kRowTile][H + 1];
-    __shared__ float dh2[H];
-    for (int e = threadIdx.x; e < H * DIN; e += kBlock) W1[e] = theta[OFF_W1 + e];
-    for (int e = threadIdx.x; e < H * H; e += kBlock) W2[e] = theta[OFF_W2 + e];
-    const int it = blockIdx.x;
-    const int t = items.inst[it];
-    const int64_t n = nrows[t];
-    for (int e = threadIdx.x; e < H; e += kBlock) {
-        b1[e] = theta[OFF_B1 + e];
-        b2[e] = theta[OFF_B2 + e];
-        dh2[e] = dmvec[(size_t)t * H + e] / (float)n;   // mean pooling
+// Row backward.  A wave takes tiles of kRowTile = 32 rows (a contiguous run of
+// the tile list) and keeps the weight gradients of all of them in registers;
+// the eight waves of a block are added once at the end into partial[block].
+// All three products run on the matrix core in FP32 like the forward pass:
+//   layer 2 (recomputed) and D1 = W2^T D2 (* relu'): operands straight from the
+//     previous product's registers, weights in lane order in LDS;
+//   dW2 = D2 A1^T over the rows: D2 is relu' times one value per neuron, so its
+//     operand is that value masked by a bit of the neuron's row mask (the
+//     ballots of the signs); A1 is turned through LDS.
+// dW1 and db1 (six columns) are vector FMAs, lane = neuron.  The vector form
+// read two LDS operands per FMA and wrote 18 KB of partial sums per 64 rows
+// (mini-batch of 354,000 rows: 453 us, now 114; the reduction of the partials
+// 32 -> 5 us); its FP32 products take 62 us at the matrix-core rate.
+constexpr int kBwdBlock = 512, kBwdWaves = kBwdBlock / kWave;
+constexpr int kBwdBlocks = 256;            // one block per CU (102 KB of LDS)
+constexpr int NG = H * DIN + H + H * H + H;
+
+struct BwdLds {
+    float4 wf[2][8][kWave], wb[2][8][kWave];   // operands of layer 2 and of D1: [block][step / 4][lane]
+    float a[kBwdWaves][kRowTile][H + 1];       // A1, then D1 of a wave's tile
+    float x[kBwdWaves][kRowTile][8];           // features
+    unsigned mask[kBwdWaves][H];               // row masks of the neurons of layer 2
+    float dh[kBwdWaves][H];                    // d loss / d h2 of the wave's instance
+    float b1[H], b2[H];
+};
+static_assert(sizeof(BwdLds) <= 160 * 1024, "one block per CU");
+
+// Compiler fence between LDS writes and reads of other lanes of the same wave
+// (the LDS serves a wave's accesses in order).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__global__ __launch_bounds__(kBwdBlock, 2) void k_mlp_bwd(const float* __restrict__ V, const int64_t* voff,
+                                                         const int64_t* nrows, const Frame* frames,
+                                                         const float* __restrict__ theta,
+                                                         const float* __restrict__ dmvec, RowItems items, int per_wave,
+                                                         float* __restrict__ partial) {
+    __shared__ BwdLds L;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave, h = lane >> 5, col = lane & 31;
+    for (int e = tid; e < 2 * 8 * kWave; e += kBwdBlock) {
+        const int l = e & (kWave - 1), q = (e / kWave) & 7, m = e / (8 * kWave), o = neuron_of(l & 31, m);
+        float f[4], g[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int k = 2 * (4 * q + c) + (l >> 5);
+            f[c] = theta[OFF_W2 + o * H + k];          // layer 2: rows are neurons, k-step s is input 2s + h
+            g[c] = theta[OFF_W2 + k * H + o];          // D1: rows are inputs, k-step s is neuron 2s + h
+        }
+        L.wf[m][q][l] = make_float4(f[0], f[1], f[2], f[3]);
+        L.wb[m][q][l] = make_float4(g[0], g[1], g[2], g[3]);
     }
+    if (tid < H) {
+        L.b1[tid] = theta[OFF_B1 + tid];
+        L.b2[tid] = theta[OFF_B2 + tid];
+    }
+    float w1[2][3];
+    load_w1(theta, lane, w1);
     __syncthreads();
-    const int64_t i0 = items.start[it];
-    // forward recompute and d pre-activations: thread (row rr = lane, part =
-    // wave) takes neurons 16 part .. 16 part + 15 of each layer
-    constexpr int HP = H / (kBlock / kWave);
-    const int rr = threadIdx.x & (kWave - 1), o0 = (threadIdx.x / kWave) * HP;
-    const int64_t i = i0 + rr;
-    const bool live = i < n;
-    {
+
+    v16f gw2[2][2];                            // dW2: neurons 32 M .., inputs 32 N ..
+    float gw1[DIN], gb1 = 0.0f, gb2[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int M = 0; M < 2; ++M)
+#pragma unroll
+        for (int N = 0; N < 2; ++N)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) gw2[M][N][i] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < DIN; ++k) gw1[k] = 0.0f;
+
+    // a += weights (LDS, lane order) times the registers of a previous product
+    auto product = [&](const float4 (&wt)[2][8][kWave], const v16f (&in)[2], v16f (&a)[2]) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float4 w0 = wt[0][q][lane], w1q = wt[1][q][lane];
+            const float wv[2][4] = {{w0.x, w0.y, w0.z, w0.w}, {w1q.x, w1q.y, w1q.z, w1q.w}};
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+                    a[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[m][c], in[q / 4][4 * (q % 4) + c], a[m], 0, 0, 0);
+        }
+    };
+    const int it0 = (blockIdx.x * kBwdWaves + w) * per_wave, it1 = min(items.count, it0 + per_wave);
+    int cur = -1;
+    float dl[2] = {0.0f, 0.0f};                // d loss / d h2 of neurons col and 32 + col
+    for (int it = it0; it < it1; ++it) {
+        const int t = __builtin_amdgcn_readfirstlane(items.inst[it]);
+        const int64_t n = nrows[t];
+        if (t != cur) {
+            cur = t;
+            wave_fence();
+            L.dh[w][lane] = dmvec[(size_t)t * H + lane] / (float)n;   // mean pooling
+            wave_fence();
+            dl[0] = L.dh[w][col];
+            dl[1] = L.dh[w][32 + col];
+        }
+        const int64_t i = items.start[it] + col;
+        const bool live = i < n;
         float x[DIN];
 #pragma unroll
         for (int k = 0; k < DIN; ++k) x[k] = 0.0f;
         if (live) feature_row(V + voff[t], i, frames[t], x);
-        if (o0 == 0) {
+        if (h == 0) {
 #pragma unroll
-            for (int k = 0; k < DIN; ++k) X[rr][k] = x[k];
+            for (int k = 0; k < DIN; ++k) L.x[w][col][k] = x[k];
+        }
+        v16f h1[2], d2[2];
+        layer1(x, w1, L.b1, h, h1);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                h1[m][q] = live ? h1[m][q] : 0.0f;
+                L.a[w][col][2 * (16 * m + q) + h] = h1[m][q];
+            }
+        v16f a[2] = {bias_regs(L.b2, 0, h), bias_regs(L.b2, 1, h)};
+        product(L.wf, h1, a);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const bool on = live && a[m][q] > 0.0f;
+                const unsigned long long rows = __ballot(on);   // low half: neuron 2s, high half: 2s + 1
+                L.mask[w][2 * (16 * m + q) + h] = h ? (unsigned)(rows >> 32) : (unsigned)rows;
+                d2[m][q] = on ? L.dh[w][2 * (16 * m + q) + h] : 0.0f;
+            }
+        }
+        wave_fence();
+        // dW2 and db2
+        unsigned bits[2];
+#pragma unroll
+        for (int M = 0; M < 2; ++M) {
+            bits[M] = L.mask[w][32 * M + col];
+            gb2[M] = fmaf((float)__popc(bits[M]), dl[M], gb2[M]);
+            bits[M] >>= h;
         }
 #pragma unroll
-        for (int oo = 0; oo < HP; ++oo) {
-            const int o = o0 + oo;
-            float a = b1[o];
+        for (int s = 0; s < kRowTile / 2; ++s) {        // rows 2s, 2s + 1
+            float dv[2], av[2];
 #pragma unroll
-            for (int k = 0; k < DIN; ++k) a = fmaf(W1[o * DIN + k], x[k], a);
-            A1[rr][o] = live ? fmaxf(a, 0.0f) : 0.0f;
-        }
-    }
-    __syncthreads();
-    for (int oo = 0; oo < HP; ++oo) {
-        const int o = o0 + oo;
-        float a = b2[o];
-#pragma unroll 16
-        for (int k = 0; k < H; ++k) a = fmaf(W2[o * H + k], A1[rr][k], a);
-        D2[rr][o] = (live && a > 0.0f) ? dh2[o] : 0.0f;
-    }
-    __syncthreads();
-    for (int kk = 0; kk < HP; ++kk) {
-        const int k = o0 + kk;
-        float a = 0.0f;
-#pragma unroll 16
-        for (int o = 0; o < H; ++o) a = fmaf(W2[o * H + k], D2[rr][o], a);
-        D1[rr][k] = A1[rr][k] > 0.0f ? a : 0.0f;
-    }
-    __syncthreads();
-    // weight gradients over the tile's rows, each entry summed over the rows
-    // in order.  dW2[o][k] = sum_r D2[r][o] A1[r][k]: thread (to, tk) of a
-    // 16 x 16 grid owns the 4 x 4 block o in 4to.., k in 4tk.. (eight LDS
-    // reads per sixteen FMAs)
-    float* out = partial + (size_t)it * NG;
-    static_assert(kBlock == 256 && H == 64, "the dW2 tiling assumes 256 threads and H = 64");
-    {
-        const int to = threadIdx.x / 16, tk = threadIdx.x % 16;
-        float acc[4][4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] = 0.0f;
-        for (int r = 0; r < kRowTile; ++r) {
-            float d[4], h[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                d[a] = D2[r][4 * to + a];
-                h[a] = A1[r][4 * tk + a];
+            for (int M = 0; M < 2; ++M) {
+                const int on = ((int)(bits[M] << (31 - 2 * s))) >> 31;
+                dv[M] = __int_as_float(__float_as_int(dl[M]) & on);
+                av[M] = L.a[w][2 * s + h][32 * M + col];
             }
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int M = 0; M < 2; ++M)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = fmaf(d[a], h[b], acc[a][b]);
+                for (int N = 0; N < 2; ++N)
+                    gw2[M][N] = __builtin_amdgcn_mfma_f32_32x32x2f32(dv[M], av[N], gw2[M][N], 0, 0, 0);
         }
+        wave_fence();
+        // D1 over A1's place
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) out[H * DIN + H + (4 * to + a) * H + 4 * tk + b] = acc[a][b];
+            for (int q = 0; q < 16; ++q) a[m][q] = 0.0f;
+        product(L.wb, d2, a);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) L.a[w][col][2 * (16 * m + q) + h] = h1[m][q] > 0.0f ? a[m][q] : 0.0f;
+        wave_fence();
+        // dW1, db1: lane = neuron
+#pragma unroll 4
+        for (int r = 0; r < kRowTile; ++r) {
+            const float d = L.a[w][r][lane];
+            gb1 += d;
+#pragma unroll
+            for (int k = 0; k < DIN; ++k) gw1[k] = fmaf(d, L.x[w][r][k], gw1[k]);
+        }
+        wave_fence();
     }
-    // dW1, db1 and db2: thread e owns entries e, e + 256 of those 512
-    for (int e = threadIdx.x; e < H * DIN + 2 * H; e += kBlock) {
-        float a = 0.0f;
-        if (e < H * DIN) {                       // dW1[o][k] = sum_r D1[r][o] X[r][k]
-            const int o = e / DIN, k = e % DIN;
-            for (int r = 0; r < kRowTile; ++r) a = fmaf(D1[r][o], X[r][k], a);
-            out[e] = a;
-        } else if (e < H * DIN + H) {            // db1
-            const int o = e - H * DIN;
-            for (int r = 0; r < kRowTile; ++r) a += D1[r][o];
-            out[e] = a;
-        } else {                                 // db2
-            const int o = e - H * DIN - H;
-            for (int r = 0; r < kRowTile; ++r) a += D2[r][o];
-            out[H * DIN + H + H * H + o] = a;
-        }
+
+    // the block's waves: half of them at a time hand their sums to the others
+    static_assert(sizeof(float) * NG * (kBwdWaves / 2) <= sizeof(BwdLds), "wave sums fit");
+    float* hand = reinterpret_cast<float*>(&L);
+    auto each = [&](auto f) {                  // (entry of partial, register, held by this lane)
+#pragma unroll
+        for (int M = 0; M < 2; ++M)
+#pragma unroll
+            for (int N = 0; N < 2; ++N)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const int o = 32 * M + 8 * (q / 4) + 4 * h + q % 4;
+                    float v = gw2[M][N][q];
+                    f(H * DIN + H + o * H + 32 * N + col, v, true);
+                    gw2[M][N][q] = v;
+                }
+#pragma unroll
+        for (int k = 0; k < DIN; ++k) f(lane * DIN + k, gw1[k], true);
+        f(H * DIN + lane, gb1, true);
+#pragma unroll
+        for (int M = 0; M < 2; ++M) f(H * DIN + H + H * H + 32 * M + col, gb2[M], h == 0);
+    };
+    for (int half = kBwdWaves / 2; half > 0; half >>= 1) {
+        __syncthreads();
+        if (w >= half && w < 2 * half)
+            each([&](int e, float& v, bool mine) { if (mine) hand[(w - half) * NG + e] = v; });
+        __syncthreads();
+        if (w < half)
+            each([&](int e, float& v, bool mine) { if (mine) v += hand[w * NG + e]; });
+    }
+    if (w == 0) {
+        float* out = partial + (size_t)blockIdx.x * NG;
+        each([&](int e, float& v, bool mine) { if (mine) out[e] = v; });
     }
 }
 
@@ -784,7 +942,6 @@ constexpr int kGradChunks = 64;
 __global__ void k_grad_partial(const float* __restrict__ mlp_partial, int nitems,
                                const float* __restrict__ head_partial, int count,
                                float* __restrict__ gpart) {
-    constexpr int NG = H * DIN + H + H * H + H;
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     const int c = blockIdx.y;
     if (p >= NP) return;
@@ -1050,7 +1207,8 @@ lrqo_status run_embed(lrqo_proposal* P, const float* V, int count, const RowPlan
     launch_frames(V, b.voff, b.n, count, b.fsplits, P->K, b.frames, b.fwork, st);
     LRQO_HIP(hipGetLastError());
     RowItems items{b.inst, b.start, (int32_t)rp.inst.size()};
-    hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)rp.inst.size()), dim3(kBlock), 0, st, V, b.voff, b.n,
+    // two blocks a CU (174 VGPRs), which keep the weights for all their items
+    hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)std::min<size_t>(rp.inst.size(), 512)), dim3(kBlock), 0, st, V, b.voff, b.n,
                        b.frames, P->theta, items, b.partial);
     LRQO_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_pool, dim3(count), dim3(H * kPoolGroups), 0, st, b.partial, b.first, b.n, count, b.mvec);
@@ -1142,7 +1300,10 @@ lrqo_status lrqo_proposal_train_step(lrqo_proposal* P, const float* V, int32_t c
     RowPlan fp, bp;
     plan_rows(count, n, kBlock, fp);
     plan_rows(count, n, kRowTile, bp);
-    constexpr int NG = H * DIN + H + H * H + H;
+    // tiles of a wave and blocks of the backward pass
+    const int tiles = (int)bp.inst.size();
+    const int per_wave = (tiles + kBwdBlocks * kBwdWaves - 1) / (kBwdBlocks * kBwdWaves);
+    const int bwd_blocks = (tiles + per_wave * kBwdWaves - 1) / (per_wave * kBwdWaves);
     CarveSize cs;
     cs.add<int64_t>(count);                  // uploaded: offsets, sizes,
     cs.add<int64_t>(count);
@@ -1159,7 +1320,7 @@ lrqo_status lrqo_proposal_train_step(lrqo_proposal* P, const float* V, int32_t c
     cs.add<float>((size_t)count * 6);        // canonical targets
     cs.add<float>(count);                    // loss
     cs.add<float>((size_t)count * (OUT * H + OUT));
-    cs.add<float>(bp.inst.size() * NG);
+    cs.add<float>((size_t)bwd_blocks * NG);
     cs.add<float>((size_t)kGradChunks * NP);
     const int fsplits = frame_splits(count, *std::max_element(n, n + count));
     cs.add<double>(frame_work(count, fsplits));
@@ -1182,7 +1343,7 @@ lrqo_status lrqo_proposal_train_step(lrqo_proposal* P, const float* V, int32_t c
     float* tcan = cv.take<float>((size_t)count * 6);
     float* loss = cv.take<float>(count);
     float* headp = cv.take<float>((size_t)count * (OUT * H + OUT));
-    float* mlpp = cv.take<float>(bp.inst.size() * NG);
+    float* mlpp = cv.take<float>((size_t)bwd_blocks * NG);
     float* gpart = cv.take<float>((size_t)kGradChunks * NP);
     b.fwork = cv.take<double>(frame_work(count, fsplits));
     b.fsplits = fsplits;
@@ -1193,11 +1354,11 @@ lrqo_status lrqo_proposal_train_step(lrqo_proposal* P, const float* V, int32_t c
     hipLaunchKernelGGL(k_head_loss, dim3(count), dim3(kBlock), 0, st, P->theta, b.mvec, tcan, P->K, loss, dm, headp);
     LRQO_HIP(hipGetLastError());
     RowItems items{inst_b, start_b, (int32_t)bp.inst.size()};
-    hipLaunchKernelGGL(k_mlp_bwd, dim3((unsigned)bp.inst.size()), dim3(kBlock), 0, st, V, b.voff, b.n, b.frames,
-                       P->theta, dm, items, mlpp);
+    hipLaunchKernelGGL(k_mlp_bwd, dim3((unsigned)bwd_blocks), dim3(kBwdBlock), 0, st, V, b.voff, b.n,
+                       b.frames, P->theta, dm, items, per_wave, mlpp);
     LRQO_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_grad_partial, dim3((NP + 255) / 256, kGradChunks), dim3(256), 0, st, mlpp,
-                       (int)bp.inst.size(), headp, count, gpart);
+                       bwd_blocks, headp, count, gpart);
     hipLaunchKernelGGL(k_grad_reduce, dim3((NP + 255) / 256), dim3(256), 0, st, gpart, count, P->grad);
     LRQO_HIP(hipGetLastError());
     if (update) {
