@@ -17,10 +17,18 @@
 // Per Lanczos step j (basis columns q_0..q_j in HBM, column-major):
 //   w = A q_j; h = Q^H w (alpha_j = Re h_j); w -= Q h; a second pass of the
 //   same (classical Gram-Schmidt, twice); beta_j = ||w||; q_{j+1} = w/beta_j.
-// alpha and beta are written on the device; the host reads them only at the
-// checks.  Every check interval one block finds the r largest eigenvalues of the
-// tridiagonal T_j by Sturm bisection and their vectors by inverse iteration;
-// |beta_j s_{j,k}| bounds the residual of Ritz pair k.  At convergence the
+// The steps between products are fused to five launches: scaling by 1/beta
+// with the product (Laplacian) or with U^H q (phase sync), and per
+// Gram-Schmidt pass the partial dots and an update whose blocks add the
+// partials themselves; the second update also leaves the partial squares of
+// beta.  (Ten launches and a wait for each check took 152 us a step at
+// n = 100,000, 106 us of them in kernels.)
+// alpha and beta stay on the device.  Every check interval one block finds
+// the r largest eigenvalues of the tridiagonal T_j by Sturm bisection and
+// their vectors by inverse iteration; |beta_j s_{j,k}| bounds the residual of
+// Ritz pair k.  The check runs on a stream of its own while the next step is
+// computed, and the host reads its verdict before it launches the step after
+// that; at convergence that one step is left unused.  At convergence the
 // Ritz vectors U = Q S are formed, each is rotated so that its
 // largest-modulus entry is real positive, and scaled by sqrt(max(theta, 0)).
 // All sums are fixed-order.
@@ -28,6 +36,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "graph_internal.h"
@@ -76,11 +85,11 @@ struct LapOp {
 };
 
 // The entries [e, e1) of a row in chunks of U: the U column and weight
-// loads, then the U gathers of x, are issued together; the additions keep
-// entry order.  Leaves e at the first entry of an incomplete chunk.
+// loads, then the U gathers of x (scaled by inv), are issued together; the
+// additions keep entry order.  Leaves e at the first entry of an incomplete chunk.
 template <int U>
-__device__ __forceinline__ void lap_chunk(const LapOp& g, const double2* __restrict__ x, int64_t& e, int64_t e1,
-                                          double& ar, double& ai, double& deg) {
+__device__ __forceinline__ void lap_chunk(const LapOp& g, const double2* __restrict__ x, double inv, int64_t& e,
+                                          int64_t e1, double& ar, double& ai, double& deg) {
     for (; e + U <= e1; e += U) {
         int32_t c[U];
         double w[U];
@@ -94,28 +103,47 @@ __device__ __forceinline__ void lap_chunk(const LapOp& g, const double2* __restr
         for (int u = 0; u < U; ++u) xj[u] = x[c[u]];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            ar += w[u] * xj[u].x;
-            ai += w[u] * xj[u].y;
+            ar += w[u] * (xj[u].x * inv);
+            ai += w[u] * (xj[u].y * inv);
             deg += w[u];
         }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_apply_lap(LapOp g, const double2* __restrict__ x, double2* __restrict__ y) {
+// beta = sqrt of the sum of the partial squares, in every thread: each wave
+// adds them all (lanes strided, then a butterfly: the same sum everywhere).
+__device__ __forceinline__ double beta_of(const double* __restrict__ part, int count) {
+    double a = 0.0;
+    for (int t = threadIdx.x & (kWave - 1); t < count; t += kWave) a += part[t];
+    return sqrt(wave_sum_f64(a));
+}
+
+// q = w / beta (stored) and y = L q, gathering w and scaling on the fly;
+// block 0 writes beta.  A zero vector (breakdown, found at the next check)
+// stays zero.
+__global__ __launch_bounds__(kBlock) void k_apply_lap(LapOp g, const double2* __restrict__ w,
+                                                      const double* __restrict__ npart, int nparts,
+                                                      double2* __restrict__ q, double2* __restrict__ y,
+                                                      double* __restrict__ beta) {
+    const double nrm = beta_of(npart, nparts);
+    const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+    if (beta && blockIdx.x == 0 && threadIdx.x == 0) beta[0] = nrm;
     const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
     if (i >= g.n) return;
-    const double2 xi = x[i];
+    const double2 wi = w[i];
+    const double2 xi = make_double2(wi.x * inv, wi.y * inv);
+    q[i] = xi;
     double ar = 0.0, ai = 0.0, deg = 0.0;
     int64_t e = g.row_ptr[i];
     const int64_t e1 = g.row_ptr[i + 1];
-    lap_chunk<8>(g, x, e, e1, ar, ai, deg);
-    lap_chunk<4>(g, x, e, e1, ar, ai, deg);
+    lap_chunk<8>(g, w, inv, e, e1, ar, ai, deg);
+    lap_chunk<4>(g, w, inv, e, e1, ar, ai, deg);
     for (; e < e1; ++e) {
-        const double w = g.w ? g.w[e] : 1.0;
-        const double2 xj = x[g.col[e]];
-        ar += w * xj.x;
-        ai += w * xj.y;
-        deg += w;
+        const double we = g.w ? g.w[e] : 1.0;
+        const double2 xj = w[g.col[e]];
+        ar += we * (xj.x * inv);
+        ai += we * (xj.y * inv);
+        deg += we;
     }
     y[i] = make_double2(deg * xi.x - ar, deg * xi.y - ai);
 }
@@ -164,12 +192,19 @@ __device__ __forceinline__ void w_use(float2 e, double2 xj, double2 xi, double& 
 // Symmetric form of sigma W x: every entry of the upper triangle is
 // generated once and used for its row and, conjugated, for its column.
 // Rows come in stripes of kSymT = 256 (one block); a work item is stripe I
-// against a chunk of up to kSymChunk column stripes J >= I.  Columns are
+// against a chunk of up to `chunk` column stripes J >= I.  Columns are
 // taken in pairs (2q, 2q + 1), the two entries of one Philox call.  Lane l
 // of wave w (row I*256 + 64w + l) visits pair (l + s) mod 128 of tile J at
 // step s, so the 64 lanes of a wave touch 128 different columns at every
 // step and each wave adds its column contributions into its own LDS row of
 // cacc in a fixed order; the four waves' sums are added in wave order.
+// x_j and the column sums of even and odd columns lie in arrays of their own,
+// so that lanes read consecutive 16 B (n = 32,768: 0.95 -> 0.93 ms a product).
+// Two rows a thread, which halves the LDS traffic, ran slower (1.13 ms: 90
+// VGPRs, five waves a SIMD).  The loop's vector instructions (per pair of
+// entries 16 64-bit integer multiply-adds, 30 exclusive-ors, 16 FP64 FMAs, 8
+// transcendentals: about 350 issue cycles) take 0.62 ms of the 0.77 ms that a
+// product takes with items sized as in lanczos_factor.
 // Tiles off the diagonal and inside the matrix need no per-entry test.
 // Outputs:
 //   rowpart[item][t]        row sums of the item's tiles
@@ -178,15 +213,15 @@ __device__ __forceinline__ void w_use(float2 e, double2 xj, double2 xi, double& 
 // column sums of the tiles (I', I), I' <= I, in that order.
 constexpr int kSymT = 256;
 constexpr int kSymPairs = kSymT / 2;
-constexpr int kSymChunk = 8;
+constexpr int kSymChunk = 8;          // tiles of an item, at most
 
 __device__ __forceinline__ int64_t tri_index(int64_t J, int64_t I) { return J * (J + 1) / 2 + I; }
 
 __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __restrict__ x,
-                                                   const int2* __restrict__ items, int64_t P,
+                                                   const int2* __restrict__ items, int64_t P, int chunk,
                                                    double2* __restrict__ rowpart, double2* __restrict__ colpart) {
-    __shared__ double2 xs[kSymT];
-    __shared__ double2 cacc[kSymT / kWave][kSymT];
+    __shared__ double2 xs[2][kSymPairs];                       // [column parity][pair]
+    __shared__ double2 cacc[kSymT / kWave][2][kSymPairs];
     const int2 item = items[blockIdx.x];
     const int64_t I = item.x;
     const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
@@ -196,13 +231,13 @@ __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __r
     const uint32_t k0 = static_cast<uint32_t>(o.seed), k1 = static_cast<uint32_t>(o.seed >> 32);
     const double2 xi = live ? x[i] : make_double2(0.0, 0.0);
     double ar = 0.0, ai = 0.0;
-    const int64_t J0 = I + (int64_t)item.y * kSymChunk, J1 = min(P, J0 + kSymChunk);
+    const int64_t J0 = I + (int64_t)item.y * chunk, J1 = min(P, J0 + chunk);
     for (int64_t J = J0; J < J1; ++J) {
         __syncthreads();
         const int64_t jt = J * kSymT + t;
-        xs[t] = jt < o.n ? x[jt] : make_double2(0.0, 0.0);
+        xs[t & 1][t >> 1] = jt < o.n ? x[jt] : make_double2(0.0, 0.0);
 #pragma unroll
-        for (int v = 0; v < kSymT / kWave; ++v) cacc[v][t] = make_double2(0.0, 0.0);
+        for (int v = 0; v < kSymT / kWave; ++v) cacc[v][t & 1][t >> 1] = make_double2(0.0, 0.0);
         __syncthreads();
         const uint32_t qbase = static_cast<uint32_t>(J * kSymPairs);
         if (J != I && (J + 1) * kSymT <= o.n) {
@@ -211,11 +246,11 @@ __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __r
             for (int st = 0; st < kSymPairs; ++st) {
                 const int q = (lane + st) & (kSymPairs - 1);
                 const U4 h = philox4x32_10(U4{iu, qbase + q, kWStream, 0u}, k0, k1);
-                double2 c0 = cacc[wv][2 * q], c1 = cacc[wv][2 * q + 1];
-                w_use(w_off(h.x, h.y), xs[2 * q], xi, ar, ai, c0);
-                w_use(w_off(h.z, h.w), xs[2 * q + 1], xi, ar, ai, c1);
-                cacc[wv][2 * q] = c0;
-                cacc[wv][2 * q + 1] = c1;
+                double2 c0 = cacc[wv][0][q], c1 = cacc[wv][1][q];
+                w_use(w_off(h.x, h.y), xs[0][q], xi, ar, ai, c0);
+                w_use(w_off(h.z, h.w), xs[1][q], xi, ar, ai, c1);
+                cacc[wv][0][q] = c0;
+                cacc[wv][1][q] = c1;
                 // the next step's lane l reads the pair lane l+1 wrote now
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
@@ -232,15 +267,15 @@ __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __r
                         const int64_t j = j0 + e;
                         if (j < i || j >= o.n) continue;
                         const uint32_t a = e ? h.z : h.x, b = e ? h.w : h.y;
-                        const double2 xj = xs[2 * q + e];
+                        const double2 xj = xs[e][q];
                         if (j == i) {
                             const double d = (double)w_diag(a, b);
                             ar = __builtin_fma(d, xj.x, ar);
                             ai = __builtin_fma(d, xj.y, ai);
                         } else {
-                            double2 c = cacc[wv][2 * q + e];
+                            double2 c = cacc[wv][e][q];
                             w_use(w_off(a, b), xj, xi, ar, ai, c);
-                            cacc[wv][2 * q + e] = c;
+                            cacc[wv][e][q] = c;
                         }
                     }
                 }
@@ -249,11 +284,11 @@ __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __r
             }
         }
         __syncthreads();
-        double2 cs = cacc[0][t];
+        double2 cs = cacc[0][t & 1][t >> 1];
 #pragma unroll
         for (int v = 1; v < kSymT / kWave; ++v) {
-            cs.x += cacc[v][t].x;
-            cs.y += cacc[v][t].y;
+            cs.x += cacc[v][t & 1][t >> 1].x;
+            cs.y += cacc[v][t & 1][t >> 1].y;
         }
         colpart[tri_index(J, I) * kSymT + t] = cs;
     }
@@ -262,25 +297,48 @@ __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __r
 
 // y_i = sum_k U_ik c_k + sigma (row sums of the items of stripe I + column
 // sums of tiles (I', I), I' <= I); item_first[I] = first item of stripe I.
-__global__ __launch_bounds__(kSymT) void k_w_combine(PhaseOp o, const double2* __restrict__ c,
+__global__ __launch_bounds__(kSymT) void k_w_combine(PhaseOp o, const double2* __restrict__ upart, int unb,
                                                      const int32_t* __restrict__ item_first, int64_t P,
                                                      const double2* __restrict__ rowpart,
                                                      const double2* __restrict__ colpart, double2* __restrict__ y) {
+    __shared__ double2 c[LRQO_MAX_R];
     const int64_t I = blockIdx.x;
     const int t = threadIdx.x;
     const int64_t i = I * kSymT + t;
+    for (int k = t / kWave; k < o.p; k += kSymT / kWave) {    // U^H x from its partials, one wave per column
+        double cr = 0.0, ci = 0.0;
+        for (int b = t & (kWave - 1); b < unb; b += kWave) {
+            const double2 v = upart[(int64_t)k * unb + b];
+            cr += v.x;
+            ci += v.y;
+        }
+        cr = wave_sum_f64(cr);
+        ci = wave_sum_f64(ci);
+        if ((t & (kWave - 1)) == 0) c[k] = make_double2(cr, ci);
+    }
+    __syncthreads();
     if (i >= o.n) return;
     double ar = 0.0, ai = 0.0;
-    for (int32_t it = item_first[I]; it < item_first[I + 1]; ++it) {
-        const double2 v = rowpart[(int64_t)it * kSymT + t];
-        ar += v.x;
-        ai += v.y;
-    }
-    for (int64_t Ip = 0; Ip <= I; ++Ip) {
-        const double2 v = colpart[tri_index(I, Ip) * kSymT + t];
-        ar += v.x;
-        ai += v.y;
-    }
+    // both lists are contiguous in memory; sixteen loads in flight, sums in order
+    auto add = [&](const double2* __restrict__ src, int64_t count) {
+        int64_t q = 0;
+        for (; q + 16 <= count; q += 16) {
+            double2 v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = src[(q + u) * kSymT];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                ar += v[u].x;
+                ai += v[u].y;
+            }
+        }
+        for (; q < count; ++q) {
+            ar += src[q * kSymT].x;
+            ai += src[q * kSymT].y;
+        }
+    };
+    add(rowpart + (int64_t)item_first[I] * kSymT + t, item_first[I + 1] - item_first[I]);
+    add(colpart + tri_index(I, 0) * kSymT + t, I + 1);
     double yr = o.sigma * ar, yi = o.sigma * ai;
     for (int k = 0; k < o.p; ++k) {
         const double2 u = cmul(o.U[i * o.p + k], c[k]);
@@ -294,19 +352,31 @@ __global__ __launch_bounds__(kSymT) void k_w_combine(PhaseOp o, const double2* _
 // ---------------------------------------------------------------- basis algebra
 // h_j = q_j^H w for j < k in two fixed-order stages.  Block (b, c) takes
 // rows [b rows, (b + 1) rows) of columns kDotCols c .. kDotCols c + 7 (rows a
-// multiple of 256, sized on the host for at least 256 row chunks up to 4096):
-// each thread sums its rows (two rows' loads in flight), the 16 sums of a
-// wave are added by a transposing butterfly (each exchange halves the
-// values a lane holds: 17 shuffles instead of 16 x 6) and the four waves in
-// order, giving part[j nb + b]; k_part_sum then adds the nb partials of
-// column j (lanes strided, then butterfly).  Q is read once, by as many
-// blocks as there are row chunks times column groups.
+// multiple of 256): each thread sums its rows (two rows' loads in flight), the
+// 16 sums of a wave are added by a transposing butterfly (each exchange halves
+// the values a lane holds: 17 shuffles instead of 16 x 6) and the four waves in
+// order, giving part[b k + j]; the update's blocks add the nb partials of each
+// column.  Q is read once, by as many blocks as there are row chunks times
+// column groups; dot_chunk_rows keeps that near kDotBlocks, one a CU, which bounds
+// what the update's blocks read to 8 kDotBlocks entries (32 KB).  n = 100,000,
+// 45 columns on average: dots 17.3 us, update 15.1 us; with 512 blocks 17.8
+// and 15.6, with 1,024 20.2 and 16.6.
 constexpr int kDotRowsMax = 4096;
 constexpr int kDotCols = 8;
+
+constexpr int kDotBlocks = 256;
 
 int dot_rows(int64_t n) {
     int64_t rows = ((n + 255) / 256 + 255) / 256 * 256;
     return (int)std::min<int64_t>(std::max<int64_t>(rows, 256), kDotRowsMax);
+}
+
+// Rows of a chunk for k columns: dot_rows(n) while the column groups are few,
+// then as many more as keep the blocks near kDotBlocks.
+int dot_chunk_rows(int64_t n, int k) {
+    const int64_t groups = (k + kDotCols - 1) / kDotCols, chunks = std::max<int64_t>(1, kDotBlocks / groups);
+    const int64_t rows = ((n + chunks - 1) / chunks + 255) / 256 * 256;
+    return (int)std::min<int64_t>(std::max<int64_t>(rows, dot_rows(n)), (int64_t)1 << 30);
 }
 
 // Wave sums of the 16 values acc[0..15]: at the exchange with lane
@@ -351,7 +421,7 @@ __device__ __forceinline__ void block_sums_to(double (&acc)[2 * kDotCols], int c
 }
 
 __global__ __launch_bounds__(kBlock) void k_dots_part(const double2* __restrict__ Q, int64_t n,
-                                                      const double2* __restrict__ w, int k, int rows, int nb,
+                                                      const double2* __restrict__ w, int k, int rows,
                                                       double2* __restrict__ part) {
     const int b = blockIdx.x, j0 = blockIdx.y * kDotCols;
     const int nc = min(kDotCols, k - j0);
@@ -392,20 +462,27 @@ __global__ __launch_bounds__(kBlock) void k_dots_part(const double2* __restrict_
             }
         }
     }
-    block_sums_to(acc, nc, reinterpret_cast<double*>(part + (int64_t)j0 * nb + b), 2 * (int64_t)nb);
+    block_sums_to(acc, nc, reinterpret_cast<double*>(part + (int64_t)b * k + j0), 2);
 }
 
-// part[k nb + b] = sum over rows of chunk b of conj(U_ik) x_i, k < p
-// (U row-major n x p, p <= 8)
-__global__ __launch_bounds__(kBlock) void k_utx_part(PhaseOp o, const double2* __restrict__ x, int rows, int nb,
-                                                     double2* __restrict__ part) {
+// x = w / beta (stored; block 0 writes beta) and part[k nb + b] = sum over
+// rows of chunk b of conj(U_ik) x_i, k < p (U row-major n x p, p <= 8)
+__global__ __launch_bounds__(kBlock) void k_scale_utx(PhaseOp o, const double2* __restrict__ w,
+                                                      const double* __restrict__ npart, int nparts, int rows, int nb,
+                                                      double2* __restrict__ x, double2* __restrict__ part,
+                                                      double* __restrict__ beta) {
+    const double nrm = beta_of(npart, nparts);
+    const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+    if (beta && blockIdx.x == 0 && threadIdx.x == 0) beta[0] = nrm;
     const int b = blockIdx.x;
     const int64_t i0 = (int64_t)b * rows, i1 = min(o.n, i0 + rows);
     double acc[2 * kDotCols];
 #pragma unroll
     for (int e = 0; e < 2 * kDotCols; ++e) acc[e] = 0.0;
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kBlock) {
-        const double2 xi = x[i];
+        const double2 wi = w[i];
+        const double2 xi = make_double2(wi.x * inv, wi.y * inv);
+        x[i] = xi;
 #pragma unroll
         for (int c = 0; c < kDotCols; ++c) {
             if (c < o.p) {
@@ -415,58 +492,87 @@ __global__ __launch_bounds__(kBlock) void k_utx_part(PhaseOp o, const double2* _
             }
         }
     }
-    block_sums_to(acc, o.p, reinterpret_cast<double*>(part + b), 2 * (int64_t)nb);
+    if (o.p > 0) block_sums_to(acc, o.p, reinterpret_cast<double*>(part + b), 2 * (int64_t)nb);
 }
 
-// h_j = sum_b part[j nb + b], one wave per column; Re h of the last column
-// also into last_re[0] when given
-__global__ __launch_bounds__(kWave) void k_part_sum(const double2* __restrict__ part, int nb,
-                                                    double2* __restrict__ h, double* __restrict__ last_re) {
-    const int j = blockIdx.x;
-    double ar = 0.0, ai = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kWave) {
-        const double2 v = part[(int64_t)j * nb + b];
-        ar += v.x;
-        ai += v.y;
-    }
-    ar = wave_sum_f64(ar);
-    ai = wave_sum_f64(ai);
-    if (threadIdx.x == 0) {
-        h[j] = make_double2(ar, ai);
-        if (last_re && j == (int)gridDim.x - 1) last_re[0] = ar;
-    }
-}
-
-// w -= sum_{j<k} q_j h_j
+// w -= sum_{j<k} q_j h_j, h_j = sum_b part[b k + j].  Each block adds the
+// partials itself (S strided runs per column, four loads in flight, then the
+// runs in order).  alpha: Re of the last h (block 0).  npart: the block's sum
+// of |w|^2 after the update.  (Four threads a row, each with a quarter of the
+// columns, ran no faster: n = 100,000, 45 columns on average, 19.0 us against
+// 17.9.)
 __global__ __launch_bounds__(kBlock) void k_sub(const double2* __restrict__ Q, int64_t n, int k,
-                                                const double2* __restrict__ h, double2* __restrict__ w) {
+                                                const double2* __restrict__ part, int nb, double2* __restrict__ w,
+                                                double* __restrict__ alpha, double* __restrict__ npart) {
     __shared__ double2 hs[kMaxIter + 1];
-    for (int j = threadIdx.x; j < k; j += kBlock) hs[j] = h[j];
-    __syncthreads();
-    const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-    if (i >= n) return;
-    double ar = 0.0, ai = 0.0;
-    // eight column loads in flight per thread, the sum still in column order
-    constexpr int U = 8;
-    int j = 0;
-    for (; j + U <= k; j += U) {
-        double2 q[U];
+    __shared__ double2 runs[kBlock];
+    const int tid = threadIdx.x;
+    const int S = k >= kBlock ? 1 : kBlock / k;
+    for (int e = tid; e < S * k; e += kBlock) {          // one trip when S > 1
+        const int j = e % k;
+        double ar = 0.0, ai = 0.0;
+        int b = e / k;
+        for (; b + 3 * S < nb; b += 4 * S) {
+            double2 v[4];
 #pragma unroll
-        for (int u = 0; u < U; ++u) q[u] = Q[(int64_t)(j + u) * n + i];
+            for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(b + u * S) * k + j];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const double2 t = cmul(q[u], hs[j + u]);
-            ar += t.x;
-            ai += t.y;
+            for (int u = 0; u < 4; ++u) {
+                ar += v[u].x;
+                ai += v[u].y;
+            }
         }
+        for (; b < nb; b += S) {
+            const double2 v = part[(int64_t)b * k + j];
+            ar += v.x;
+            ai += v.y;
+        }
+        if (S == 1) hs[j] = make_double2(ar, ai);
+        else runs[e] = make_double2(ar, ai);
     }
-    for (; j < k; ++j) {
-        const double2 t = cmul(Q[(int64_t)j * n + i], hs[j]);
-        ar += t.x;
-        ai += t.y;
+    __syncthreads();
+    if (S > 1 && tid < k) {
+        double2 a = runs[tid];
+        for (int q = 1; q < S; ++q) {
+            const double2 v = runs[q * k + tid];
+            a.x += v.x;
+            a.y += v.y;
+        }
+        hs[tid] = a;
     }
-    const double2 wi = w[i];
-    w[i] = make_double2(wi.x - ar, wi.y - ai);
+    __syncthreads();
+    if (alpha && blockIdx.x == 0 && tid == 0) alpha[0] = hs[k - 1].x;
+    double sq = 0.0, unused = 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)kBlock + tid; i < n; i += (int64_t)gridDim.x * kBlock) {
+        double ar = 0.0, ai = 0.0;
+        // sixteen column loads in flight per thread, the sum still in column order
+        auto cols = [&](auto U, int& j) {
+            constexpr int N = decltype(U)::value;
+            for (; j + N <= k; j += N) {
+                double2 q[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) q[u] = Q[(int64_t)(j + u) * n + i];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const double2 t = cmul(q[u], hs[j + u]);
+                    ar += t.x;
+                    ai += t.y;
+                }
+            }
+        };
+        int j = 0;
+        cols(std::integral_constant<int, 16>{}, j);
+        cols(std::integral_constant<int, 4>{}, j);
+        cols(std::integral_constant<int, 1>{}, j);
+        const double2 wi = w[i];
+        const double2 v = make_double2(wi.x - ar, wi.y - ai);
+        w[i] = v;
+        sq += v.x * v.x + v.y * v.y;
+    }
+    if (npart) {
+        block_sum2(sq, unused);
+        if (tid == 0) npart[blockIdx.x] = sq;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_norm_part(const double2* __restrict__ w, int64_t n, double* __restrict__ part) {
@@ -479,27 +585,10 @@ __global__ __launch_bounds__(kBlock) void k_norm_part(const double2* __restrict_
     if (threadIdx.x == 0) part[blockIdx.x] = a;
 }
 
-// out[0] = sqrt(sum of the partials); also into copy[0] when given
-__global__ __launch_bounds__(kBlock) void k_norm_final(const double* __restrict__ part, int count, double* __restrict__ out,
-                                                       double* __restrict__ copy) {
-    double a = 0.0, b = 0.0;
-    for (int t = threadIdx.x; t < count; t += kBlock) a += part[t];
-    block_sum2(a, b);
-    if (threadIdx.x == 0) {
-        out[0] = sqrt(a);
-        if (copy) copy[0] = sqrt(a);
-    }
-}
-
-// q = w / nrm (nrm read on the device)
-__global__ __launch_bounds__(kBlock) void k_scale(const double2* __restrict__ w, int64_t n, const double* __restrict__ nrm,
-                                                  double2* __restrict__ q) {
-    const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-    if (i >= n) return;
-    // a zero vector (breakdown, found by the host at the next check) stays zero
-    const double inv = nrm[0] > 0.0 ? 1.0 / nrm[0] : 0.0;
-    const double2 t = w[i];
-    q[i] = make_double2(t.x * inv, t.y * inv);
+// beta at the last step, which no further step scales by
+__global__ __launch_bounds__(kBlock) void k_beta(const double* __restrict__ npart, int nparts, double* __restrict__ beta) {
+    const double nrm = beta_of(npart, nparts);
+    if (threadIdx.x == 0) beta[0] = nrm;
 }
 
 // start vector: standard complex Gaussian entries from the Philox stream
@@ -539,20 +628,23 @@ __device__ __forceinline__ int sturm_below(const double* a, const double* bb, in
 // iteration on T - mu I, mu just off theta (one elimination with partial
 // pivoting, three solves); wave 0 orthonormalises the r vectors in order
 // (two Gram-Schmidt passes, lane-strided dots added by butterfly) and forms
-// the residual bounds |b_last s_{m-1,t}|.  S is m x r column-major; the
-// elimination works in LDS for m <= kTriLds, else in `work`.
+// the residual bounds |b_last s_{m-1,t}| (b_last = beta_{m-1}, or 0 at the end
+// of an invariant space).  out (host memory): theta, the bounds, and the index
+// of a breakdown.  S is m x r column-major; the elimination works in LDS for
+// m <= kTriLds, else in `work`.
 constexpr int kTriThreads = 256;
 constexpr int kTriLds = 224;
 
 __global__ __launch_bounds__(kTriThreads) void k_tridiag_top(const double* __restrict__ a_g,
                                                              const double* __restrict__ b_g, int m, int r,
-                                                             double b_last, double* __restrict__ theta,
-                                                             double* __restrict__ S, double* __restrict__ resid,
+                                                             int exact_end, double* __restrict__ theta,
+                                                             double* __restrict__ S, double* __restrict__ out,
                                                              double* __restrict__ work) {
     __shared__ double a[kMaxIter + 1], b[kMaxIter + 1], bb[kMaxIter + 1];
     __shared__ double wl[LRQO_MAX_R][6 * kTriLds];
     __shared__ double red_lo[kTriThreads / kWave], red_hi[kTriThreads / kWave];
     __shared__ double th_s[LRQO_MAX_R];
+    __shared__ int bad_s;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     double lo = INFINITY, hi = -INFINITY;
     for (int i = tid; i < m; i += kTriThreads) {
@@ -564,6 +656,7 @@ __global__ __launch_bounds__(kTriThreads) void k_tridiag_top(const double* __res
         lo = fmin(lo, ai - rad);
         hi = fmax(hi, ai + rad);
     }
+    const double b_last = exact_end ? 0.0 : b_g[m - 1];
     for (int off = kWave / 2; off > 0; off >>= 1) {
         lo = fmin(lo, __shfl_xor(lo, off, kWave));
         hi = fmax(hi, __shfl_xor(hi, off, kWave));
@@ -598,9 +691,32 @@ __global__ __launch_bounds__(kTriThreads) void k_tridiag_top(const double* __res
         if (lane == 0) {
             th_s[t] = 0.5 * (l0 + h0);
             theta[t] = th_s[t];
+            out[t] = th_s[t];
         }
     }
+    // breakdown: the first beta_t not above 1e-13 times the largest
+    // |alpha_u| + |beta_u|, u <= t (a running maximum; m when there is none)
+    if (wv == kTriThreads / kWave - 1) {
+        const int per = (m + kWave - 1) / kWave, i0 = min(m, lane * per), i1 = min(m, i0 + per);
+        double mx = 0.0;
+        for (int i = i0; i < i1; ++i) mx = fmax(mx, fabs(a[i]) + fabs(b_g[i]));
+        double pre = mx;                           // inclusive maximum over the lanes
+        for (int off = 1; off < kWave; off <<= 1) {
+            const double o = __shfl_up(pre, off, kWave);
+            if (lane >= off) pre = fmax(pre, o);
+        }
+        double run = __shfl_up(pre, 1, kWave);
+        run = lane ? run : 0.0;
+        int bad = m;
+        for (int i = i0; i < i1; ++i) {
+            run = fmax(run, fabs(a[i]) + fabs(b_g[i]));
+            if (!(b_g[i] > 1e-13 * run)) bad = min(bad, i);
+        }
+        for (int off = kWave / 2; off > 0; off >>= 1) bad = min(bad, __shfl_xor(bad, off, kWave));
+        if (lane == 0) bad_s = bad;
+    }
     __syncthreads();
+    if (tid == 0) out[2 * LRQO_MAX_R] = (double)bad_s;
     if (tid < r) {
         const int t = tid;
         const double mu = th_s[t] + 1e-13 * span;
@@ -682,7 +798,7 @@ __global__ __launch_bounds__(kTriThreads) void k_tridiag_top(const double* __res
             const double inv = 1.0 / sqrt(nrm);
             for (int i = lane; i < m; i += kWave) {
                 su[i] *= inv;
-                if (i == m - 1) resid[u] = fabs(b_last * su[i]);
+                if (i == m - 1) out[LRQO_MAX_R + u] = fabs(b_last * su[i]);
             }
         }
     }
@@ -806,55 +922,65 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
     CarveSize cs;
     cs.add<double2>((size_t)n * (max_iter + 1));   // basis
     cs.add<double2>(n);                           // w
-    cs.add<double2>(kMaxIter + 1);                // h
     const int drows = dot_rows(n);
     const int nbd = (int)((n + drows - 1) / drows);
-    cs.add<double2>((size_t)(kMaxIter + 1) * nbd);  // partial dots
-    cs.add<double2>(LRQO_MAX_R);                  // U^H x
+    cs.add<double2>((size_t)(kMaxIter + 1) * nbd);  // partial dots (and of U^H x, before them)
+    cs.add<double2>(LRQO_MAX_R);                  // column phases
     cs.add<double>(nparts);                       // norm partials
-    cs.add<double>(4);                            // norm
     cs.add<double>(kMaxIter + 1);                 // alpha
     cs.add<double>(kMaxIter + 1);                 // beta
     cs.add<double>(LRQO_MAX_R);                   // theta
-    cs.add<double>(LRQO_MAX_R);                   // resid
     cs.add<double>((size_t)(kMaxIter + 1) * LRQO_MAX_R);       // S
     cs.add<double>((size_t)6 * (kMaxIter + 1) * LRQO_MAX_R);   // tridiagonal work
-    cs.add<double2>((size_t)n * r);               // Ritz vectors
+    cs.add<double2>((size_t)n * r);               // second w, then the Ritz vectors
     cs.add<double>((size_t)nparts * LRQO_MAX_R);
     cs.add<int64_t>((size_t)nparts * LRQO_MAX_R);
-    // symmetric W tiles (phase-sync operator only)
-    const int64_t P = (n + kSymT - 1) / kSymT;
+    // symmetric W tiles (phase-sync operator only).  An item of eight tiles
+    // keeps the row sums few, but at n = 32,768 leaves 4.25 blocks a CU, five
+    // on some: the smaller the matrix, the smaller the items, about 4,096 of
+    // them (n = 32,768: 0.93 -> 0.77 ms a
+    // product).  Where their row sums do not fit the
+    // scratch, items are of eight tiles.
+    const int64_t P = (n + kSymT - 1) / kSymT, tiles = P * (P + 1) / 2;
     std::vector<int2> items;
     std::vector<int32_t> item_first;
-    if (kind == kOpPhase) {
-        item_first.reserve(P + 1);
-        for (int64_t I = 0; I < P; ++I) {
+    CarveSize cs0 = cs;
+    int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(kSymChunk, tiles / 4096));
+    for (;;) {
+        cs = cs0;
+        if (kind == kOpPhase) {
+            items.clear();
+            item_first.clear();
+            item_first.reserve(P + 1);
+            for (int64_t I = 0; I < P; ++I) {
+                item_first.push_back((int32_t)items.size());
+                for (int64_t cidx = 0; I + cidx * chunk < P; ++cidx) items.push_back(make_int2((int)I, (int)cidx));
+            }
             item_first.push_back((int32_t)items.size());
-            for (int64_t cidx = 0; I + cidx * kSymChunk < P; ++cidx) items.push_back(make_int2((int)I, (int)cidx));
+            cs.add<int2>(items.size());
+            cs.add<int32_t>(item_first.size());
+            cs.add<double2>(items.size() * (size_t)kSymT);
+            cs.add<double2>((size_t)tiles * kSymT);
         }
-        item_first.push_back((int32_t)items.size());
-        cs.add<int2>(items.size());
-        cs.add<int32_t>(item_first.size());
-        cs.add<double2>(items.size() * (size_t)kSymT);
-        cs.add<double2>((size_t)(P * (P + 1) / 2) * kSymT);
+        const lrqo_status fits = reserve_arena(ctx, cs.bytes);
+        if (fits == LRQO_OK) break;
+        if (fits != LRQO_ENOMEM || kind != kOpPhase || chunk == kSymChunk) return fits;
+        chunk = kSymChunk;
+        clear_error();
     }
     CarveSize hs;
-    hs.add<double>(2 * (kMaxIter + 1));
-    hs.add<double>(2 * LRQO_MAX_R);
-    LRQO_TRY(reserve_arena(ctx, cs.bytes));
+    hs.add<double>(2 * LRQO_MAX_R + 1);
     LRQO_TRY(reserve_host(ctx, hs.bytes));
+    LRQO_TRY(reserve_side(ctx));
     Carve cv(ctx->arena);
     double2* Q = cv.take<double2>((size_t)n * (max_iter + 1));
     double2* w = cv.take<double2>(n);
-    double2* h = cv.take<double2>(kMaxIter + 1);
     double2* dpart = cv.take<double2>((size_t)(kMaxIter + 1) * nbd);
     double2* uc = cv.take<double2>(LRQO_MAX_R);
     double* npart = cv.take<double>(nparts);
-    double* nrm = cv.take<double>(4);
     double* alpha = cv.take<double>(kMaxIter + 1);
     double* beta = cv.take<double>(kMaxIter + 1);
     double* theta = cv.take<double>(LRQO_MAX_R);
-    double* resid = cv.take<double>(LRQO_MAX_R);
     double* S = cv.take<double>((size_t)(kMaxIter + 1) * LRQO_MAX_R);
     double* work = cv.take<double>((size_t)6 * (kMaxIter + 1) * LRQO_MAX_R);
     double2* Uo = cv.take<double2>((size_t)n * r);
@@ -868,94 +994,104 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
         d_items = cv.take<int2>(items.size());
         d_first = cv.take<int32_t>(item_first.size());
         rowpart = cv.take<double2>(items.size() * (size_t)kSymT);
-        colpart = cv.take<double2>((size_t)(P * (P + 1) / 2) * kSymT);
+        colpart = cv.take<double2>((size_t)tiles * kSymT);
         LRQO_HIP(hipMemcpyAsync(d_items, items.data(), sizeof(int2) * items.size(), hipMemcpyHostToDevice, st));
         LRQO_HIP(hipMemcpyAsync(d_first, item_first.data(), sizeof(int32_t) * item_first.size(),
                                 hipMemcpyHostToDevice, st));
         LRQO_HIP(hipStreamSynchronize(st));
     }
     Carve hv(ctx->host);
-    double* h_ab = hv.take<double>(2 * (kMaxIter + 1));     // alpha then beta
-    double* h_tr = hv.take<double>(2 * LRQO_MAX_R);         // theta then resid
-    double* h_alpha = h_ab;
-    double* h_beta = h_ab + (kMaxIter + 1);
+    double* h_tr = hv.take<double>(2 * LRQO_MAX_R + 1);     // theta, residual bounds, breakdown index
 
-    auto apply = [&](const double2* x, double2* y) -> lrqo_status {
+    // q_j = w / beta_{j-1} into dst and A q_j into y (start vector: no beta)
+    auto scale_apply = [&](const double2* from, double2* dst, double2* y, double* bet) -> lrqo_status {
         if (kind == kOpLap) {
-            hipLaunchKernelGGL(k_apply_lap, dim3((unsigned)blocks), dim3(kBlock), 0, st, lap, x, y);
+            hipLaunchKernelGGL(k_apply_lap, dim3((unsigned)blocks), dim3(kBlock), 0, st, lap, from, npart, nparts, dst,
+                               y, bet);
         } else {
-            if (ph.p > 0) {
-                hipLaunchKernelGGL(k_utx_part, dim3(nbd), dim3(kBlock), 0, st, ph, x, drows, nbd, dpart);
-                hipLaunchKernelGGL(k_part_sum, dim3(ph.p), dim3(kWave), 0, st, dpart, nbd, uc, nullptr);
-            }
-            hipLaunchKernelGGL(k_w_tiles, dim3((unsigned)items.size()), dim3(kSymT), 0, st, ph, x, d_items, P,
-                               rowpart, colpart);
-            hipLaunchKernelGGL(k_w_combine, dim3((unsigned)P), dim3(kSymT), 0, st, ph, uc, d_first, P, rowpart,
-                               colpart, y);
+            hipLaunchKernelGGL(k_scale_utx, dim3(nbd), dim3(kBlock), 0, st, ph, from, npart, nparts, drows, nbd, dst,
+                               dpart, bet);
         }
         LRQO_HIP(hipGetLastError());
         return LRQO_OK;
     };
-    auto normalize_into = [&](double2* dst) -> lrqo_status {
-        hipLaunchKernelGGL(k_norm_part, dim3(nparts), dim3(kBlock), 0, st, w, n, npart);
-        hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(kBlock), 0, st, npart, nparts, nrm, nullptr);
-        hipLaunchKernelGGL(k_scale, dim3((unsigned)blocks), dim3(kBlock), 0, st, w, n, nrm, dst);
+    auto w_product = [&](const double2* x, double2* y) -> lrqo_status {
+        if (kind == kOpPhase) {
+            hipLaunchKernelGGL(k_w_tiles, dim3((unsigned)items.size()), dim3(kSymT), 0, st, ph, x, d_items, P, chunk,
+                               rowpart, colpart);
+            hipLaunchKernelGGL(k_w_combine, dim3((unsigned)P), dim3(kSymT), 0, st, ph, dpart, nbd, d_first, P, rowpart,
+                               colpart, y);
+            LRQO_HIP(hipGetLastError());
+        }
+        return LRQO_OK;
+    };
+    auto tridiag = [&](int mm, bool end, hipStream_t on) -> lrqo_status {
+        hipLaunchKernelGGL(k_tridiag_top, dim3(1), dim3(kTriThreads), 0, on, alpha, beta, mm, r, end ? 1 : 0, theta, S,
+                           h_tr, work);
         LRQO_HIP(hipGetLastError());
         return LRQO_OK;
     };
 
     LRQO_HIP(hipEventRecord(ctx->ev_start, st));
     hipLaunchKernelGGL(k_start, dim3((unsigned)blocks), dim3(kBlock), 0, st, n, o.seed, w);
-    LRQO_TRY(normalize_into(Q));
+    hipLaunchKernelGGL(k_norm_part, dim3(nparts), dim3(kBlock), 0, st, w, n, npart);
+    LRQO_HIP(hipGetLastError());
     int m = 0;              // Lanczos vectors q_0..q_{m-1} complete, T is m x m
-    bool converged = false, breakdown = false;
-    // alpha and beta stay on the device; the host reads them at each check,
-    // where it also finds a breakdown (the first beta_t not above 1e-13
-    // times the largest |alpha_u| + |beta_u|, u <= t) and truncates there
+    bool converged = false, breakdown = false, pending = false;
+    // the verdict on T_m once h_tr holds it: sets m, converged, breakdown
+    auto verdict = [&](int mm, bool at_end) -> lrqo_status {
+        m = mm;
+        const int bad = (int)h_tr[2 * LRQO_MAX_R];
+        if (bad < mm) m = bad + 1;
+        breakdown = bad < mm || m == n;
+        if (m < r) return LRQO_OK;
+        if (breakdown && !(at_end && m == mm)) {   // the space ends at m: its pairs are exact
+            LRQO_TRY(tridiag(m, true, st));
+            LRQO_HIP(hipStreamSynchronize(st));
+        }
+        const double scale = std::max(std::fabs(h_tr[0]), 1e-300);
+        converged = true;
+        for (int k = 0; k < r; ++k) converged &= h_tr[LRQO_MAX_R + k] <= tol * scale;
+        return LRQO_OK;
+    };
+    double2 *cur = w, *other = Uo;
+    int last = 0;           // steps launched
     for (int j = 0; j < max_iter; ++j) {
         double2* qj = Q + (int64_t)j * n;
-        LRQO_TRY(apply(qj, w));
+        LRQO_TRY(scale_apply(cur, qj, other, j ? beta + (j - 1) : nullptr));
+        if (pending) {      // T_j is complete: check it beside the rest of this step
+            LRQO_HIP(hipEventRecord(ctx->ev_fork, st));
+            LRQO_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
+            LRQO_TRY(tridiag(j, false, ctx->side));
+            LRQO_HIP(hipEventRecord(ctx->ev_join, ctx->side));
+        }
+        std::swap(cur, other);
+        LRQO_TRY(w_product(qj, cur));
+        const int k = j + 1, rows = dot_chunk_rows(n, k), nb = (int)((n + rows - 1) / rows);
         for (int pass = 0; pass < 2; ++pass) {
-            hipLaunchKernelGGL(k_dots_part, dim3(nbd, (j + kDotCols) / kDotCols), dim3(kBlock), 0, st, Q, n, w,
-                               j + 1, drows, nbd, dpart);
-            hipLaunchKernelGGL(k_part_sum, dim3(j + 1), dim3(kWave), 0, st, dpart, nbd, h,
-                               pass == 0 ? alpha + j : nullptr);
-            hipLaunchKernelGGL(k_sub, dim3((unsigned)blocks), dim3(kBlock), 0, st, Q, n, j + 1, h, w);
+            hipLaunchKernelGGL(k_dots_part, dim3(nb, (k + kDotCols - 1) / kDotCols), dim3(kBlock), 0, st, Q, n, cur,
+                               k, rows, dpart);
+            hipLaunchKernelGGL(k_sub, dim3(nparts), dim3(kBlock), 0, st, Q, n, k, dpart, nb, cur,
+                               pass == 0 ? alpha + j : nullptr, pass == 1 ? npart : nullptr);
         }
-        hipLaunchKernelGGL(k_norm_part, dim3(nparts), dim3(kBlock), 0, st, w, n, npart);
-        hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(kBlock), 0, st, npart, nparts, nrm, beta + j);
         LRQO_HIP(hipGetLastError());
-        m = j + 1;
-        const bool check = m >= r && (m % every == 0 || j + 1 == max_iter || m == n);
-        if (check) {
-            LRQO_HIP(hipMemcpyAsync(h_alpha, alpha, sizeof(double) * m, hipMemcpyDeviceToHost, st));
-            LRQO_HIP(hipMemcpyAsync(h_beta, beta, sizeof(double) * m, hipMemcpyDeviceToHost, st));
-            LRQO_HIP(hipStreamSynchronize(st));
-            double amax = 0.0;
-            for (int t = 0; t < m; ++t) {
-                amax = std::max(amax, std::fabs(h_alpha[t]) + std::fabs(h_beta[t]));
-                if (!(h_beta[t] > 1e-13 * amax)) {
-                    m = t + 1;
-                    breakdown = true;
-                    break;
-                }
-            }
-            breakdown = breakdown || m == n;
-            if (m < r) break;
-            hipLaunchKernelGGL(k_tridiag_top, dim3(1), dim3(kTriThreads), 0, st, alpha, beta, m, r,
-                               breakdown ? 0.0 : h_beta[m - 1], theta, S, resid, work);
-            LRQO_HIP(hipGetLastError());
-            LRQO_HIP(hipMemcpyAsync(h_tr, theta, sizeof(double) * r, hipMemcpyDeviceToHost, st));
-            LRQO_HIP(hipMemcpyAsync(h_tr + LRQO_MAX_R, resid, sizeof(double) * r, hipMemcpyDeviceToHost, st));
-            LRQO_HIP(hipStreamSynchronize(st));
-            const double scale = std::max(std::fabs(h_tr[0]), 1e-300);
-            converged = true;
-            for (int k = 0; k < r; ++k) converged &= h_tr[LRQO_MAX_R + k] <= tol * scale;
-            if (converged || breakdown) break;
+        last = j + 1;
+        if (pending) {
+            pending = false;
+            LRQO_HIP(hipEventSynchronize(ctx->ev_join));
+            LRQO_TRY(verdict(j, false));
+            if (m < r || converged || breakdown) break;
         }
-        hipLaunchKernelGGL(k_scale, dim3((unsigned)blocks), dim3(kBlock), 0, st, w, n, nrm,
-                           Q + (int64_t)(j + 1) * n);
-        LRQO_HIP(hipGetLastError());
+        const bool check = last >= r && (last % every == 0 || last == max_iter || last == n);
+        if (check && (last == max_iter || last == n)) {
+            hipLaunchKernelGGL(k_beta, dim3(1), dim3(kBlock), 0, st, npart, nparts, beta + j);
+            LRQO_TRY(tridiag(last, last == n, st));
+            LRQO_HIP(hipStreamSynchronize(st));
+            LRQO_TRY(verdict(last, last == n));
+            break;
+        }
+        m = last;
+        pending = check;
     }
     if (m < r) return fail(LRQO_EINVAL, "the Krylov space is smaller than r (graph or operator too small)");
     hipLaunchKernelGGL(k_ritz, dim3((unsigned)blocks), dim3(kBlock), 0, st, Q, n, m, r, S, Uo);

@@ -29,6 +29,8 @@ struct DeviceCtx {
     size_t host_bytes = 0;
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
     hipEvent_t ev_score0 = nullptr, ev_score1 = nullptr;  // bracket the scoring kernels
+    hipStream_t side = nullptr;                          // work beside the caller's stream (reserve_side)
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr;     // order it against that stream
     void* static_scratch = nullptr;  // this device's copy of the allocation-free entry point's array
 };
 
@@ -39,6 +41,8 @@ DeviceCtx* device_ctx();
 // Ensures the arena holds at least `bytes`; the old contents are dropped.
 lrqo_status reserve_arena(DeviceCtx* ctx, size_t bytes);
 lrqo_status reserve_host(DeviceCtx* ctx, size_t bytes);
+// Ensures the side stream and its two events exist.
+lrqo_status reserve_side(DeviceCtx* ctx);
 
 // Bump allocator over a reserved block (256-byte alignment).
 struct Carve {

@@ -101,6 +101,13 @@ lrqo_status reserve_host(DeviceCtx* ctx, size_t bytes) {
     return LRQO_OK;
 }
 
+lrqo_status reserve_side(DeviceCtx* ctx) {
+    if (!ctx->ev_fork) LRQO_HIP(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
+    if (!ctx->ev_join) LRQO_HIP(hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming));
+    if (!ctx->side) LRQO_HIP(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
+    return LRQO_OK;
+}
+
 bool is_device_pointer(const void* p) {
     hipPointerAttribute_t attr;
     std::memset(&attr, 0, sizeof attr);
@@ -141,6 +148,9 @@ lrqo_status lrqo_shutdown(void) {
                 (void)hipEventDestroy(c->ev_stop);
                 (void)hipEventDestroy(c->ev_score0);
                 (void)hipEventDestroy(c->ev_score1);
+                if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
+                if (c->ev_join) (void)hipEventDestroy(c->ev_join);
+                if (c->side) (void)hipStreamDestroy(c->side);
             }
         }
         lrqo::g_ctx[d] = nullptr;
