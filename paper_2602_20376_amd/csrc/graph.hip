@@ -10,18 +10,30 @@
 //                   w [k_i != k_j] (each edge is seen from both ends), block
 //                   partial sums in a fixed order
 //   k_sum2          fixed-order sum of the block partials
-//   k_gain          per vertex: neighbour label weights c_k in LDS, the best
-//                   other label and its gain 2 sum_k c_k (cos(a-k) - cos(b-k))
+//   k_gain          per vertex whose own label or a neighbour's changed since
+//                   its last gain: neighbour label weights c_k in LDS, the best
+//                   other label and its gain 2 sum_k c_k (cos(a-k) - cos(b-k));
+//                   the others keep theirs
 //   k_move          per candidate: moves when its (gain, -index) beats every
-//                   neighbouring candidate; labels go to the other buffer;
-//                   moves counted per round (per block, into 64 counters)
+//                   neighbouring candidate, and marks itself and its neighbours
+//                   for the next k_gain; the movers are an independent set and
+//                   no label is read here, so labels change in place; moves
+//                   counted per round (per block, into 64 counters)
+// Later rounds move few vertices, so most gains stand (10^5 vertices, mean
+// degree 10, 24 launched rounds: gains 203 -> 149 us; moves, which now also
+// leave the marks, 124 -> 142; the whole call 0.49 -> 0.44 ms).  A round that
+// changes nothing still takes 5 us a kernel, against 1.8 us for one that
+// returns at once: what is left is the chain of dependent reads.
 // Rounds go out in batches between host checks; a round whose predecessor
 // moved nothing returns at once, so a batch that converges early costs a
-// launch per remaining round.
+// launch per remaining round.  The layout checks, the first objective and the
+// first batch are queued together: each kernel returns at once when a check
+// before it failed, and the host reads the verdict with the batch's counts.
 // One thread per vertex; the CSR entries of a vertex are read in order, so
 // every per-vertex sum has a fixed order.
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <string>
 
@@ -60,7 +72,7 @@ __global__ __launch_bounds__(kBlock) void k_check_ptr(GraphDev g, int* flag) {
 
 __global__ __launch_bounds__(kBlock) void k_check_rows(GraphDev g, int K, const uint8_t* z, int* flag) {
     const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-    if (i >= g.n) return;
+    if (i >= g.n || (*flag & kBadPtr)) return;   // k_check_ptr failed: row_ptr must not be followed
     int bad = (z && z[i] >= K) ? kBadLabel : 0;
     for (int64_t e = g.row_ptr[i]; e < g.row_ptr[i + 1]; ++e) {
         const int32_t j = g.col[e];
@@ -121,10 +133,10 @@ __device__ __forceinline__ void objective_chunk(const GraphDev& g, int K, const 
 
 __global__ __launch_bounds__(kBlock) void k_objective(GraphDev g, int K, const uint8_t* __restrict__ z,
                                                       const double* __restrict__ sqd,
-                                                      double* __restrict__ partial) {
+                                                      double* __restrict__ partial, const int* __restrict__ flag) {
     const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
     double q = 0.0, cut = 0.0;
-    if (i < g.n) {
+    if (i < g.n && *flag == 0) {
         const int a = z[i];
         int64_t e = g.row_ptr[i];
         const int64_t e1 = g.row_ptr[i + 1];
@@ -189,34 +201,22 @@ __device__ __forceinline__ void gain_chunk(const GraphDev& g, const uint8_t* __r
     }
 }
 
-// Whether a neighbour in [e, e1) beats (gi, i), U neighbours' gains in
-// flight at a time; stops at the first chunk that holds one.
-template <int U>
-__device__ __forceinline__ void move_chunk(const GraphDev& g, const double* __restrict__ gain, int64_t i, double gi,
-                                           int64_t& e, int64_t e1, bool& win) {
-    for (; win && e + U <= e1; e += U) {
-        int32_t j[U];
-        double gj[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) j[u] = g.col[e + u];
-#pragma unroll
-        for (int u = 0; u < U; ++u) gj[u] = gain[j[u]];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (gj[u] > 0.0 && (gj[u] > gi || (gj[u] == gi && j[u] < i))) win = false;
-    }
-}
+// A vertex's byte of `target` holds its best label (below 16) and this mark:
+// its label or a neighbour's changed since its gain was taken.
+constexpr int kStale = 0x80;
 
 // cosd[d] = cos(2 pi d / K).  Gain of moving i from a to b:
-// 2 sum_k c_k (cosd[(a-k) mod K] - cosd[(b-k) mod K]).
+// 2 sum_k c_k (cosd[(a-k) mod K] - cosd[(b-k) mod K]).  first: every vertex.
 template <int KM>
 __global__ __launch_bounds__(kRefineBlock) void k_gain(GraphDev g, int K, const uint8_t* __restrict__ z,
                                                  const double* __restrict__ cosd,
-                                                 double* __restrict__ gain, uint8_t* __restrict__ target,
-                                                 const unsigned long long* __restrict__ prev) {
+                                                 double* __restrict__ gain, uint8_t* __restrict__ target, bool first,
+                                                 const unsigned long long* __restrict__ prev,
+                                                 const int* __restrict__ flag) {
     __shared__ double cnt[KM][kRefineBlock];   // KM >= K rows
     const int64_t i = blockIdx.x * (int64_t)kRefineBlock + threadIdx.x;
-    if (no_moves(prev) || i >= g.n) return;   // the vote first, with every lane active
+    if (no_moves(prev) || *flag || i >= g.n) return;   // the vote first, with every lane active
+    if (!first && !(target[i] & kStale)) return;
     for (int k = 0; k < K; ++k) cnt[k][threadIdx.x] = 0.0;
     double wdeg = 0.0;
     int64_t e = g.row_ptr[i];
@@ -251,37 +251,192 @@ __global__ __launch_bounds__(kRefineBlock) void k_gain(GraphDev g, int K, const 
     target[i] = (uint8_t)(cand ? bl : a);
 }
 
+// Rows by groups of sixteen lanes: a wave takes kRowsPerWave = 16 vertices,
+// lane l looks after vertex l % 16, and in trip q of four the group l / 16
+// reads the entries of vertex 4 q + l / 16, one a lane.  The columns of all
+// four trips are in flight together, then whatever they point at.  A thread a
+// vertex instead reads its row entry by entry, 64 rows apart in memory across
+// the wave (24 rounds as above: gains 160 us, moves 177; with sixteen entries
+// of a row in flight 197 and 148).
+constexpr int kRowsPerWave = 16;
 
-__global__ __launch_bounds__(kRefineBlock) void k_move(GraphDev g, const uint8_t* __restrict__ z,
-                                                 const double* __restrict__ gain,
-                                                 const uint8_t* __restrict__ target,
-                                                 uint8_t* __restrict__ z_next,
-                                                 unsigned long long* __restrict__ moves,
-                                                 const unsigned long long* __restrict__ prev) {
-    const int64_t i = blockIdx.x * (int64_t)kRefineBlock + threadIdx.x;
-    if (no_moves(prev)) return;   // uniform over the grid
-    bool win = false;
-    if (i < g.n) {
-        const double gi = gain[i];
-        win = gi > 0.0;
-        int64_t e = g.row_ptr[i];
-        const int64_t e1 = g.row_ptr[i + 1];
-        // eight, then four neighbours' gains in flight at a time
-        move_chunk<8>(g, gain, i, gi, e, e1, win);
-        move_chunk<4>(g, gain, i, gi, e, e1, win);
-        for (; win && e < e1; ++e) {
-            const int32_t j = g.col[e];
-            const double gj = gain[j];
-            if (gj > 0.0 && (gj > gi || (gj == gi && j < i))) win = false;
+struct WaveRows {
+    int64_t i;            // this lane's vertex
+    bool in;
+    int64_t e0, e1;       // its entries (read_rows)
+};
+
+__device__ __forceinline__ WaveRows wave_rows(const GraphDev& g) {
+    const int64_t wave = blockIdx.x * (int64_t)(kRefineBlock / kWave) + threadIdx.x / kWave;
+    WaveRows r;
+    r.i = wave * kRowsPerWave + (threadIdx.x & (kRowsPerWave - 1));
+    r.in = r.i < g.n;
+    r.e0 = r.e1 = 0;
+    return r;
+}
+__device__ __forceinline__ void read_rows(const GraphDev& g, WaveRows& r) {
+    if (r.in) {
+        r.e0 = g.row_ptr[r.i];
+        r.e1 = g.row_ptr[r.i + 1];
+    }
+}
+
+// Unit weights, K <= 4: label counts by ballots (whole numbers, so the FP64
+// sums of the general kernel are the same).
+__global__ __launch_bounds__(kRefineBlock) void k_gain_unit(GraphDev g, int K, const uint8_t* __restrict__ z,
+                                                      const double* __restrict__ cosd,
+                                                      double* __restrict__ gain, uint8_t* __restrict__ target,
+                                                      bool first, const unsigned long long* __restrict__ prev,
+                                                      const int* __restrict__ flag) {
+    __shared__ double ctab[4];
+    if ((int)threadIdx.x < K) ctab[threadIdx.x] = cosd[threadIdx.x];
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), grp = lane / kRowsPerWave, sub = lane & (kRowsPerWave - 1);
+    const int bad = *flag;
+    WaveRows r = wave_rows(g);
+    const bool stale = r.in && (first || (target[r.i] & kStale));
+    const int a = r.in ? z[r.i] : 0;
+    if (no_moves(prev) || bad || __ballot(stale) == 0ull) return;   // uniform over the wave
+    read_rows(g, r);
+    int64_t e[4], e1[4];
+    int32_t c[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        e[q] = __shfl(r.e0, 4 * q + grp, kWave) + sub;
+        const int64_t end = __shfl(r.e1, 4 * q + grp, kWave);   // every lane takes part in a shuffle
+        e1[q] = __shfl((int)stale, 4 * q + grp, kWave) ? end : 0;
+        c[q] = e[q] < e1[q] ? g.col[e[q]] : -1;
+    }
+    int cnt[4] = {0, 0, 0, 0};
+    bool more = true;
+    while (more) {        // once, unless a row has more than sixteen entries
+        int l[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) l[q] = c[q] >= 0 ? z[c[q]] : -1;
+        more = false;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned long long b = __ballot(l[q] == k);
+                if (sub / 4 == q) cnt[k] += __popcll((b >> (kRowsPerWave * (sub & 3))) & 0xffffull);
+            }
+            e[q] += kRowsPerWave;
+            c[q] = e[q] < e1[q] ? g.col[e[q]] : -1;
+            more |= __ballot(c[q] >= 0) != 0ull;
         }
-        z_next[i] = win ? target[i] : z[i];
+    }
+    if (!stale || grp != 0) return;
+    double best = -INFINITY;
+    int bl = a;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if (b >= K || b == a) continue;
+        double d = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (k >= K) break;
+            const int da = a - k + (a < k ? K : 0), db = b - k + (b < k ? K : 0);
+            d += (double)cnt[k] * (ctab[da] - ctab[db]);
+        }
+        d *= 2.0;
+        if (d > best) {
+            best = d;
+            bl = b;
+        }
+    }
+    const bool cand = best > 1e-12 * (double)(r.e1 - r.e0);
+    gain[r.i] = cand ? best : 0.0;
+    target[r.i] = (uint8_t)(cand ? bl : a);
+}
+
+// The marks: several movers may mark one vertex in the same launch; its label
+// bits are constant here, so all of them store the same byte.
+__global__ __launch_bounds__(kRefineBlock) void k_move(GraphDev g, uint8_t* __restrict__ z,
+                                                 const double* __restrict__ gain, uint8_t* target,
+                                                 unsigned long long* __restrict__ moves,
+                                                 const unsigned long long* __restrict__ prev,
+                                                 const int* __restrict__ flag) {
+    const int lane = threadIdx.x & (kWave - 1), grp = lane / kRowsPerWave, sub = lane & (kRowsPerWave - 1);
+    const int bad = *flag;
+    WaveRows r = wave_rows(g);
+    const double mine = r.in ? gain[r.i] : 0.0;
+    if (no_moves(prev) || bad) return;   // uniform over the grid
+    unsigned lost = 0;                   // bit v: a neighbour beats vertex v of the wave
+    const unsigned cand = (unsigned)__ballot(mine > 0.0) & 0xffffu;
+    if (cand) {
+        read_rows(g, r);
+        int64_t e[4], e1[4];
+        int32_t c[4];
+        double gi[4];
+        int ii[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int v = 4 * q + grp;
+            gi[q] = __shfl(mine, v, kWave);
+            ii[q] = (int)__shfl(r.i, v, kWave);
+            e[q] = __shfl(r.e0, v, kWave) + sub;
+            const int64_t end = __shfl(r.e1, v, kWave);
+            e1[q] = gi[q] > 0.0 ? end : 0;
+            c[q] = e[q] < e1[q] ? g.col[e[q]] : -1;
+        }
+        bool more = true;
+        while (more) {
+            double gj[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) gj[q] = c[q] >= 0 ? gain[c[q]] : 0.0;
+            more = false;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool beaten = gj[q] > 0.0 && (gj[q] > gi[q] || (gj[q] == gi[q] && c[q] < ii[q]));
+                const unsigned long long b = __ballot(beaten);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if ((b >> (kRowsPerWave * v)) & 0xffffull) lost |= 1u << (4 * q + v);
+                e[q] += kRowsPerWave;
+                c[q] = e[q] < e1[q] ? g.col[e[q]] : -1;
+                more |= __ballot(c[q] >= 0) != 0ull;
+            }
+        }
+    }
+    const unsigned wins = cand & ~lost;
+    if (wins) {
+        // no neighbour of a mover moves, so nobody marks a mover
+        if (grp == 0 && ((wins >> sub) & 1u)) {
+            const uint8_t t = target[r.i] & (kStale - 1);
+            z[r.i] = t;
+            target[r.i] = t | kStale;
+        }
+        int64_t e[4], e1[4];
+        bool more = false;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int v = 4 * q + grp;
+            e[q] = __shfl(r.e0, v, kWave) + sub;
+            const int64_t end = __shfl(r.e1, v, kWave);
+            e1[q] = (wins >> v) & 1u ? end : 0;
+            more |= __ballot(e[q] < e1[q]) != 0ull;
+        }
+        while (more) {
+            int32_t c[4];
+            uint8_t t[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] = e[q] < e1[q] ? g.col[e[q]] : -1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) t[q] = c[q] >= 0 ? target[c[q]] : 0;
+            more = false;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (c[q] >= 0) target[c[q]] = t[q] | kStale;
+                e[q] += kRowsPerWave;
+                more |= __ballot(e[q] < e1[q]) != 0ull;
+            }
+        }
     }
     // the block's count into one of kMoveLanes counters (block index mod
-    // kMoveLanes), so that same-address atomics stay few (at 10^6 vertices
-    // 1,954 blocks share them)
+    // kMoveLanes), so that same-address atomics stay few
     __shared__ unsigned int wm[kRefineBlock / kWave];
-    const unsigned long long bal = __ballot(win);
-    if ((threadIdx.x & (kWave - 1)) == 0) wm[threadIdx.x / kWave] = (unsigned)__popcll(bal);
+    if (lane == 0) wm[threadIdx.x / kWave] = (unsigned)__popc(wins);
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long b = 0;
@@ -290,59 +445,54 @@ __global__ __launch_bounds__(kRefineBlock) void k_move(GraphDev g, const uint8_t
     }
 }
 
+constexpr int kMaxCheck = 64;
+
+// What the host reads back, in one copy: the checks' verdict, an objective and
+// the move counters of the rounds of a batch.
+struct GraphReport {
+    int flag;
+    int pad;
+    double out[2];
+    alignas(256) unsigned long long moves[kMaxCheck * kMoveLanes];
+};
+constexpr size_t kReportHead = offsetof(GraphReport, moves);
+
 struct GraphScratch {
-    int* flag;
+    GraphReport* rep;     // moves only for the local search
     double* partial;
-    double* out2;
     double* table;        // sqd[K] then cosd[K]
     double* gain;
     uint8_t* target;
-    uint8_t* zb;
-    unsigned long long* moves;
 };
 
-constexpr int kMaxCheck = 64;
-
 struct HostScratch {
-    double* out;                  // [4]
-    int* flag;                    // [16]
-    unsigned long long* moves;    // [kMaxCheck][kMoveLanes]
+    GraphReport* rep;
     double* table;                // [2 * LRQO_MAX_K]
 };
 
 lrqo_status reserve_graph(DeviceCtx* ctx, int64_t n, bool refine, GraphScratch& s, HostScratch& h) {
     const int64_t blocks = (n + kBlock - 1) / kBlock;
     CarveSize cs;
-    cs.add<int>(16);
+    cs.add<char>(refine ? sizeof(GraphReport) : kReportHead);
     cs.add<double>(2 * blocks);
-    cs.add<double>(4);
     cs.add<double>(2 * LRQO_MAX_K);
     if (refine) {
         cs.add<double>(n);
         cs.add<uint8_t>(n);
-        cs.add<uint8_t>(n);
-        cs.add<unsigned long long>(kMaxCheck * kMoveLanes);
     }
     CarveSize hs;
-    hs.add<double>(4);
-    hs.add<int>(16);
-    hs.add<unsigned long long>(kMaxCheck * kMoveLanes);
+    hs.add<GraphReport>(1);
     hs.add<double>(2 * LRQO_MAX_K);
     LRQO_TRY(reserve_arena(ctx, cs.bytes));
     LRQO_TRY(reserve_host(ctx, hs.bytes));
     Carve cv(ctx->arena);
-    s.flag = cv.take<int>(16);
+    s.rep = reinterpret_cast<GraphReport*>(cv.take<char>(refine ? sizeof(GraphReport) : kReportHead));
     s.partial = cv.take<double>(2 * blocks);
-    s.out2 = cv.take<double>(4);
     s.table = cv.take<double>(2 * LRQO_MAX_K);
     s.gain = refine ? cv.take<double>(n) : nullptr;
     s.target = refine ? cv.take<uint8_t>(n) : nullptr;
-    s.zb = refine ? cv.take<uint8_t>(n) : nullptr;
-    s.moves = refine ? cv.take<unsigned long long>(kMaxCheck * kMoveLanes) : nullptr;
     Carve hv(ctx->host);
-    h.out = hv.take<double>(4);
-    h.flag = hv.take<int>(16);
-    h.moves = hv.take<unsigned long long>(kMaxCheck * kMoveLanes);
+    h.rep = hv.take<GraphReport>(1);
     h.table = hv.take<double>(2 * LRQO_MAX_K);
     return LRQO_OK;
 }
@@ -366,18 +516,41 @@ lrqo_status upload_tables(int K, const GraphScratch& s, double* h_tab, hipStream
     return LRQO_OK;
 }
 
-lrqo_status objective(const GraphDev& gd, int K, const uint8_t* z, const GraphScratch& s, double* h_out,
-                      hipStream_t st, double* quad, double* cut) {
+// Queues the objective of z into the report (skipped when a check failed).
+lrqo_status launch_objective(const GraphDev& gd, int K, const uint8_t* z, const GraphScratch& s, hipStream_t st) {
     const int64_t blocks = (gd.n + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_objective, dim3((unsigned)blocks), dim3(kBlock), 0, st, gd, K, z, s.table, s.partial);
+    hipLaunchKernelGGL(k_objective, dim3((unsigned)blocks), dim3(kBlock), 0, st, gd, K, z, s.table, s.partial,
+                       &s.rep->flag);
+    hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kBlock), 0, st, s.partial, blocks, s.rep->out);
     LRQO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sum2, dim3(1), dim3(kBlock), 0, st, s.partial, blocks, s.out2);
+    return LRQO_OK;
+}
+
+// Queues the layout checks: *d_flag is cleared, then holds what they found.
+lrqo_status launch_checks(const GraphDev& gd, int K, const uint8_t* z, int* d_flag, int* h_flag, hipStream_t st) {
+    const unsigned blocks = (unsigned)((gd.n + kBlock - 1) / kBlock);
+    *h_flag = 0;
+    LRQO_HIP(hipMemcpyAsync(d_flag, h_flag, sizeof(int), hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_check_ptr, dim3(blocks), dim3(kBlock), 0, st, gd, d_flag);
+    hipLaunchKernelGGL(k_check_rows, dim3(blocks), dim3(kBlock), 0, st, gd, K, z, d_flag);
     LRQO_HIP(hipGetLastError());
-    LRQO_HIP(hipMemcpyAsync(h_out, s.out2, sizeof(double) * 2, hipMemcpyDeviceToHost, st));
+    return LRQO_OK;
+}
+
+lrqo_status read_checks(int flag) {
+    if (flag & kBadPtr)
+        return fail(LRQO_EINVAL, "row_ptr is not a CSR row pointer (row_ptr[0] = 0, non-decreasing, row_ptr[n] = nnz)");
+    if (flag & kBadCol) return fail(LRQO_EINVAL, "a column index is out of range or a self loop");
+    if (flag & kBadWeight) return fail(LRQO_EINVAL, "a weight is not finite");
+    if (flag & kBadLabel) return fail(LRQO_EINVAL, "a label is not below K");
+    return LRQO_OK;
+}
+
+// The report (its first `bytes`) to the host; every edge was seen from both
+// of its ends.
+lrqo_status read_report(const GraphScratch& s, const HostScratch& h, size_t bytes, hipStream_t st) {
+    LRQO_HIP(hipMemcpyAsync(h.rep, s.rep, bytes, hipMemcpyDeviceToHost, st));
     LRQO_HIP(hipStreamSynchronize(st));
-    // every edge was seen from both of its ends
-    *quad = 0.5 * h_out[0];
-    *cut = 0.5 * h_out[1];
     return LRQO_OK;
 }
 
@@ -398,22 +571,10 @@ lrqo_status check_graph_args(const lrqo_graph* g) {
 lrqo_status validate_graph(const lrqo_graph* g, int K, const uint8_t* z, int* d_flag, int* h_flag,
                            hipStream_t st) {
     const GraphDev gd{g->row_ptr, g->col, g->w, g->n, g->nnz};
-    const unsigned blocks = (unsigned)((gd.n + kBlock - 1) / kBlock);
-    *h_flag = 0;
-    LRQO_HIP(hipMemcpyAsync(d_flag, h_flag, sizeof(int), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_check_ptr, dim3(blocks), dim3(kBlock), 0, st, gd, d_flag);
-    LRQO_HIP(hipGetLastError());
+    LRQO_TRY(launch_checks(gd, K, z, d_flag, h_flag, st));
     LRQO_HIP(hipMemcpyAsync(h_flag, d_flag, sizeof(int), hipMemcpyDeviceToHost, st));
     LRQO_HIP(hipStreamSynchronize(st));
-    if (*h_flag) return fail(LRQO_EINVAL, "row_ptr is not a CSR row pointer (row_ptr[0] = 0, non-decreasing, row_ptr[n] = nnz)");
-    hipLaunchKernelGGL(k_check_rows, dim3(blocks), dim3(kBlock), 0, st, gd, K, z, d_flag);
-    LRQO_HIP(hipGetLastError());
-    LRQO_HIP(hipMemcpyAsync(h_flag, d_flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    LRQO_HIP(hipStreamSynchronize(st));
-    if (*h_flag & kBadCol) return fail(LRQO_EINVAL, "a column index is out of range or a self loop");
-    if (*h_flag & kBadWeight) return fail(LRQO_EINVAL, "a weight is not finite");
-    if (*h_flag & kBadLabel) return fail(LRQO_EINVAL, "a label is not below K");
-    return LRQO_OK;
+    return read_checks(*h_flag);
 }
 
 }  // namespace lrqo
@@ -436,9 +597,14 @@ lrqo_status lrqo_graph_objective(const lrqo_graph* g, int32_t K, const uint8_t* 
     HostScratch h{};
     LRQO_TRY(reserve_graph(ctx, g->n, false, s, h));
     const GraphDev gd{g->row_ptr, g->col, g->w, g->n, g->nnz};
-    LRQO_TRY(validate_graph(g, K, z, s.flag, h.flag, st));
+    LRQO_TRY(launch_checks(gd, K, z, &s.rep->flag, &h.rep->flag, st));
     LRQO_TRY(upload_tables(K, s, h.table, st));
-    return objective(gd, K, z, s, h.out, st, quad, cut);
+    LRQO_TRY(launch_objective(gd, K, z, s, st));
+    LRQO_TRY(read_report(s, h, kReportHead, st));
+    LRQO_TRY(read_checks(h.rep->flag));
+    *quad = 0.5 * h.rep->out[0];
+    *cut = 0.5 * h.rep->out[1];
+    return LRQO_OK;
 }
 
 lrqo_status lrqo_refine_greedy(const lrqo_graph* g, int32_t K, uint8_t* z, const lrqo_refine_options* opt,
@@ -463,49 +629,56 @@ lrqo_status lrqo_refine_greedy(const lrqo_graph* g, int32_t K, uint8_t* z, const
     HostScratch h{};
     LRQO_TRY(reserve_graph(ctx, g->n, true, s, h));
     const GraphDev gd{g->row_ptr, g->col, g->w, g->n, g->nnz};
-    LRQO_TRY(validate_graph(g, K, z, s.flag, h.flag, st));
+    LRQO_TRY(launch_checks(gd, K, z, &s.rep->flag, &h.rep->flag, st));
     LRQO_TRY(upload_tables(K, s, h.table, st));
+    LRQO_TRY(launch_objective(gd, K, z, s, st));
 
     lrqo_refine_result r{};
-    LRQO_TRY(objective(gd, K, z, s, h.out, st, &r.quad_before, &r.cut_before));
-
+    constexpr int64_t kRowsPerBlock = kRefineBlock / kWave * kRowsPerWave;
     const unsigned blocks = (unsigned)((gd.n + kRefineBlock - 1) / kRefineBlock);
+    const unsigned row_blocks = (unsigned)((gd.n + kRowsPerBlock - 1) / kRowsPerBlock);
     const double* cosd = s.table + LRQO_MAX_K;
-    uint8_t* zbuf[2] = {z, s.zb};
-    int cur = 0;
+    const int* flag = &s.rep->flag;
     int64_t rounds = 0, moves = 0, launched = 0;
     bool converged = false;
     float total_ms = 0.0f;
     while (!converged && rounds < max_rounds) {
         const int todo = (int)std::min<int64_t>(chunk, max_rounds - rounds);
-        LRQO_HIP(hipMemsetAsync(s.moves, 0, sizeof(unsigned long long) * todo * kMoveLanes, st));
+        LRQO_HIP(hipMemsetAsync(s.rep->moves, 0, sizeof(unsigned long long) * todo * kMoveLanes, st));
         LRQO_HIP(hipEventRecord(ctx->ev_start, st));
         for (int t = 0; t < todo; ++t) {
             // the batch runs only after rounds that all moved something
-            const unsigned long long* prev = t ? s.moves + (size_t)(t - 1) * kMoveLanes : nullptr;
-            if (K <= 4)
-                hipLaunchKernelGGL(k_gain<4>, dim3(blocks), dim3(kRefineBlock), 0, st, gd, K, zbuf[cur], cosd, s.gain,
-                                   s.target, prev);
+            const unsigned long long* prev = t ? s.rep->moves + (size_t)(t - 1) * kMoveLanes : nullptr;
+            const bool first = launched == 0 && t == 0;
+            if (K <= 4 && !g->w)
+                hipLaunchKernelGGL(k_gain_unit, dim3(row_blocks), dim3(kRefineBlock), 0, st, gd, K, z, cosd, s.gain,
+                                   s.target, first, prev, flag);
+            else if (K <= 4)
+                hipLaunchKernelGGL(k_gain<4>, dim3(blocks), dim3(kRefineBlock), 0, st, gd, K, z, cosd, s.gain,
+                                   s.target, first, prev, flag);
             else
-                hipLaunchKernelGGL(k_gain<kMaxKRefine>, dim3(blocks), dim3(kRefineBlock), 0, st, gd, K, zbuf[cur], cosd,
-                                   s.gain, s.target, prev);
-            hipLaunchKernelGGL(k_move, dim3(blocks), dim3(kRefineBlock), 0, st, gd, zbuf[cur], s.gain, s.target,
-                               zbuf[cur ^ 1], s.moves + (size_t)t * kMoveLanes, prev);
-            cur ^= 1;
+                hipLaunchKernelGGL(k_gain<kMaxKRefine>, dim3(blocks), dim3(kRefineBlock), 0, st, gd, K, z, cosd,
+                                   s.gain, s.target, first, prev, flag);
+            hipLaunchKernelGGL(k_move, dim3(row_blocks), dim3(kRefineBlock), 0, st, gd, z, s.gain, s.target,
+                               s.rep->moves + (size_t)t * kMoveLanes, prev, flag);
         }
         LRQO_HIP(hipGetLastError());
         LRQO_HIP(hipEventRecord(ctx->ev_stop, st));
+        const bool head = launched == 0;
         launched += todo;
-        LRQO_HIP(hipMemcpyAsync(h.moves, s.moves, sizeof(unsigned long long) * todo * kMoveLanes,
-                                hipMemcpyDeviceToHost, st));
-        LRQO_HIP(hipStreamSynchronize(st));
+        LRQO_TRY(read_report(s, h, kReportHead + sizeof(unsigned long long) * todo * kMoveLanes, st));
+        if (head) {
+            LRQO_TRY(read_checks(h.rep->flag));
+            r.quad_before = 0.5 * h.rep->out[0];
+            r.cut_before = 0.5 * h.rep->out[1];
+        }
         float ms = 0.0f;
         LRQO_HIP(hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop));
         total_ms += ms;
         // a round without moves leaves the labels as they were, and so do all after it
         for (int t = 0; t < todo; ++t) {
             unsigned long long m = 0;
-            for (int l = 0; l < kMoveLanes; ++l) m += h.moves[(size_t)t * kMoveLanes + l];
+            for (int l = 0; l < kMoveLanes; ++l) m += h.rep->moves[(size_t)t * kMoveLanes + l];
             if (m == 0) {
                 converged = true;
                 break;
@@ -514,11 +687,10 @@ lrqo_status lrqo_refine_greedy(const lrqo_graph* g, int32_t K, uint8_t* z, const
             moves += (int64_t)m;
         }
     }
-    // round t reads labels from buffer t mod 2 and writes the other; rounds
-    // after the first one without moves were skipped, so the result is in
-    // buffer rounds mod 2 (the caller's z is buffer 0)
-    if (rounds % 2 == 1) LRQO_HIP(hipMemcpyAsync(z, s.zb, (size_t)gd.n, hipMemcpyDeviceToDevice, st));
-    LRQO_TRY(objective(gd, K, z, s, h.out, st, &r.quad_after, &r.cut_after));
+    LRQO_TRY(launch_objective(gd, K, z, s, st));
+    LRQO_TRY(read_report(s, h, kReportHead, st));
+    r.quad_after = 0.5 * h.rep->out[0];
+    r.cut_after = 0.5 * h.rep->out[1];
     r.moves = moves;
     r.rounds = (int32_t)rounds;
     r.converged = converged ? 1 : 0;

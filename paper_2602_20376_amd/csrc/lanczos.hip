@@ -28,7 +28,9 @@
 // their vectors by inverse iteration; |beta_j s_{j,k}| bounds the residual of
 // Ritz pair k.  The check runs on a stream of its own while the next step is
 // computed, and the host reads its verdict before it launches the step after
-// that; at convergence that one step is left unused.  At convergence the
+// that; at convergence that one step is left unused.  Where a step costs more
+// than the waits of a whole run (about 70 us each) the host reads the verdict
+// before the step's large kernels.  At convergence the
 // Ritz vectors U = Q S are formed, each is rotated so that its
 // largest-modulus entry is real positive, and scaled by sqrt(max(theta, 0)).
 // All sums are fixed-order.
@@ -110,12 +112,13 @@ __device__ __forceinline__ void lap_chunk(const LapOp& g, const double2* __restr
     }
 }
 
-// beta = sqrt of the sum of the partial squares, in every thread: each wave
-// adds them all (lanes strided, then a butterfly: the same sum everywhere).
+// beta = sqrt of the sum of the partial squares, in every thread of the block
+// (threads strided, then the block's tree: the same sum in every block).
 __device__ __forceinline__ double beta_of(const double* __restrict__ part, int count) {
-    double a = 0.0;
-    for (int t = threadIdx.x & (kWave - 1); t < count; t += kWave) a += part[t];
-    return sqrt(wave_sum_f64(a));
+    double a = 0.0, b = 0.0;
+    for (int t = threadIdx.x; t < count; t += kBlock) a += part[t];
+    block_sum2(a, b);
+    return sqrt(a);
 }
 
 // q = w / beta (stored) and y = L q, gathering w and scaling on the fly;
@@ -357,14 +360,14 @@ __global__ __launch_bounds__(kSymT) void k_w_combine(PhaseOp o, const double2* _
 // the values a lane holds: 17 shuffles instead of 16 x 6) and the four waves in
 // order, giving part[b k + j]; the update's blocks add the nb partials of each
 // column.  Q is read once, by as many blocks as there are row chunks times
-// column groups; dot_chunk_rows keeps that near kDotBlocks, one a CU, which bounds
-// what the update's blocks read to 8 kDotBlocks entries (32 KB).  n = 100,000,
-// 45 columns on average: dots 17.3 us, update 15.1 us; with 512 blocks 17.8
-// and 15.6, with 1,024 20.2 and 16.6.
+// column groups; below kDotFold rows dot_chunk_rows keeps that near one a CU, which
+// bounds what each of the update's blocks reads to 32 KB (n = 100,000, 45
+// columns on average: dots 17.3 us, update 15.1 us with 256 blocks, 17.8 and
+// 15.6 with 512, 20.2 and 16.6 with 1,024).  Above, the update has so many
+// blocks that their reading of the partials costs more than a launch
+// (n = 900,000: update 131 us against 122), and k_part_sum adds them first.
 constexpr int kDotRowsMax = 4096;
 constexpr int kDotCols = 8;
-
-constexpr int kDotBlocks = 256;
 
 int dot_rows(int64_t n) {
     int64_t rows = ((n + 255) / 256 + 255) / 256 * 256;
@@ -372,11 +375,14 @@ int dot_rows(int64_t n) {
 }
 
 // Rows of a chunk for k columns: dot_rows(n) while the column groups are few,
-// then as many more as keep the blocks near kDotBlocks.
+// then as many more as keep the number of blocks.
+constexpr int64_t kDotFold = 256000;
+
 int dot_chunk_rows(int64_t n, int k) {
-    const int64_t groups = (k + kDotCols - 1) / kDotCols, chunks = std::max<int64_t>(1, kDotBlocks / groups);
+    if (n >= kDotFold) return dot_rows(n);
+    const int64_t groups = (k + kDotCols - 1) / kDotCols, chunks = std::max<int64_t>(1, 256 / groups);
     const int64_t rows = ((n + chunks - 1) / chunks + 255) / 256 * 256;
-    return (int)std::min<int64_t>(std::max<int64_t>(rows, dot_rows(n)), (int64_t)1 << 30);
+    return (int)std::max<int64_t>(rows, dot_rows(n));
 }
 
 // Wave sums of the 16 values acc[0..15]: at the exchange with lane
@@ -495,17 +501,33 @@ __global__ __launch_bounds__(kBlock) void k_scale_utx(PhaseOp o, const double2* 
     if (o.p > 0) block_sums_to(acc, o.p, reinterpret_cast<double*>(part + b), 2 * (int64_t)nb);
 }
 
+// h_j = sum_b part[b k + j], one wave per column
+__global__ __launch_bounds__(kWave) void k_part_sum(const double2* __restrict__ part, int nb, double2* __restrict__ h) {
+    const int j = blockIdx.x, k = gridDim.x;
+    double ar = 0.0, ai = 0.0;
+    for (int b = threadIdx.x; b < nb; b += kWave) {
+        const double2 v = part[(int64_t)b * k + j];
+        ar += v.x;
+        ai += v.y;
+    }
+    ar = wave_sum_f64(ar);
+    ai = wave_sum_f64(ai);
+    if (threadIdx.x == 0) h[j] = make_double2(ar, ai);
+}
+
 // w -= sum_{j<k} q_j h_j, h_j = sum_b part[b k + j].  Each block adds the
 // partials itself (S strided runs per column, four loads in flight, then the
 // runs in order).  alpha: Re of the last h (block 0).  npart: the block's sum
 // of |w|^2 after the update.  (Four threads a row, each with a quarter of the
 // columns, ran no faster: n = 100,000, 45 columns on average, 19.0 us against
 // 17.9.)
-__global__ __launch_bounds__(kBlock) void k_sub(const double2* __restrict__ Q, int64_t n, int k,
+// Four waves a SIMD asked for: sixteen loads a thread take 92 VGPRs (left to
+// itself the compiler keeps 62 and eight loads).
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_sub(const double2* __restrict__ Q, int64_t n, int k,
                                                 const double2* __restrict__ part, int nb, double2* __restrict__ w,
                                                 double* __restrict__ alpha, double* __restrict__ npart) {
-    __shared__ double2 hs[kMaxIter + 1];
-    __shared__ double2 runs[kBlock];
+    extern __shared__ double2 hs[];                      // k entries, then kBlock run sums
+    double2* runs = hs + k;
     const int tid = threadIdx.x;
     const int S = k >= kBlock ? 1 : kBlock / k;
     for (int e = tid; e < S * k; e += kBlock) {          // one trip when S > 1
@@ -542,8 +564,9 @@ __global__ __launch_bounds__(kBlock) void k_sub(const double2* __restrict__ Q, i
     }
     __syncthreads();
     if (alpha && blockIdx.x == 0 && tid == 0) alpha[0] = hs[k - 1].x;
-    double sq = 0.0, unused = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)kBlock + tid; i < n; i += (int64_t)gridDim.x * kBlock) {
+    double sq = 0.0;
+    const int64_t i = blockIdx.x * (int64_t)kBlock + tid;
+    if (i < n) {
         double ar = 0.0, ai = 0.0;
         // sixteen column loads in flight per thread, the sum still in column order
         auto cols = [&](auto U, int& j) {
@@ -570,8 +593,14 @@ __global__ __launch_bounds__(kBlock) void k_sub(const double2* __restrict__ Q, i
         sq += v.x * v.x + v.y * v.y;
     }
     if (npart) {
-        block_sum2(sq, unused);
-        if (tid == 0) npart[blockIdx.x] = sq;
+        __shared__ double red[kBlock / kWave];
+        sq = wave_sum_f64(sq);
+        if ((tid & (kWave - 1)) == 0) red[tid / kWave] = sq;
+        __syncthreads();
+        if (tid == 0) {
+            for (int q = 1; q < kBlock / kWave; ++q) sq += red[q];
+            npart[blockIdx.x] = sq;
+        }
     }
 }
 
@@ -583,6 +612,14 @@ __global__ __launch_bounds__(kBlock) void k_norm_part(const double2* __restrict_
     }
     block_sum2(a, b);
     if (threadIdx.x == 0) part[blockIdx.x] = a;
+}
+
+// Sum of the partial squares of many blocks, in one block.
+__global__ __launch_bounds__(kBlock) void k_fold(const double* __restrict__ part, int64_t count, double* __restrict__ out) {
+    double a = 0.0, b = 0.0;
+    for (int64_t t = threadIdx.x; t < count; t += kBlock) a += part[t];
+    block_sum2(a, b);
+    if (threadIdx.x == 0) out[0] = a;
 }
 
 // beta at the last step, which no further step scales by
@@ -925,6 +962,7 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
     const int drows = dot_rows(n);
     const int nbd = (int)((n + drows - 1) / drows);
     cs.add<double2>((size_t)(kMaxIter + 1) * nbd);  // partial dots (and of U^H x, before them)
+    cs.add<double2>(kMaxIter + 1);                // h
     cs.add<double2>(LRQO_MAX_R);                  // column phases
     cs.add<double>(nparts);                       // norm partials
     cs.add<double>(kMaxIter + 1);                 // alpha
@@ -976,6 +1014,7 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
     double2* Q = cv.take<double2>((size_t)n * (max_iter + 1));
     double2* w = cv.take<double2>(n);
     double2* dpart = cv.take<double2>((size_t)(kMaxIter + 1) * nbd);
+    double2* hsum = cv.take<double2>(kMaxIter + 1);
     double2* uc = cv.take<double2>(LRQO_MAX_R);
     double* npart = cv.take<double>(nparts);
     double* alpha = cv.take<double>(kMaxIter + 1);
@@ -1004,12 +1043,14 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
     double* h_tr = hv.take<double>(2 * LRQO_MAX_R + 1);     // theta, residual bounds, breakdown index
 
     // q_j = w / beta_{j-1} into dst and A q_j into y (start vector: no beta)
+    // partial squares of beta: one per block, folded into one where npart cannot hold them
+    int ncount = nparts;
     auto scale_apply = [&](const double2* from, double2* dst, double2* y, double* bet) -> lrqo_status {
         if (kind == kOpLap) {
-            hipLaunchKernelGGL(k_apply_lap, dim3((unsigned)blocks), dim3(kBlock), 0, st, lap, from, npart, nparts, dst,
+            hipLaunchKernelGGL(k_apply_lap, dim3((unsigned)blocks), dim3(kBlock), 0, st, lap, from, npart, ncount, dst,
                                y, bet);
         } else {
-            hipLaunchKernelGGL(k_scale_utx, dim3(nbd), dim3(kBlock), 0, st, ph, from, npart, nparts, drows, nbd, dst,
+            hipLaunchKernelGGL(k_scale_utx, dim3(nbd), dim3(kBlock), 0, st, ph, from, npart, ncount, drows, nbd, dst,
                                dpart, bet);
         }
         LRQO_HIP(hipGetLastError());
@@ -1054,6 +1095,16 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
         for (int k = 0; k < r; ++k) converged &= h_tr[LRQO_MAX_R + k] <= tol * scale;
         return LRQO_OK;
     };
+    // whether a step is launched in full beside the check: a Laplacian step
+    // below kDotFold rows takes under 0.2 ms (n = 997,712: 0.65 ms, and the
+    // unused step made a factor 1.6% slower), a product with W of
+    // n = 49,152 about 1.7 ms
+    const bool ahead = kind == kOpLap ? n < kDotFold : n <= 49152;
+    auto read_check = [&](int j) -> lrqo_status {
+        pending = false;
+        LRQO_HIP(hipEventSynchronize(ctx->ev_join));
+        return verdict(j, false);
+    };
     double2 *cur = w, *other = Uo;
     int last = 0;           // steps launched
     for (int j = 0; j < max_iter; ++j) {
@@ -1064,6 +1115,10 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
             LRQO_HIP(hipStreamWaitEvent(ctx->side, ctx->ev_fork, 0));
             LRQO_TRY(tridiag(j, false, ctx->side));
             LRQO_HIP(hipEventRecord(ctx->ev_join, ctx->side));
+            if (!ahead) {
+                LRQO_TRY(read_check(j));
+                if (m < r || converged || breakdown) break;
+            }
         }
         std::swap(cur, other);
         LRQO_TRY(w_product(qj, cur));
@@ -1071,20 +1126,27 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
         for (int pass = 0; pass < 2; ++pass) {
             hipLaunchKernelGGL(k_dots_part, dim3(nb, (k + kDotCols - 1) / kDotCols), dim3(kBlock), 0, st, Q, n, cur,
                                k, rows, dpart);
-            hipLaunchKernelGGL(k_sub, dim3(nparts), dim3(kBlock), 0, st, Q, n, k, dpart, nb, cur,
-                               pass == 0 ? alpha + j : nullptr, pass == 1 ? npart : nullptr);
+            const bool fold = n >= kDotFold;
+            if (fold) hipLaunchKernelGGL(k_part_sum, dim3(k), dim3(kWave), 0, st, dpart, nb, hsum);
+            // a row a thread; the partial squares of more blocks than npart
+            // holds go to the vector that is free, and are folded
+            double* squares = blocks > nparts ? reinterpret_cast<double*>(other) : npart;
+            hipLaunchKernelGGL(k_sub, dim3((unsigned)blocks), dim3(kBlock), sizeof(double2) * (k + kBlock), st, Q, n, k,
+                               fold ? hsum : dpart, fold ? 1 : nb, cur, pass == 0 ? alpha + j : nullptr, pass == 1 ? squares : nullptr);
+        }
+        if (blocks > nparts) {
+            hipLaunchKernelGGL(k_fold, dim3(1), dim3(kBlock), 0, st, reinterpret_cast<const double*>(other), blocks, npart);
+            ncount = 1;
         }
         LRQO_HIP(hipGetLastError());
         last = j + 1;
         if (pending) {
-            pending = false;
-            LRQO_HIP(hipEventSynchronize(ctx->ev_join));
-            LRQO_TRY(verdict(j, false));
+            LRQO_TRY(read_check(j));
             if (m < r || converged || breakdown) break;
         }
         const bool check = last >= r && (last % every == 0 || last == max_iter || last == n);
         if (check && (last == max_iter || last == n)) {
-            hipLaunchKernelGGL(k_beta, dim3(1), dim3(kBlock), 0, st, npart, nparts, beta + j);
+            hipLaunchKernelGGL(k_beta, dim3(1), dim3(kBlock), 0, st, npart, ncount, beta + j);
             LRQO_TRY(tridiag(last, last == n, st));
             LRQO_HIP(hipStreamSynchronize(st));
             LRQO_TRY(verdict(last, last == n));
