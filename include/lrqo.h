@@ -367,8 +367,8 @@ typedef struct lrqo_rank1_result {
     double sweep_obj;        /* the chosen cell's value from the sweep's prefix sums */
     int64_t best_cell;       /* 0: assignment at phi = -pi/K; l: after the l-th boundary point */
     float device_ms;
-    int32_t sort_passes;     /* 8-bit radix passes run: 4 over 32-bit images of the points, plus
-                                those over the exact 64-bit keys (digits that differ) when a run
+    int32_t sort_passes;     /* 8-bit digits sorted: the 4 of the points' 32-bit images, plus
+                                those of the exact 64-bit keys (digits that differ) when a run
                                 of more than 16 equal images holds distinct points */
 } lrqo_rank1_result;
 
