@@ -179,9 +179,10 @@ lrqo_status lrqo_solve_sampled_ex(const float* V, int64_t n, int32_t r, int32_t 
     DevResult* hres = static_cast<DevResult*>(ctx->host);
 
     LRQO_HIP(hipEventRecord(ctx->ev_start, st));
+    if (plan.tail) job.host_result = hres;   // its last kernel writes the pinned record itself
     LRQO_TRY(launch_sampled(job, plan, ctx->arena, st));
     // the result block sits first in the arena
-    LRQO_HIP(hipMemcpyAsync(hres, ctx->arena, sizeof(DevResult), hipMemcpyDeviceToHost, st));
+    if (!plan.tail) LRQO_HIP(hipMemcpyAsync(hres, ctx->arena, sizeof(DevResult), hipMemcpyDeviceToHost, st));
     LRQO_HIP(hipEventRecord(ctx->ev_stop, st));
     LRQO_HIP(hipStreamSynchronize(st));
     float ms = 0.0f, score_ms = 0.0f;

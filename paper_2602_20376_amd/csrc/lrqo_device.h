@@ -109,6 +109,47 @@ __device__ __forceinline__ int label_f32_generic(float wr, float wi, int K) {
     return (wr == 0.0f && wi == 0.0f) ? 0 : k;
 }
 
+// ---------------------------------------------------------------- lane exchange
+// The value of lane ^ M, M a power of two below 64, by the vector ALU: quad
+// permutes (1, 2), a half-row mirror and a quad permute (4), a row rotation
+// (8), row and half-wave swaps (16, 32).  A shuffle goes through the LDS
+// crossbar and its latency (about 130 cycles a step of a 64-key sort, whose 21
+// steps depend on each other); these take a few.  Every lane of the wave must
+// take part.
+template <int M>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x) {
+    static_assert(M == 1 || M == 2 || M == 4 || M == 8 || M == 16 || M == 32, "one bit of the lane");
+    if constexpr (M == 1) return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);
+    else if constexpr (M == 2) return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);
+    else if constexpr (M == 4)
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (M == 8) return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);
+    else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (__lane_id() & 16) ? r[0] : r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (__lane_id() & 32) ? r[0] : r[1];
+    }
+}
+
+template <int M>
+__device__ __forceinline__ unsigned long long lane_xor(unsigned long long x) {
+    return ((unsigned long long)lane_xor<M>((uint32_t)(x >> 32)) << 32) | lane_xor<M>((uint32_t)x);
+}
+
+template <int M>
+__device__ __forceinline__ double lane_xor(double x) {
+    return __longlong_as_double((long long)lane_xor<M>((unsigned long long)__double_as_longlong(x)));
+}
+
+// The value of lane 63 - lane.
+__device__ __forceinline__ unsigned long long lane_reverse(unsigned long long x) {
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(x >> 32), 0x140, 0xF, 0xF, true);   // within rows of 16
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)x, 0x140, 0xF, 0xF, true);
+    return lane_xor<32>(lane_xor<16>(((unsigned long long)hi << 32) | lo));
+}
+
 // ---------------------------------------------------------------- reductions
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
 #pragma unroll
@@ -120,8 +161,12 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
 }
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+    v += lane_xor<32>(v);
+    v += lane_xor<16>(v);
+    v += lane_xor<8>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    v += lane_xor<1>(v);
     return v;
 }
 
@@ -137,28 +182,37 @@ __device__ __forceinline__ unsigned long long key_min(unsigned long long a, unsi
     return a < b ? a : b;
 }
 
+// One step: the lane and its partner at distance J keep the larger key where
+// keep_max is set, else the smaller.
+template <int J>
+__device__ __forceinline__ unsigned long long exchange(unsigned long long x, bool keep_max) {
+    const unsigned long long y = lane_xor<J>(x);
+    return (x > y) == keep_max ? x : y;
+}
+
+// The last steps of a bitonic merge, distances J, J/2, ..., 1, into
+// descending order where `desc`, else ascending.
+template <int J>
+__device__ __forceinline__ unsigned long long merge_steps(unsigned long long x, int lane, bool desc) {
+    x = exchange<J>(x, ((lane & J) == 0) == desc);
+    if constexpr (J > 1) x = merge_steps<J / 2>(x, lane, desc);
+    return x;
+}
+
 // One key per lane, returned sorted descending by lane.
 __device__ __forceinline__ unsigned long long wave_sort_desc(unsigned long long x, int lane) {
-    for (int k = 2; k <= 64; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const unsigned long long y = __shfl_xor(x, j, 64);
-            // in a descending run the lower lane of a pair keeps the larger key
-            const bool keep_max = ((lane & j) == 0) == ((lane & k) == 0);
-            x = keep_max ? key_max(x, y) : key_min(x, y);
-        }
-    }
-    return x;
+    x = merge_steps<1>(x, lane, (lane & 2) == 0);
+    x = merge_steps<2>(x, lane, (lane & 4) == 0);
+    x = merge_steps<4>(x, lane, (lane & 8) == 0);
+    x = merge_steps<8>(x, lane, (lane & 16) == 0);
+    x = merge_steps<16>(x, lane, (lane & 32) == 0);
+    return merge_steps<32>(x, lane, true);
 }
 
 // Best 64 of two descending lists (one key per lane), descending.
 __device__ __forceinline__ unsigned long long wave_top_union(unsigned long long a,
                                                              unsigned long long b, int lane) {
-    unsigned long long x = key_max(a, __shfl(b, 63 - lane, 64));  // bitonic, holds the best 64
-    for (int j = 32; j > 0; j >>= 1) {
-        const unsigned long long y = __shfl_xor(x, j, 64);
-        x = (lane & j) == 0 ? key_max(x, y) : key_min(x, y);
-    }
-    return x;
+    return merge_steps<32>(key_max(a, lane_reverse(b)), lane, true);   // bitonic, holds the best 64
 }
 
 // Best 64 keys of two descending lists with one key per objective value: the
@@ -169,14 +223,9 @@ __device__ __forceinline__ unsigned long long wave_top_union(unsigned long long 
 // the result a list padded at its end.
 __device__ __forceinline__ unsigned long long wave_top_union_distinct(unsigned long long a,
                                                                       unsigned long long b, int lane) {
-    const unsigned long long br = __shfl(b, 63 - lane, 64);
-    unsigned long long hi = key_max(a, br), lo = key_min(a, br);
-    for (int j = 32; j > 0; j >>= 1) {
-        const unsigned long long yh = __shfl_xor(hi, j, 64), yl = __shfl_xor(lo, j, 64);
-        const bool up = (lane & j) == 0;
-        hi = up ? key_max(hi, yh) : key_min(hi, yh);
-        lo = up ? key_max(lo, yl) : key_min(lo, yl);
-    }
+    const unsigned long long br = lane_reverse(b);
+    unsigned long long hi = merge_steps<32>(key_max(a, br), lane, true);
+    unsigned long long lo = merge_steps<32>(key_min(a, br), lane, true);
     // hi holds positions 0..63 of the merged sequence, lo positions 64..127
     const unsigned long long h63 = __shfl(hi, 63, 64);
     const unsigned long long hp = __shfl_up(hi, 1, 64);

@@ -18,6 +18,8 @@
 //   k_rescore       FP64 re-evaluation of each kept direction, row-sliced
 //   k_pick          FP64 arg-max of the rescored candidates (ties -> lowest index)
 //   k_labels        FP64 decision rule of the winner -> uint8 labels
+//   k_tail          small problems: the selection to the labels in one block,
+//                   and where the scorer needs neither, the prologue's checks
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -121,6 +123,40 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const float* __restrict__ p
 }
 
 // ------------------------------------------------------------ FP64 rescore
+// One row's FP64 terms of conj(V_i) z_i, added to acc (a real V leaves out
+// the products with Im V: half the FP64 work).
+template <int R, bool REAL, int KS>
+__device__ __forceinline__ void rescore_row(const float (&row)[Row<R, REAL>::F], const double (&c)[2 * R], int K,
+                                            const double2* roots, double (&acc)[2 * R]) {
+    double wr = 0.0, wi = 0.0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if constexpr (REAL) {
+            const double vr = (double)row[j];
+            wr += vr * c[2 * j];
+            wi += vr * c[2 * j + 1];
+        } else {
+            const double vr = (double)row[2 * j], vi = (double)row[2 * j + 1];
+            wr += vr * c[2 * j] - vi * c[2 * j + 1];
+            wi += vr * c[2 * j + 1] + vi * c[2 * j];
+        }
+    }
+    double zr, zi;
+    nearest_root64<KS>(wr, wi, K, roots, zr, zi);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        if constexpr (REAL) {
+            const double vr = (double)row[j];
+            acc[2 * j] += vr * zr;
+            acc[2 * j + 1] += vr * zi;
+        } else {
+            const double vr = (double)row[2 * j], vi = (double)row[2 * j + 1];
+            acc[2 * j] += vr * zr + vi * zi;
+            acc[2 * j + 1] += vr * zi - vi * zr;
+        }
+    }
+}
+
 template <int R, bool REAL, int KS>
 __global__ __launch_bounds__(kBlock) void k_rescore(RescoreParams p) {
     __shared__ double2 roots_s[LRQO_MAX_K];
@@ -140,37 +176,6 @@ __global__ __launch_bounds__(kBlock) void k_rescore(RescoreParams p) {
     const int64_t r0 = (int64_t)blockIdx.y * p.rows_per_slice;
     const int64_t r1 = min(p.n, r0 + p.rows_per_slice);
     constexpr int RF = Row<R, REAL>::F;
-    // one row's FP64 terms, added to acc
-    // (a real V leaves out the products with Im V: half the FP64 work)
-    auto add_row = [&](const float (&row)[RF]) {
-        double wr = 0.0, wi = 0.0;
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if constexpr (REAL) {
-                const double vr = (double)row[j];
-                wr += vr * c[2 * j];
-                wi += vr * c[2 * j + 1];
-            } else {
-                const double vr = (double)row[2 * j], vi = (double)row[2 * j + 1];
-                wr += vr * c[2 * j] - vi * c[2 * j + 1];
-                wi += vr * c[2 * j + 1] + vi * c[2 * j];
-            }
-        }
-        double zr, zi;
-        nearest_root64<KS>(wr, wi, p.K, roots_s, zr, zi);
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if constexpr (REAL) {
-                const double vr = (double)row[j];
-                acc[2 * j] += vr * zr;
-                acc[2 * j + 1] += vr * zi;
-            } else {
-                const double vr = (double)row[2 * j], vi = (double)row[2 * j + 1];
-                acc[2 * j] += vr * zr + vi * zi;
-                acc[2 * j + 1] += vr * zi - vi * zr;
-            }
-        }
-    };
     // four rows' loads in flight; the rows are still added in order
     int64_t i = r0 + threadIdx.x;
     for (; i + 3 * kBlock < r1; i += 4 * kBlock) {
@@ -180,13 +185,13 @@ __global__ __launch_bounds__(kBlock) void k_rescore(RescoreParams p) {
 #pragma unroll
             for (int e = 0; e < RF; ++e) rows[u][e] = p.V[(i + (int64_t)u * kBlock) * RF + e];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) add_row(rows[u]);
+        for (int u = 0; u < 4; ++u) rescore_row<R, REAL, KS>(rows[u], c, p.K, roots_s, acc);
     }
     for (; i < r1; i += kBlock) {
         float row[RF];
 #pragma unroll
         for (int e = 0; e < RF; ++e) row[e] = p.V[i * RF + e];
-        add_row(row);
+        rescore_row<R, REAL, KS>(row, c, p.K, roots_s, acc);
     }
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
 #pragma unroll
@@ -199,6 +204,22 @@ __global__ __launch_bounds__(kBlock) void k_rescore(RescoreParams p) {
         double s = 0.0;
         for (int w = 0; w < kBlock / kWave; ++w) s += red[w][threadIdx.x];
         p.partial[((size_t)t * gridDim.y + blockIdx.y) * (2 * R) + threadIdx.x] = s;
+    }
+}
+
+// FP64 arg-max over the wave of the kept candidates' values f (lane t: key of
+// candidate t), ties to the lowest index; every lane gets the winner.
+__device__ __forceinline__ void wave_pick(double& f, unsigned long long& key, uint32_t& idx) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const double fo = __shfl_xor(f, off, kWave);
+        const uint32_t io = __shfl_xor(idx, off, kWave);
+        const unsigned long long ko = __shfl_xor(key, off, kWave);
+        if (fo > f || (fo == f && io < idx)) {
+            f = fo;
+            idx = io;
+            key = ko;
+        }
     }
 }
 
@@ -242,17 +263,7 @@ __global__ __launch_bounds__(64 * 2 * R) void k_pick(const double* __restrict__ 
         idx = key_index(key);
         f = s >= 0.0 ? s : -1.0;      // a non-finite score is never picked
     }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const double fo = __shfl_xor(f, off, kWave);
-        const uint32_t io = __shfl_xor(idx, off, kWave);
-        const unsigned long long ko = __shfl_xor(key, off, kWave);
-        if (fo > f || (fo == f && io < idx)) {
-            f = fo;
-            idx = io;
-            key = ko;
-        }
-    }
+    wave_pick(f, key, idx);
     if (lane != 0) return;
     if (f < 0.0) {  // only with non-finite scores; the host reports the error
         key = keys[0];
@@ -267,6 +278,20 @@ __global__ __launch_bounds__(64 * 2 * R) void k_pick(const double* __restrict__ 
     for (int jj = 0; jj < 2 * LRQO_MAX_R; ++jj) res->c[jj] = jj < 2 * R ? (double)cf[jj] : 0.0;
 }
 
+// FP64 decision rule of one row at direction c.
+template <int R, bool REAL>
+__device__ __forceinline__ uint8_t row_label(const float* row, const double* c, int K) {
+    double wr = 0.0, wi = 0.0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const double vr = REAL ? (double)row[j] : (double)row[2 * j];
+        const double vi = REAL ? 0.0 : (double)row[2 * j + 1];
+        wr += vr * c[2 * j] - vi * c[2 * j + 1];
+        wi += vr * c[2 * j + 1] + vi * c[2 * j];
+    }
+    return (uint8_t)label_f64(wr, wi, K);
+}
+
 template <int R, bool REAL>
 __global__ __launch_bounds__(kBlock) void k_labels(const float* __restrict__ V, int64_t n, int K,
                                                    const DevResult* __restrict__ res,
@@ -274,16 +299,174 @@ __global__ __launch_bounds__(kBlock) void k_labels(const float* __restrict__ V, 
     constexpr int RF = Row<R, REAL>::F;
     const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
     if (i >= n) return;
-    const float* row = V + i * RF;
-    double wr = 0.0, wi = 0.0;
+    z[i] = row_label<R, REAL>(V + i * RF, res->c, K);
+}
+
+// ------------------------------------------------------------ small problems
+// Everything after the scorer in one block: the best T keys, their FP64
+// values, the pick and the labels.  With at most kTailRows rows a thread of
+// k_rescore holds one row, and the four kernels (17 us for the selection, 5, 4
+// and 2 for the others at n = 64, S = 1,024) are latency and launches; here
+// sixteen waves sort a tile of scores each and merge them in a tree; then a
+// lane holds a kept candidate and the waves split the rows, in the order of
+// k_rescore's sums, so every value is the same number.  A call also loses the prologue and the copy of the
+// record: 81 -> 52 us at n = 64, r = 2, K = 4, S = 1,024, 116 -> 103 us at
+// n = 256, r = 4, K = 16, S = 8,192.  One compute unit does all of it, so the
+// range ends there; an arbitrary K (an FP64 arctangent for each row and
+// candidate) took 146 -> 165 us at n = 256 and keeps to one group of 64 rows.
+constexpr int kTailRows = 256;         // k_rescore's block: one row a thread
+constexpr int kTailRowsAnyK = 64;
+constexpr int64_t kTailScores = 8192;  // eight tiles a wave
+constexpr int kTailWaves = 16;
+
+struct TailParams {
+    RescoreParams rs;
+    const float* f;
+    uint32_t S;
+    int T;
+    int ks;                            // k_special(K)
+    const int* bad;                    // the prologue's finiteness flags; null: no prologue ran
+    int nbad;
+    const DevResult* prev;             // the record the scorer counted flagged rows in
+    DevResult* res;
+    uint8_t* z;
+};
+
+// Rows g + w, + 16, + 32 and + 48 of a group of 64 for candidate `lane`: the
+// first two levels of k_rescore's sum over the group (it pairs lanes 32 apart,
+// then 16, 8, 4, 2, 1).  Rows beyond n count as zeros there too.
+template <int R, bool REAL, int KS>
+__device__ __forceinline__ void tail_rows(const TailParams& p, const float* Vs, int i0, const double (&c)[2 * R],
+                                          double (&out)[2 * R]) {
+    constexpr int RF = Row<R, REAL>::F;
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {                    // pairs (0, 32) and (16, 48); one at a time: registers
+        double a[2][2 * R];
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-        const double vr = REAL ? (double)row[j] : (double)row[2 * j];
-        const double vi = REAL ? 0.0 : (double)row[2 * j + 1];
-        wr += vr * res->c[2 * j] - vi * res->c[2 * j + 1];
-        wi += vr * res->c[2 * j + 1] + vi * res->c[2 * j];
+        for (int u = 0; u < 2; ++u) {
+            const int i = i0 + 16 * h + 32 * u;
+#pragma unroll
+            for (int j = 0; j < 2 * R; ++j) a[u][j] = 0.0;
+            if (i < (int)p.rs.n) {                   // the same in every lane
+                float row[RF];
+#pragma unroll
+                for (int e = 0; e < RF; ++e) row[e] = Vs[i * RF + e];
+                rescore_row<R, REAL, KS>(row, c, p.rs.K, p.rs.roots64, a[u]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2 * R; ++j) {
+            const double pair = a[0][j] + a[1][j];
+            out[j] = h == 0 ? pair : out[j] + pair;
+        }
     }
-    z[i] = (uint8_t)label_f64(wr, wi, K);
+}
+
+template <int R, bool REAL>
+__global__ __launch_bounds__(kTailWaves * kWave) void k_tail(TailParams p) {
+    constexpr int RF = Row<R, REAL>::F;
+    __shared__ float Vs[kTailRows * RF];
+    __shared__ unsigned long long top[kTailWaves][kWave];
+    __shared__ double part[kTailWaves][2 * R][kWave];
+    __shared__ double comp[2 * R][kWave];
+    __shared__ double cbest[2 * R];
+    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+    const int n = (int)p.rs.n;
+    int b = 0;
+    for (int e = tid; e < n * RF; e += kTailWaves * kWave) {
+        const float x = p.rs.V[e];
+        Vs[e] = x;
+        b |= !isfinite(x);
+    }
+    if (p.bad)
+        for (int q = tid; q < p.nbad; q += kTailWaves * kWave) b |= p.bad[q];
+    // the best 64 keys
+    unsigned long long run = 0;
+    for (uint32_t g0 = w * kWave; g0 < p.S; g0 += kTailWaves * kWave) {
+        const uint32_t g = g0 + lane;
+        const unsigned long long key = g < p.S ? pack_key(p.f[g], g) : 0ull;
+        const unsigned long long floor64 = __shfl(run, 63, kWave);
+        if (__ballot(key > floor64) == 0) continue;  // uniform across the wave
+        const unsigned long long tile = wave_sort_desc(key, lane);
+        run = g0 == (uint32_t)(w * kWave) ? tile : wave_top_union(run, tile, lane);
+    }
+    top[w][lane] = run;
+    const int any_bad = __syncthreads_or(b);
+    for (int h = kTailWaves / 2; h > 0; h >>= 1) {
+        if (w < h && (uint32_t)((w + h) * kWave) < p.S) {   // uniform across the wave; beyond S: empty lists
+            run = wave_top_union(run, top[w + h][lane], lane);
+            top[w][lane] = run;
+        }
+        __syncthreads();
+    }
+    // lane t: candidate t
+    unsigned long long key = lane < p.T ? top[0][lane] : 0ull;
+    uint32_t idx = lane < p.T ? key_index(key) : 0u;
+    float cf[2 * R];
+    direction_any<R>(p.rs.dirs, p.rs.seed, p.rs.first + idx, p.rs.instance, cf);
+    double c[2 * R];
+#pragma unroll
+    for (int j = 0; j < 2 * R; ++j) c[j] = (double)cf[j];
+    double sum = 0.0;                            // thread (component w, candidate lane)
+    for (int g = 0; g < n; g += kWave) {
+        double s[2 * R];
+        switch (p.ks) {
+            case 2: tail_rows<R, REAL, 2>(p, Vs, g + w, c, s); break;
+            case 3: tail_rows<R, REAL, 3>(p, Vs, g + w, c, s); break;
+            case 4: tail_rows<R, REAL, 4>(p, Vs, g + w, c, s); break;
+            case 8: tail_rows<R, REAL, 8>(p, Vs, g + w, c, s); break;
+            case 16: tail_rows<R, REAL, 16>(p, Vs, g + w, c, s); break;
+            default: tail_rows<R, REAL, 0>(p, Vs, g + w, c, s); break;
+        }
+#pragma unroll
+        for (int j = 0; j < 2 * R; ++j) part[w][j][lane] = s[j];
+        __syncthreads();
+        if (w < 2 * R) {
+            double v[kTailWaves];
+#pragma unroll
+            for (int q = 0; q < kTailWaves; ++q) v[q] = part[q][w][lane];
+#pragma unroll
+            for (int h = kTailWaves / 2; h > 0; h >>= 1)
+#pragma unroll
+                for (int q = 0; q < h; ++q) v[q] += v[q + h];
+            sum += v[0];
+        }
+        __syncthreads();
+    }
+    if (w < 2 * R) comp[w][lane] = sum;
+    __syncthreads();
+    if (w == 0) {
+        double f = -1.0;
+        if (lane < p.T) {
+            double s = 0.0;
+            for (int jj = 0; jj < 2 * R; ++jj) s += comp[jj][lane] * comp[jj][lane];
+            f = s >= 0.0 ? s : -1.0;      // a non-finite score is never picked
+        } else {
+            idx = 0xFFFFFFFFu;
+        }
+        const uint32_t own = idx;
+        const unsigned long long key0 = __shfl(key, 0, kWave);
+        wave_pick(f, key, idx);
+        if (f < 0.0) {  // only with non-finite scores; the host reports the error
+            key = key0;
+            idx = key_index(key);
+        }
+        if (own == idx && lane < p.T) {   // the winner's lane: one, as the kept indices differ
+            DevResult o{};
+            o.nonfinite = any_bad ? 1 : 0;
+            o.best_index = (int64_t)(p.rs.first + idx);
+            o.obj = f;
+            o.fp32_obj = (double)key_value(key);
+#pragma unroll
+            for (int jj = 0; jj < 2 * R; ++jj) o.c[jj] = c[jj];
+            o.flagged_rows = p.bad ? p.prev->flagged_rows : 0ull;
+            *p.res = o;
+#pragma unroll
+            for (int jj = 0; jj < 2 * R; ++jj) cbest[jj] = c[jj];
+        }
+    }
+    __syncthreads();
+    if (tid < n) p.z[tid] = row_label<R, REAL>(Vs + tid * RF, cbest, p.rs.K);
 }
 
 // ------------------------------------------------------------ host driver
@@ -415,8 +598,29 @@ lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
     launch_score_k<R, REAL>(p, dim3((unsigned)cand_blocks, (unsigned)sc.slices), st, sc.form);
     LRQO_HIP(hipGetLastError());
     LRQO_HIP(hipEventRecord(job.ev_score1, st));
-    // ---- top-T
     const int T = sc.topk;
+    RescoreParams rp{};
+    rp.V = job.V;
+    rp.n = job.n;
+    rp.K = job.K;
+    rp.seed = job.seed;
+    rp.instance = job.instance;
+    rp.first = job.first;
+    rp.roots64 = sc.roots64;
+    rp.partial = sc.rescore;
+    rp.rows_per_slice = sc.rescore_rows;
+    rp.dirs = job.dirs;
+    if constexpr (R <= 4) {
+        if (sc.tail) {
+            hipLaunchKernelGGL((k_tail<R, REAL>), dim3(1), dim3(kTailWaves * kWave), 0, st,
+                               TailParams{rp, sc.f32, S, T, k_special(job.K), sc.prologue ? sc.bad_blocks : nullptr,
+                                          kCheckBlocks, sc.result, job.host_result ? job.host_result : sc.result,
+                                          job.z});
+            LRQO_HIP(hipGetLastError());
+            return LRQO_OK;
+        }
+    }
+    // ---- top-T
     const unsigned long long* keys = nullptr;
     if (sc.slices > 1) {
         const uint32_t fblocks = (S + kBlock - 1) / kBlock;
@@ -429,18 +633,7 @@ lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
     }
 
     // ---- FP64 rescore of the T kept keys
-    RescoreParams rp{};
-    rp.V = job.V;
-    rp.n = job.n;
-    rp.K = job.K;
-    rp.seed = job.seed;
-    rp.instance = job.instance;
-    rp.first = job.first;
     rp.keys = keys;
-    rp.roots64 = sc.roots64;
-    rp.partial = sc.rescore;
-    rp.rows_per_slice = sc.rescore_rows;
-    rp.dirs = job.dirs;
     const dim3 rgrid(T, sc.rescore_slices);
     switch (k_special(job.K)) {
         case 2: hipLaunchKernelGGL((k_rescore<R, REAL, 2>), rgrid, dim3(kBlock), 0, st, rp); break;
@@ -513,6 +706,8 @@ void plan_sampled(const SampledJob& job, ScratchPlan& plan) {
     int64_t rrows = std::max<int64_t>(4096, (job.n + 127) / 128);
     plan.rescore_rows = rrows;
     plan.rescore_slices = (int)((job.n + rrows - 1) / rrows);
+    plan.tail = R <= 4 && job.n <= (k_special(job.K) ? kTailRows : kTailRowsAnyK) &&
+                job.S <= kTailScores && plan.slices == 1;
     CarveSize cs;
     cs.add<DevResult>(1);
     cs.add<float2>(LRQO_MAX_K);
@@ -552,8 +747,13 @@ lrqo_status launch_sampled(const SampledJob& job, const ScratchPlan& plan, void*
     sc.vmax = cv.take<float>(kCheckBlocks);
 
     const int64_t vcount = job.n * job.r * (job.real ? 1 : 2);
-    hipLaunchKernelGGL(k_prologue, dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K, sc.roots64, sc.roots32,
-                       sc.result, job.V, vcount, sc.bad_blocks, sc.vmax);
+    // a small solve whose scorer reads neither the roots, nor the largest
+    // entry, nor counts into the record leaves the checks to k_tail
+    sc.tail = plan.tail;
+    sc.prologue = !(plan.tail && plan.form == kFormFp32 && k_special(job.K) != 0 && !(job.real && job.K == 3));
+    if (sc.prologue)
+        hipLaunchKernelGGL(k_prologue, dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K, sc.roots64, sc.roots32,
+                           sc.result, job.V, vcount, sc.bad_blocks, sc.vmax);
     LRQO_HIP(hipGetLastError());
     return job.real ? dispatch_r<true>(job, sc, st) : dispatch_r<false>(job, sc, st);
 }

@@ -85,6 +85,7 @@ struct SampledJob {
     uint8_t* z;
     hipEvent_t ev_score0;   // recorded before / after the scoring kernels
     hipEvent_t ev_score1;
+    DevResult* host_result = nullptr;   // pinned host record, written where the plan ends in k_tail (else unused)
 };
 
 // The scorer of a call: FP32 on the vector ALU, the precision form, or both
@@ -98,10 +99,13 @@ struct ScratchPlan {
     int topk = 64;
     int rescore_slices = 1;
     int64_t rescore_rows = 0;
+    bool tail = false;         // everything after the scorer in one block (small problems)
     size_t bytes = 0;
 };
 
 struct Scratch {
+    bool tail;
+    bool prologue;             // k_prologue has run
     DevResult* result;
     float2* roots32;
     double2* roots64;

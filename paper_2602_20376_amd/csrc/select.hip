@@ -5,7 +5,7 @@
 // then a bitonic merge); tiles with no key above the running 64th are
 // skipped; input already sorted in lists of 64 (the slice sum's per-wave
 // lists, or a previous pass's block lists when T = 64) is merged without the
-// sort.  The four lists of a block are merged the same way, the block writes
+// sort.  The lists of a block's waves are merged in a tree, the block writes
 // its best T, and passes repeat over the survivors until one block remains.
 #include "lrqo_device.h"
 #include "lrqo_runtime.h"
@@ -15,9 +15,15 @@ namespace lrqo {
 
 namespace {
 
-constexpr int kWaves = 4;
-constexpr int kBlock = 64 * kWaves;
-constexpr int kChunk = 2048;  // keys per block, kChunk / kWaves per wave
+// Waves per block of k_topk: sixteen (two tiles a wave) where the blocks do
+// not fill the chip and the chain of sorts and merges is what they cost (the
+// two passes over 4,096 scores: 14.4 us with four waves, 10.0 with sixteen),
+// four where they stream (2^26 scores above a floor: 0.13 ms a selection, 0.28
+// with sixteen).
+constexpr int kWaves = 16;
+constexpr int kStreamWaves = 4;
+constexpr int kBlock = 256;
+constexpr int kChunk = 2048;  // keys per block of k_topk, shared by its waves
 
 // Keys come from f (index = position) or from a previous pass.  Padding keys
 // are 0, below every real key (a real key's index is < 2^32-1, so its low
@@ -26,14 +32,15 @@ constexpr int kChunk = 2048;  // keys per block, kChunk / kWaves per wave
 // where many candidates share a bit-identical score.
 // floor_f (may be null; read on the device): scores strictly below *floor_f
 // are dropped (their keys count as padding) when *floor_f >= 0.
-__global__ __launch_bounds__(kBlock) void k_topk(const float* __restrict__ f,
+__global__ __launch_bounds__(64 * kWaves) void k_topk(const float* __restrict__ f,
                                                  const unsigned long long* __restrict__ keys_in,
                                                  uint32_t count, int T, int sorted, int distinct,
                                                  const float* __restrict__ floor_f,
                                                  unsigned long long* __restrict__ keys_out) {
     __shared__ unsigned long long top[kWaves][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t base = blockIdx.x * (uint32_t)kChunk + (uint32_t)w * (kChunk / kWaves);
+    const int waves = blockDim.x >> 6, per = kChunk / waves;
+    const uint32_t base = blockIdx.x * (uint32_t)kChunk + (uint32_t)(w * per);
     // non-negative floats order as their bits; a key with score x is at
     // least bits(x) << 32
     unsigned long long lo = 0;
@@ -42,7 +49,7 @@ __global__ __launch_bounds__(kBlock) void k_topk(const float* __restrict__ f,
         if (fl >= 0.0f) lo = (unsigned long long)__float_as_uint(fl) << 32;
     }
     unsigned long long run = 0;
-    for (int t = 0; t < kChunk / kWaves; t += 64) {
+    for (int t = 0; t < per; t += 64) {
         const uint32_t g = base + (uint32_t)(t + lane);
         unsigned long long key = 0;
         if (g < count) key = f ? pack_key(f[g], g) : keys_in[g];
@@ -54,17 +61,22 @@ __global__ __launch_bounds__(kBlock) void k_topk(const float* __restrict__ f,
     }
     top[w][lane] = run;
     __syncthreads();
-    if (w != 0) return;
-    for (int v = 1; v < kWaves; ++v)
-        run = distinct ? wave_top_union_distinct(run, top[v][lane], lane) : wave_top_union(run, top[v][lane], lane);
-    if (lane < T) keys_out[(size_t)blockIdx.x * T + lane] = run;
+    for (int h = waves / 2; h > 0; h >>= 1) {
+        if (w < h && top[w + h][0] != 0ull) {   // uniform across the wave
+            run = distinct ? wave_top_union_distinct(run, top[w + h][lane], lane)
+                           : wave_top_union(run, top[w + h][lane], lane);
+            top[w][lane] = run;
+        }
+        __syncthreads();
+    }
+    if (w == 0 && lane < T) keys_out[(size_t)blockIdx.x * T + lane] = run;
 }
 
 // Per group of kChunk scores (k_topk's grouping): the key of its largest
 // score.
 __global__ __launch_bounds__(kBlock) void k_block_max(const float* __restrict__ f, uint32_t count,
                                                       unsigned long long* __restrict__ out) {
-    __shared__ unsigned long long wm[kWaves];
+    __shared__ unsigned long long wm[kBlock / 64];
     const uint32_t base = blockIdx.x * (uint32_t)kChunk;
     unsigned long long m = 0;
     for (int e = threadIdx.x; e < kChunk; e += kBlock) {
@@ -76,7 +88,7 @@ __global__ __launch_bounds__(kBlock) void k_block_max(const float* __restrict__ 
     if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kWaves; ++w) m = key_max(m, wm[w]);
+        for (int w = 1; w < kBlock / 64; ++w) m = key_max(m, wm[w]);
         out[blockIdx.x] = m;
     }
 }
@@ -108,7 +120,8 @@ lrqo_status topk_passes(const float* f, const unsigned long long* keys, bool sor
     for (;;) {
         const uint32_t blocks = (n + kChunk - 1) / kChunk;
         unsigned long long* dst = ping ? buf_b : buf_a;
-        hipLaunchKernelGGL(k_topk, dim3(blocks), dim3(kBlock), 0, st, from_f ? f : nullptr, keys, n,
+        const int waves = blocks <= 512 ? kWaves : kStreamWaves;
+        hipLaunchKernelGGL(k_topk, dim3(blocks), dim3(64 * waves), 0, st, from_f ? f : nullptr, keys, n,
                            T, sorted ? 1 : 0, distinct ? 1 : 0, from_f ? floor_f : nullptr, dst);
         LRQO_HIP(hipGetLastError());
         keys = dst;
