@@ -161,6 +161,31 @@ __device__ __forceinline__ void unrank(uint64_t rank, const unsigned long long* 
     c[0] = (int64_t)rank;     // C(x, 1) = x
 }
 
+// The same for a rank at most a few hundred above `base`, whose rows are b:
+// where the higher rows are base's, row t is at or a few steps above b[t];
+// where one of them moved on, the rest of the rank is small and so is row t.
+// The base is uniform over the block, so its binary searches (eleven dependent
+// loads each at N = 1,500) run on the scalar unit.
+template <int M>
+__device__ __forceinline__ void unrank_near(uint64_t rank, const unsigned long long* binom, int64_t N,
+                                            const int64_t (&b)[M], int64_t (&c)[M]) {
+    bool same = true;
+#pragma unroll
+    for (int t = M - 1; t >= 1; --t) {
+        const unsigned long long* col = binom + (size_t)(t + 1) * (N + 1);
+        int64_t x = same ? b[t] : t;
+        unsigned long long at = col[x], next = col[x + 1];
+        while (next <= rank) {          // rank < C(N, M), so x + 1 stays within the column
+            at = next;
+            next = col[++x + 1];
+        }
+        c[t] = x;
+        rank -= at;
+        same &= x == b[t];
+    }
+    c[0] = (int64_t)rank;     // C(x, 1) = x
+}
+
 // Null-vector sampler, draw s: M rows of the augmented matrix, row j =
 // (2^32 w[2j+1] + w[2j]) mod N with w the words of Philox4x32-10 (key seed,
 // counter (s lo, s hi, kNullvecStream, block)), sorted; `distinct` is false
@@ -198,13 +223,16 @@ __device__ __forceinline__ void draw_rows(uint64_t seed, uint64_t s, int64_t N, 
 }
 
 // The rows of one index set: groups g[t] and boundary ids mm[t]; false for
-// a set with a repeated row (random draws) or three rows of one group.
+// a set with a repeated row (random draws) or three rows of one group.  near:
+// the rows of the block's first set, or null.
 template <int D>
-__device__ bool set_rows(const ExactParams& p, uint64_t rank, int64_t (&g)[2 * D - 1], int (&mm)[2 * D - 1]) {
+__device__ bool set_rows(const ExactParams& p, uint64_t rank, const int64_t (*near)[2 * D - 1],
+                         int64_t (&g)[2 * D - 1], int (&mm)[2 * D - 1]) {
     constexpr int M = 2 * D - 1;
     int64_t c[M];
     bool distinct = true;
     if (p.random) draw_rows<M>(p.draw_seed, rank, p.N, c, distinct);
+    else if (near) unrank_near<M>(rank, p.binom, p.N, *near, c);
     else unrank<M>(rank, p.binom, p.N, c);
 #pragma unroll
     for (int t = 0; t < M; ++t) {
@@ -222,10 +250,10 @@ __device__ bool set_rows(const ExactParams& p, uint64_t rank, int64_t (&g)[2 * D
 // invalid set or one below the rank tolerance (rank_deficient set
 // accordingly).
 template <int D>
-__device__ bool vertex(const ExactParams& p, uint64_t rank, int64_t (&g)[2 * D - 1],
+__device__ bool vertex(const ExactParams& p, uint64_t rank, const int64_t (*near)[2 * D - 1], int64_t (&g)[2 * D - 1],
                        int (&mm)[2 * D - 1], double (&v)[2 * D], bool& valid) {
     constexpr int M = 2 * D - 1, C2 = 2 * D;
-    valid = set_rows<D>(p, rank, g, mm);
+    valid = set_rows<D>(p, rank, near, g, mm);
     if (!valid) return false;
 
     double a[M][C2];
@@ -243,8 +271,9 @@ __device__ bool vertex(const ExactParams& p, uint64_t rank, int64_t (&g)[2 * D -
             a[t][D + j] = pr;
             nrm += pr * pr + pi * pi;
         }
-        amax = fmax(amax, sqrt(nrm));
+        amax = fmax(amax, nrm);
     }
+    amax = sqrt(amax);       // the largest row's norm: the square root is monotone
     // orthonormalise the rows (Gram-Schmidt, two passes)
     double rmin = INFINITY;
 #pragma unroll
@@ -401,21 +430,30 @@ __device__ __forceinline__ CoopLds& coop_lds() {
     return s;
 }
 
+// Rows of the block's first set (near above), for the levels that use them.
+template <int D>
+__device__ __forceinline__ void block_rows(const ExactParams& p, uint64_t base, int64_t (&near)[2 * D - 1]) {
+    if constexpr (D <= kThreadMaxD) {
+        if (!p.random) unrank<2 * D - 1>(p.rank0 + base, p.binom, p.N, near);
+    }
+}
+
 // The vertex of each thread's set for every level: alone for d <= 4; for
 // d > 4 every thread of the block must call it (it has barriers), sixteen
 // lanes per set, each thread getting back its own set's vertex (uniform:
 // every thread passes the same rank, solved once).
 template <int D>
 __device__ bool vertex_blk(const ExactParams& p, uint64_t rank, bool active, bool uniform,
+                           const int64_t (*near)[2 * D - 1],
                            int64_t (&g)[2 * D - 1], int (&mm)[2 * D - 1], double (&v)[2 * D], bool& valid) {
     if constexpr (D <= kThreadMaxD) {
         valid = false;
-        return active && vertex<D>(p, rank, g, mm, v, valid);
+        return active && vertex<D>(p, rank, near, g, mm, v, valid);
     } else {
         constexpr int M = 2 * D - 1, C2 = 2 * D;
         CoopLds& sh = coop_lds();
         const int tid = threadIdx.x;
-        valid = active && set_rows<D>(p, rank, g, mm);
+        valid = active && set_rows<D>(p, rank, nullptr, g, mm);
         sh.rank[tid] = rank;
         sh.state[tid] = valid ? 1 : 0;
         __syncthreads();
@@ -425,7 +463,7 @@ __device__ bool vertex_blk(const ExactParams& p, uint64_t rank, bool active, boo
             if (sh.state[q] == 0) continue;          // the same for the sixteen lanes
             int64_t gq[M];
             int mq[M];
-            set_rows<D>(p, sh.rank[q], gq, mq);
+            set_rows<D>(p, sh.rank[q], nullptr, gq, mq);
             bool okq = false;
             const double vk = solve_columns<D>(p, gq, mq, lane, okq);
             if (lane < C2) sh.v[q][lane] = vk;
@@ -441,13 +479,37 @@ __device__ bool vertex_blk(const ExactParams& p, uint64_t rank, bool active, boo
     }
 }
 
-// Options left open at a vertex for the coordinates of the set (both rows
-// of a double group share one entry; the second gets count 1): first label
-// o[t] and count cnt[t] of consecutive labels mod K.
+// Re(rho_m V_i c) of the set's rows, whose sign says on which ray of the line
+// of boundary m the row lies (0 for the rows of a double group, V_i c = 0).
 template <int D>
-__device__ void open_labels(const ExactParams& p, const int64_t (&g)[2 * D - 1],
-                            const int (&mm)[2 * D - 1], const double (&c)[2 * D],
-                            int (&o)[2 * D - 1], int (&cnt)[2 * D - 1]) {
+__device__ void ray_sides(const ExactParams& p, const int64_t (&g)[2 * D - 1], const int (&mm)[2 * D - 1],
+                          const double (&c)[2 * D], double (&re)[2 * D - 1]) {
+    constexpr int M = 2 * D - 1;
+#pragma unroll
+    for (int t = 0; t < M; ++t) {
+        const bool first = (t == 0) || (g[t] != g[t - 1]);
+        const bool dbl = first && (t + 1 < M) && (g[t + 1] == g[t]);
+        re[t] = 0.0;
+        if (!first || dbl) continue;
+        double wr = 0.0, wi = 0.0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            const double vr = p.V64[(g[t] * p.r + j) * 2], vi = p.V64[(g[t] * p.r + j) * 2 + 1];
+            wr += vr * c[j] - vi * c[D + j];
+            wi += vr * c[D + j] + vi * c[j];
+        }
+        const double2 rh = p.rho[mm[t]];
+        re[t] = rh.x * wr - rh.y * wi;
+    }
+}
+
+// Options left open at a vertex (neg: at its negative, where every ray_sides
+// value changes sign and nothing else) for the coordinates of the set (both
+// rows of a double group share one entry; the second gets count 1): first
+// label o[t] and count cnt[t] of consecutive labels mod K.
+template <int D>
+__device__ void open_labels(const ExactParams& p, const int64_t (&g)[2 * D - 1], const int (&mm)[2 * D - 1],
+                            const double (&re)[2 * D - 1], bool neg, int (&o)[2 * D - 1], int (&cnt)[2 * D - 1]) {
     constexpr int M = 2 * D - 1;
 #pragma unroll
     for (int t = 0; t < M; ++t) {
@@ -460,16 +522,7 @@ __device__ void open_labels(const ExactParams& p, const int64_t (&g)[2 * D - 1],
             cnt[t] = p.K;   // V_i c = 0: every label borders the vertex
             continue;
         }
-        double wr = 0.0, wi = 0.0;
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            const double vr = p.V64[(g[t] * p.r + j) * 2], vi = p.V64[(g[t] * p.r + j) * 2 + 1];
-            wr += vr * c[j] - vi * c[D + j];
-            wi += vr * c[D + j] + vi * c[j];
-        }
-        const double2 rh = p.rho[mm[t]];
-        const double re = rh.x * wr - rh.y * wi;   // Re(rho_m w_i)
-        if (re > 0.0) {
+        if (neg ? re[t] < 0.0 : re[t] > 0.0) {
             o[t] = mm[t];                          // on ray pi(2m+1)/K: labels m, m+1
             cnt[t] = 2;
         } else if (p.K & 1) {
@@ -758,6 +811,62 @@ __device__ __forceinline__ void score_rows(const ExactParams& p, const float (&c
     }
 }
 
+// Root of label k.  KS = 3 takes it in closed form (the same FP32 values as
+// the table), other K from the table.
+template <int KS>
+__device__ __forceinline__ void combo_root(int k, const float2* roots_s, float (&z)[2]) {
+    if constexpr (KS == 3) {
+        z[0] = k == 0 ? 1.0f : -0.5f;
+        z[1] = k == 0 ? 0.0f : (k == 1 ? 0.8660254037844386f : -0.8660254037844386f);
+    } else {
+        const float2 r = roots_s[k];
+        z[0] = r.x;
+        z[1] = r.y;
+    }
+}
+
+// The largest score over the labels of rows T .. M-1 (two each, a row with
+// one open label twice the same), from the sums s of everything before them.
+// Rows enter in their order, so every sum is the one the mixed-radix loop
+// forms, but a common start is added once: 2 + 4 + ... + 2^M row terms for
+// M 2^M.  The last five rows are unrolled.  With the signs taken once and the
+// block-relative unranking, what a set costs besides its rows (a fifth of the
+// vector instructions at n = 500) fell by a quarter: rank 2, K = 3, real,
+// n = 500: 104.0 -> 98.4 ms; K = 4, n = 300: 7.4 -> 6.2 ms.
+template <int T, int R, int M, bool REAL, int VM, int VR>
+__device__ __forceinline__ void combos_from(const float (&vt)[VM][VR], const float (&z)[M][2][2],
+                                            const float (&s)[2 * R], float& best) {
+    if constexpr (T == M) {
+        float f = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 2 * R; ++j) f = fmaf(s[j], s[j], f);
+        best = fmaxf(best, f);
+    } else {
+        auto branch = [&](float zx, float zy) {
+            float n[2 * R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const float vr = vt[T][2 * j], vi = vt[T][2 * j + 1];
+                if constexpr (REAL) {
+                    n[2 * j] = fmaf(vr, zx, s[2 * j]);
+                    n[2 * j + 1] = fmaf(vr, zy, s[2 * j + 1]);
+                } else {
+                    n[2 * j] = fmaf(vr, zx, fmaf(vi, zy, s[2 * j]));
+                    n[2 * j + 1] = fmaf(vr, zy, fmaf(-vi, zx, s[2 * j + 1]));
+                }
+            }
+            combos_from<T + 1, R, M, REAL>(vt, z, n, best);
+        };
+        if constexpr (M - T > 5) {
+#pragma unroll 1
+            for (int b = 0; b < 2; ++b) branch(b ? z[T][1][0] : z[T][0][0], b ? z[T][1][1] : z[T][0][1]);
+        } else {
+            branch(z[T][0][0], z[T][0][1]);
+            branch(z[T][1][0], z[T][1][1]);
+        }
+    }
+}
+
 // Best FP32 score over both signs and every open-label combination of the
 // set's coordinates, from the sums acc[s] of the untouched rows; also the
 // number of combinations tried.  Both signs run in one loop (the mixed-radix
@@ -765,13 +874,12 @@ __device__ __forceinline__ void score_rows(const ExactParams& p, const float (&c
 // turns to -v), so a wave runs the longest lane's total of the two rather
 // than the sum of each sign's longest.  The second row of a coordinate with
 // two rows adds nothing (its labels are the first row's); it enters as a
-// zero row.  KS = 3 takes the roots in closed form (the same FP32 values as
-// the table), other K from the table roots_s.
-template <int R, int D, int KS>
+// zero row.
+template <int R, int D, int KS, bool REAL>
 __device__ float combos_best(const ExactParams& p, const int64_t (&g)[2 * D - 1], const int (&mm)[2 * D - 1],
                              const double (&v)[2 * D], const float (&acc)[2][2 * R],
                              const float2* roots_s, unsigned long long& ncand) {
-    constexpr int M = 2 * D - 1, C2 = 2 * D;
+    constexpr int M = 2 * D - 1;
     // the set's rows in registers once (every combination reads them) when
     // they fit; above that they are read from the FP32 copy (cached)
     constexpr bool kHold = M * 2 * R <= 64;
@@ -787,24 +895,48 @@ __device__ float combos_best(const ExactParams& p, const int64_t (&g)[2 * D - 1]
     }
     int o[2][M], cn[2][M];
     int64_t tot[2];
+    double re[M];
+    ray_sides<D>(p, g, mm, v, re);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-        double cs[C2];
-#pragma unroll
-        for (int k = 0; k < C2; ++k) cs[k] = s ? -v[k] : v[k];
-        open_labels<D>(p, g, mm, cs, o[s], cn[s]);
+        open_labels<D>(p, g, mm, re, s == 1, o[s], cn[s]);
         tot[s] = 1;
 #pragma unroll
         for (int t = 0; t < M; ++t) tot[s] *= cn[s][t];
     }
     ncand += (unsigned long long)(tot[0] + tot[1]);
+    float best = 0.0f;
+    if constexpr (kHold && M <= 7) {
+        // no coordinate with two rows in the wave: one or two labels each
+        bool two = false;
+#pragma unroll
+        for (int t = 1; t < M; ++t) two |= g[t] == g[t - 1];
+        if (!__any(two)) {
+#pragma unroll 1
+            for (int s = 0; s < 2; ++s) {
+                float z[M][2][2];
+#pragma unroll
+                for (int t = 0; t < M; ++t) {
+                    const int k0 = s ? o[1][t] : o[0][t];
+                    int k1 = k0 + (s ? cn[1][t] : cn[0][t]) - 1;
+                    k1 = k1 >= p.K ? k1 - p.K : k1;
+                    combo_root<KS>(k0, roots_s, z[t][0]);
+                    combo_root<KS>(k1, roots_s, z[t][1]);
+                }
+                float sr[2 * R];
+#pragma unroll
+                for (int j = 0; j < 2 * R; ++j) sr[j] = s ? acc[1][j] : acc[0][j];
+                combos_from<0, R, M, REAL>(vt, z, sr, best);
+            }
+            return best;
+        }
+    }
     // the combinations in mixed radix cn[s][0], cn[s][1], ... (digit t least
     // significant first), stepped by a counter instead of divisions
     int dig[M];
 #pragma unroll
     for (int t = 0; t < M; ++t) dig[t] = 0;
     bool neg = false;                 // false: +v, true: -v
-    float best = 0.0f;
     for (int64_t it = 0; it < tot[0] + tot[1]; ++it) {
         float sr[2 * R];
 #pragma unroll
@@ -813,15 +945,9 @@ __device__ float combos_best(const ExactParams& p, const int64_t (&g)[2 * D - 1]
         for (int t = 0; t < M; ++t) {
             int k = (neg ? o[1][t] : o[0][t]) + dig[t];
             k = k >= p.K ? k - p.K : k;
-            float zx, zy;
-            if constexpr (KS == 3) {
-                zx = k == 0 ? 1.0f : -0.5f;
-                zy = k == 0 ? 0.0f : (k == 1 ? 0.8660254037844386f : -0.8660254037844386f);
-            } else {
-                const float2 z = roots_s[k];
-                zx = z.x;
-                zy = z.y;
-            }
+            float z[2];
+            combo_root<KS>(k, roots_s, z);
+            const float zx = z[0], zy = z[1];
 #pragma unroll
             for (int j = 0; j < R; ++j) {
                 float vr, vi;
@@ -832,8 +958,13 @@ __device__ float combos_best(const ExactParams& p, const int64_t (&g)[2 * D - 1]
                     vr = first[t] ? p.V32[g[t] * 2 * R + 2 * j] : 0.0f;
                     vi = first[t] ? p.V32[g[t] * 2 * R + 2 * j + 1] : 0.0f;
                 }
-                sr[2 * j] = fmaf(vr, zx, fmaf(vi, zy, sr[2 * j]));
-                sr[2 * j + 1] = fmaf(vr, zy, fmaf(-vi, zx, sr[2 * j + 1]));
+                if constexpr (REAL) {
+                    sr[2 * j] = fmaf(vr, zx, sr[2 * j]);
+                    sr[2 * j + 1] = fmaf(vr, zy, sr[2 * j + 1]);
+                } else {
+                    sr[2 * j] = fmaf(vr, zx, fmaf(vi, zy, sr[2 * j]));
+                    sr[2 * j + 1] = fmaf(vr, zy, fmaf(-vi, zx, sr[2 * j + 1]));
+                }
             }
         }
         float f = 0.0f;
@@ -920,7 +1051,9 @@ void k_exact_score(ExactParams p) {
         int mm[M];
         double v[C2];
         bool valid = false;
-        const bool ok = vertex_blk<D>(p, p.rank0 + rank, active, false, g, mm, v, valid);
+        int64_t near[M];
+        block_rows<D>(p, base, near);
+        const bool ok = vertex_blk<D>(p, p.rank0 + rank, active, false, &near, g, mm, v, valid);
         if (!ok) {
 #pragma unroll
             for (int t = 0; t < M; ++t) g[t] = -1;
@@ -940,7 +1073,11 @@ void k_exact_score(ExactParams p) {
         else
             score_rows<R, D, KS, true>(p, c, g32, 0, p.n, tile, roots_s, colsum, acc);
         unsigned long long ncand = 0;
-        const float best = ok ? combos_best<R, D, KS>(p, g, mm, v, acc, roots_all, ncand) : 0.0f;
+        float best = 0.0f;
+        if (ok) {
+            if (cplx || R > kThreadMaxD) best = combos_best<R, D, KS, false>(p, g, mm, v, acc, roots_all, ncand);
+            else best = combos_best<R, D, KS, true>(p, g, mm, v, acc, roots_all, ncand);
+        }
         if (active) p.fbuf[rank] = best;
         add_stats(p, active, valid, ok, ncand);
     }
@@ -961,7 +1098,9 @@ __global__ __launch_bounds__(kBlock) void k_exact_vertex(ExactParams p, VertexRe
         int mm[M];
         double v[C2];
         bool valid = false;
-        const bool ok = vertex_blk<D>(p, p.rank0 + rank, active, false, g, mm, v, valid);
+        int64_t near[M];
+        block_rows<D>(p, base, near);
+        const bool ok = vertex_blk<D>(p, p.rank0 + rank, active, false, &near, g, mm, v, valid);
         if (!active) continue;
         Rec rec;
 #pragma unroll
@@ -1047,7 +1186,9 @@ __global__ __launch_bounds__(kBlock) void k_exact_combine(ExactParams p, int sli
         int mm[M];
         double v[C2];
         bool valid = false;
-        const bool ok = vertex_blk<D>(p, p.rank0 + rank, active, false, g, mm, v, valid);
+        int64_t near[M];
+        block_rows<D>(p, base, near);
+        const bool ok = vertex_blk<D>(p, p.rank0 + rank, active, false, &near, g, mm, v, valid);
         unsigned long long ncand = 0;
         float best = 0.0f;
         if (ok) {
@@ -1060,7 +1201,7 @@ __global__ __launch_bounds__(kBlock) void k_exact_combine(ExactParams p, int sli
                     for (int q = 0; q < slices; ++q) a += p.part[(((uint64_t)q * 2 + s) * (2 * R) + j) * p.count + rank];
                     acc[s][j] = a;
                 }
-            best = combos_best<R, D, 0>(p, g, mm, v, acc, roots_all, ncand);
+            best = combos_best<R, D, 0, false>(p, g, mm, v, acc, roots_all, ncand);
         }
         if (active) p.fbuf[rank] = best;
         add_stats(p, active, valid, ok, ncand);
@@ -1132,7 +1273,7 @@ __device__ void rescore_rows_one(const ExactParams& p, uint64_t rank, int64_t r0
     int mm[M];
     double v[C2];
     bool valid;
-    const bool ok = vertex_blk<D>(p, rank, true, true, g, mm, v, valid);
+    const bool ok = vertex_blk<D>(p, rank, true, true, nullptr, g, mm, v, valid);
     if (!ok) {
         if (threadIdx.x < 4 * R) out[threadIdx.x] = 0.0;
         return;
@@ -1190,7 +1331,7 @@ __device__ void rescore_one(ExactParams p, uint64_t rank, const double* part, in
     int mm[M];
     double v[C2];
     bool valid;
-    const bool ok = vertex_blk<D>(p, rank, true, true, g, mm, v, valid);
+    const bool ok = vertex_blk<D>(p, rank, true, true, nullptr, g, mm, v, valid);
     RescoreEntry best{-1.0, 0, 0, 0};
     if (!ok) {
         if (threadIdx.x == 0) *out = best;
@@ -1208,7 +1349,9 @@ __device__ void rescore_one(ExactParams p, uint64_t rank, const double* part, in
         }
         __syncthreads();
         int o[M], cn[M];
-        open_labels<D>(p, g, mm, cs, o, cn);
+        double re[M];
+        ray_sides<D>(p, g, mm, cs, re);
+        open_labels<D>(p, g, mm, re, false, o, cn);
         int64_t total = 1;
 #pragma unroll
         for (int t = 0; t < M; ++t) total *= cn[t];
@@ -1341,13 +1484,15 @@ __device__ void labels_one(const ExactParams& p, uint64_t rank, const ExactDevRe
     int mm[M];
     double v[C2];
     bool valid;
-    vertex_blk<D>(p, rank, true, true, g, mm, v, valid);
+    vertex_blk<D>(p, rank, true, true, nullptr, g, mm, v, valid);
     if (i >= p.n) return;
     double cs[C2];
 #pragma unroll
     for (int k = 0; k < C2; ++k) cs[k] = res.sign ? -v[k] : v[k];
     int o[M], cn[M];
-    open_labels<D>(p, g, mm, cs, o, cn);
+    double re[M];
+    ray_sides<D>(p, g, mm, cs, re);
+    open_labels<D>(p, g, mm, re, false, o, cn);
     int64_t rest = res.combo;
     int lab = -1;
 #pragma unroll
