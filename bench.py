@@ -110,10 +110,22 @@ def _fp64_roofline(flops: float, ms: float, what: str) -> dict:
             "what": what}
 
 
-def _mfma_roofline(flops: float, ms: float, what: str) -> dict:
-    achieved = flops / (ms / 1000.0) / 1e12
-    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": round(achieved / BF16_MFMA_PEAK_TFLOPS, 4), "flops": flops, "ms": ms, "what": what}
+I8_MFMA_PEAK_TOPS = 5000.0
+
+
+def _split_roofline(n: int, r: int, K: int, S: int, ms: float) -> dict:
+    """The matrix-core scorer of a real V (K = 2, 3, 4, 2 <= r <= 4), operations
+    as issued per 32 rows x 32 candidates: v_mfma_f32_32x32x16_f16 for Re w and
+    Im w (Re alone for K = 2), one k-chunk for r <= 3 and two for r = 4, and one
+    v_mfma_i32_32x32x32_i8 per label plane (one for K = 2, else two).  The peak
+    is that of this mix: each kind at its own dense rate."""
+    f16 = (1 if K == 2 else 2) * (1 if r <= 3 else 2) * 2 * 32 * 32 * 16 / 1024.0 * n * S
+    i8 = (1 if K == 2 else 2) * 2 * 32 * 32 * 32 / 1024.0 * n * S
+    peak = (f16 + i8) / (f16 / BF16_MFMA_PEAK_TFLOPS + i8 / I8_MFMA_PEAK_TOPS)
+    achieved = (f16 + i8) / (ms / 1000.0) / 1e12
+    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": "TOP/s",
+            "frac": round(achieved / peak, 4), "f16_flops": f16, "i8_ops": i8, "ms": ms,
+            "what": "k_score_split, F16 and I8 operations as issued"}
 
 
 def _hbm_roofline(nbytes: float, ms: float, what: str) -> dict:
@@ -137,7 +149,7 @@ def _source_hash() -> str:
     import hashlib
 
     h = hashlib.sha1()
-    for f in ("sampled_kernels.h", "lrqo_device.h", "sampled_internal.h"):
+    for f in ("sampled_kernels.h", "sampled_split.h", "lrqo_device.h", "sampled_internal.h"):
         with open(os.path.join(ROOT, "paper_2602_20376_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:12]
@@ -155,8 +167,9 @@ def _time(fn, reps):
 
 
 def form_precision():
-    """BF16-MFMA precision form against the FP32 scorer on the 3-block planted
-    partition (n = 1e6, r = 3, K = 3, S = 2^20), same direction stream."""
+    """The precision form against the FP32 scorer on the 3-block planted
+    partition (n = 1e6, r = 3, K = 3, S = 2^20), same direction stream.  At this
+    size both take the matrix-core scorer from split FP32 values."""
     import torch
 
     from paper_2602_20376_amd import inputs, lrqo
@@ -174,18 +187,10 @@ def form_precision():
     cnt = 64
     oms, ores = _timed(lambda: oracle.sampled(inst.V, inst.K, cnt, inst.seed, want_f=False))
     flops = 8 * inst.r * inst.n * inst.S
-    # the K = 3 precision scorer per 32 rows x 32 candidates: 8 (V c, six split
-    # products in one 32-slot chunk) + 4 (V^H z) v_mfma_f32_16x16x32_bf16,
-    # 16,384 flops each as issued; of these, 6 products x 4r flops for V c and
-    # 3 parts x 4r flops for V^H z are the split arithmetic itself
-    issued = 12 * 16384 / 1024 * inst.n * inst.S
-    split = (6 * 4 * inst.r + 3 * 4 * inst.r) * inst.n * inst.S
     return {"workload": "maxcut_ppm", "n": inst.n, "r": inst.r, "K": inst.K, "S": inst.S,
-            "roofline_fp32": _alu_roofline(flops, o32.score_ms, "k_score_rows, 8r flops per row-candidate"),
-            "roofline_bf16": _alu_roofline(flops, o16.score_ms, "k_score_bf16x, the same 8r algorithmic flops"),
-            "roofline_bf16_mfma": _mfma_roofline(issued, o16.score_ms,
-                                                 "k_score_bf16x, MFMA flops as issued (K-slot and row padding included)"),
-            "bf16_split_flops_per_launch": split,
+            "roofline_fp32": _split_roofline(inst.n, inst.r, inst.K, inst.S, o32.score_ms),
+            "roofline_bf16": _split_roofline(inst.n, inst.r, inst.K, inst.S, o16.score_ms),
+            "algorithmic_flops_per_launch": flops,
             "oracle": {"kind": "oracle", "ms": oms, "candidate_rows_per_s": cnt * inst.n / (oms / 1000.0),
                        "cores": ores["threads"],
                        "sample": f"first {cnt} of the {inst.S} directions (FP64, {ores['threads']} threads)"},
@@ -390,19 +395,15 @@ def form_rank1_hybrid():
     m = 1 << 16
     oms, _ = _timed(lambda: R1.rank1_sweep(q[:m], inst.K))
     dev = min(r[1] for r in runs)
-    # per coordinate: prep reads q (16 B) and writes the exact key, the
-    # 32-bit image, label and d (29 B); a pass of the image sort reads the
-    # 8 B pairs twice and writes them once (the first reads no values: 4 B
-    # less); the run check reads the sorted images (4 B); an exact-key pass,
-    # if a long run needs them, 36 B; the tile pass reads the order (4 B),
-    # gathers d (16 B) and writes it in sorted order (16 B); the cell pass
-    # reads that (16 B); the label pass reads key, label and q (25 B) and
-    # writes z (1 B)
-    exact_passes = res.sort_passes - 4
-    sweep_bytes = (45 + 24 * 4 - 4 + 4 + 36 * exact_passes + 36 + 16 + 26) * float(inst.n)
+    # per coordinate, bucket form: prep reads q (16 B) and writes the exact key,
+    # the 32-bit image and the label (13 B); the split reads image and label
+    # (5 B) and writes the 8 B pair; the bucket sort reads that twice, gathers q
+    # (16 B) and writes step and coordinate in sorted order (20 B); the cell
+    # pass reads the steps (16 B); the label pass reads key, label and q (25 B)
+    # and writes z (1 B)
+    sweep_bytes = (29 + 13 + 52 + 16 + 26) * float(inst.n)
     return {"workload": "maxcut_ppm", "n": inst.n, "K": inst.K, "edges": int(len(i)),
-            "roofline": _hbm_roofline(sweep_bytes, dev, "whole sweep: prep, radix passes, run check, tile, "
-                                      "cell and label passes"),
+            "roofline": _hbm_roofline(sweep_bytes, dev, "whole sweep: prep, split, bucket sort, cell and label passes"),
             "oracle": {"kind": "oracle", "ms": oms, "ms_scaled_to_n": oms * inst.n / m,
                        "sample": f"Alg. 1 on the first {m} coordinates of the same q (FP64, Python loop)"},
             "rank1_ms": min(r[0] for r in runs), "rank1_device_ms": min(r[1] for r in runs),
@@ -646,16 +647,14 @@ def measure_headline(inst, workload: str, steps: int, warmup: int) -> dict:
     flops_per_rowcand = 8 * r                      # real V: 2r FMA for V c, 2r FMA for V^H z
     flops = flops_per_rowcand * n * S
     avg_score_ms = sum(score_ms) / len(score_ms)
-    achieved = flops / (avg_score_ms / 1000.0) / 1e12
-    kernel = f"k_score_rows<{r}, 4, true, {K if K in (2, 3, 4, 8, 16) else 0}, false>"
-    rows_at_peak = FP32_VECTOR_PEAK_TFLOPS * 1e12 / flops_per_rowcand
-    roofline = {"bound": "alu", "achieved": round(achieved, 3), "peak": FP32_VECTOR_PEAK_TFLOPS,
-                "unit": "TFLOP/s", "frac": round(achieved / FP32_VECTOR_PEAK_TFLOPS, 4),
-                "traffic": load_traffic(kernel, workload), "kernel": kernel,
-                "kernel_ms": round(avg_score_ms, 4),
-                "algorithmic_flops_per_launch": flops,
-                "candidate_rows_per_s_at_peak": rows_at_peak,
-                "end_to_end_frac": round(value / rows_at_peak, 4)}
+    kernel = f"k_score_split<{r}, true, {K}, false>"
+    roofline = _split_roofline(n, r, K, S, avg_score_ms)
+    rows_at_peak = n * S / (avg_score_ms * roofline["frac"] / 1000.0)
+    roofline.update({"traffic": load_traffic(kernel, workload), "kernel": kernel,
+                     "kernel_ms": round(avg_score_ms, 4),
+                     "algorithmic_flops_per_launch": flops,
+                     "candidate_rows_per_s_at_peak": rows_at_peak,
+                     "end_to_end_frac": round(value / rows_at_peak, 4)})
     data = ("synthetic (seeded 3-block planted-partition graph Laplacian, FP64 Lanczos factor stored FP32)"
             if workload == "maxcut_ppm" else
             "synthetic (seeded ER graph Laplacian, FP64 Lanczos factor stored FP32)")
