@@ -646,12 +646,15 @@ lrqo_status lrqo_solve_batched(const float* V, int32_t count, const int64_t* v_o
 
     // the caller's earlier work on its stream comes first
     LRQO_HIP(hipStreamSynchronize(current_stream()));
-    // ---- finiteness of every factor
+    // ---- finiteness of every factor, checked while the host plans the batch
+    // (16 us of kernel and its wait, beside the sort of the items)
     *h_flag = 0;                       // pinned: the kernel sets it there
     hipLaunchKernelGGL(k_batch_check, dim3(256), dim3(256), 0, bs, V, vfloats, h_flag);
     LRQO_HIP(hipGetLastError());
-    LRQO_HIP(hipStreamSynchronize(bs));
-    if (*h_flag) return fail(LRQO_ENOTFINITE, "a factor holds a NaN or an infinity");
+    const auto finite = [&]() -> lrqo_status {
+        LRQO_HIP(hipStreamSynchronize(bs));
+        return *h_flag ? fail(LRQO_ENOTFINITE, "a factor holds a NaN or an infinity") : LRQO_OK;
+    };
 
     // ---- launch shape: explicit, cached, or tuned now
     LaunchShape ls;
@@ -666,6 +669,7 @@ lrqo_status lrqo_solve_batched(const float* V, int32_t count, const int64_t* v_o
         } else if (itc != g_tune.end()) {
             ls = itc->second;
         } else {
+            LRQO_TRY(finite());
             // time each candidate shape once on this batch (after one warm-up)
             float best_ms = 1e30f;
             const int cpls[3] = {1, 2, 4};
@@ -733,6 +737,7 @@ lrqo_status lrqo_solve_batched(const float* V, int32_t count, const int64_t* v_o
         LRQO_HIP(hipMemcpyAsync(h_obj, d_obj, shared_bytes - results_at, hipMemcpyDeviceToHost, s));
         return LRQO_OK;
     };
+    LRQO_TRY(finite());
     bool captured_now = false;
     if (use_graph && !gc.exec) {
         LRQO_HIP(hipStreamBeginCapture(bs, hipStreamCaptureModeThreadLocal));
