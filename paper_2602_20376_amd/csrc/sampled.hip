@@ -47,11 +47,15 @@ namespace {
 // share of V holds a NaN or an infinity, into bad[blockIdx.x] (so that no
 // block writes the record while block 0 clears it; k_pick gathers them), and
 // the largest finite |V| entry of the share, into vmax[blockIdx.x] (the real
-// K = 3 scorer sizes its quantiser scale from it).
+// K = 3 scorer sizes its quantiser scale from it).  TILES: also the exponents
+// of the columns' largest entries over each tile of the matrix-core scorer.
+template <int R, bool REAL, bool TILES>
 __global__ __launch_bounds__(kBlock) void k_prologue(int K, double2* __restrict__ roots64,
                                                      float2* __restrict__ roots32, DevResult* __restrict__ res,
-                                                     const float* __restrict__ V, int64_t count,
-                                                     int* __restrict__ bad, float* __restrict__ vmax) {
+                                                     const float* __restrict__ V, int64_t n,
+                                                     int* __restrict__ bad, float* __restrict__ vmax,
+                                                     TileExp* __restrict__ tile_exp) {
+    constexpr int RF = Row<R, REAL>::F;
     __shared__ float wmax[kBlock / kWave];
     if (blockIdx.x == 0) {
         for (int k = threadIdx.x; k < K; k += blockDim.x) {
@@ -64,12 +68,49 @@ __global__ __launch_bounds__(kBlock) void k_prologue(int K, double2* __restrict_
     }
     bool b = false;
     float m = 0.0f;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const float x = V[e];
-        const bool fin = isfinite(x);
-        b |= !fin;
-        m = fin ? fmaxf(m, fabsf(x)) : m;
+    if constexpr (TILES) {
+        // a wave takes whole tiles: four rows a lane, and the columns' maxima over the wave
+        const int lane = threadIdx.x & (kWave - 1);
+        const int64_t tiles = (n + kSplitTile - 1) / kSplitTile;
+        for (int64_t t = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; t < tiles;
+             t += (int64_t)gridDim.x * (kBlock / kWave)) {
+            float x[kSplitTile / kWave][RF], c[R];
+#pragma unroll
+            for (int u = 0; u < kSplitTile / kWave; ++u) {
+                const int64_t i = t * kSplitTile + u * kWave + lane;
+#pragma unroll
+                for (int e = 0; e < RF; ++e) x[u][e] = i < n ? V[i * RF + e] : 0.0f;
+            }
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                c[j] = 0.0f;
+#pragma unroll
+                for (int u = 0; u < kSplitTile / kWave; ++u)
+#pragma unroll
+                    for (int e = j * (RF / R); e < (j + 1) * (RF / R); ++e) {
+                        const bool fin = isfinite(x[u][e]);
+                        b |= !fin;
+                        c[j] = fin ? fmaxf(c[j], fabsf(x[u][e])) : c[j];
+                    }
+#pragma unroll
+                for (int off = kWave / 2; off > 0; off >>= 1) c[j] = fmaxf(c[j], __shfl_xor(c[j], off, kWave));
+                m = fmaxf(m, c[j]);
+            }
+            if (lane == 0) {
+                TileExp te{};
+#pragma unroll
+                for (int j = 0; j < R; ++j) te.e[j] = (int16_t)(c[j] > 0.0f ? ilogbf(c[j]) : kZeroColumn);
+                tile_exp[t] = te;
+            }
+        }
+    } else {
+        for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n * RF;
+             e += (int64_t)gridDim.x * blockDim.x) {
+            const float x = V[e];
+            const bool fin = isfinite(x);
+            b |= !fin;
+            m = fin ? fmaxf(m, fabsf(x)) : m;
+        }
     }
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
@@ -570,6 +611,18 @@ void launch_score_k(const ScoreParams& p, dim3 grid, hipStream_t st, ScoreForm f
 template <int R, bool REAL>
 lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
     const uint32_t S = (uint32_t)job.S;
+    if (sc.prologue) {
+        if constexpr (R >= 2 && R <= 4) {
+            if (sc.form == kFormSplit)
+                hipLaunchKernelGGL((k_prologue<R, REAL, true>), dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K,
+                                   sc.roots64, sc.roots32, sc.result, job.V, job.n, sc.bad_blocks, sc.vmax, sc.tile_exp);
+        }
+        if (sc.form != kFormSplit)       // V as one column of floats
+            hipLaunchKernelGGL((k_prologue<1, true, false>), dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K,
+                               sc.roots64, sc.roots32, sc.result, job.V, job.n * Row<R, REAL>::F, sc.bad_blocks,
+                               sc.vmax, nullptr);
+        LRQO_HIP(hipGetLastError());
+    }
     const int cpb = cands_per_block(job, sc.form);
     const int64_t cand_blocks = ((int64_t)S + cpb - 1) / cpb;
 
@@ -595,6 +648,7 @@ lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
     for (int t = 0; t < job.probe_count; ++t) p.probe_idx[t] = job.probe_idx[t];
     p.vmax = sc.vmax;
     p.vmax_count = kCheckBlocks;
+    p.tile_exp = sc.tile_exp;
     launch_score_k<R, REAL>(p, dim3((unsigned)cand_blocks, (unsigned)sc.slices), st, sc.form);
     LRQO_HIP(hipGetLastError());
     LRQO_HIP(hipEventRecord(job.ev_score1, st));
@@ -670,6 +724,14 @@ lrqo_status dispatch_r(const SampledJob& job, Scratch& sc, hipStream_t st) {
 
 }  // namespace
 
+// Doubles of the rescore's buffer, which holds the tiles' exponents before it
+// (they fit in it where the call keeps 64 candidates).
+static size_t rescore_doubles(const SampledJob& job, const ScratchPlan& plan) {
+    static_assert(sizeof(TileExp) == sizeof(double), "one per tile");
+    const size_t tiles = plan.form == kFormSplit ? (size_t)((job.n + kSplitTile - 1) / kSplitTile) : 0;
+    return std::max(tiles, (size_t)plan.topk * plan.rescore_slices * 2 * job.r);
+}
+
 // Plans the launch shapes and the scratch layout of one sampled solve.
 void plan_sampled(const SampledJob& job, ScratchPlan& plan) {
     const int R = job.r;
@@ -698,7 +760,8 @@ void plan_sampled(const SampledJob& job, ScratchPlan& plan) {
         slices = best;
     }
     int64_t rows = (job.n + slices - 1) / slices;
-    rows = ((rows + 63) / 64) * 64;
+    const int64_t align = plan.form == kFormSplit ? kSplitTile : 64;
+    rows = ((rows + align - 1) / align) * align;
     slices = (job.n + rows - 1) / rows;
     plan.slices = (int)slices;
     plan.rows_per_slice = rows;
@@ -717,7 +780,7 @@ void plan_sampled(const SampledJob& job, ScratchPlan& plan) {
     cs.add<unsigned long long>(topk_buffer_keys((uint32_t)job.S, plan.topk));
     cs.add<unsigned long long>(topk_buffer_keys((uint32_t)job.S, plan.topk));
     cs.add<unsigned long long>(slices > 1 ? (size_t)(job.S + kBlock - 1) / kBlock * kBlock : 0);
-    cs.add<double>((size_t)plan.topk * plan.rescore_slices * 2 * R);
+    cs.add<double>(rescore_doubles(job, plan));
     cs.add<int>(kCheckBlocks);
     cs.add<float>(kCheckBlocks);
     plan.bytes = cs.bytes;
@@ -741,20 +804,16 @@ lrqo_status launch_sampled(const SampledJob& job, const ScratchPlan& plan, void*
                                : nullptr;
     sc.rescore_slices = plan.rescore_slices;
     sc.rescore_rows = plan.rescore_rows;
-    sc.rescore = cv.take<double>((size_t)plan.topk * plan.rescore_slices * 2 * job.r);
+    sc.rescore = cv.take<double>(rescore_doubles(job, plan));
+    sc.tile_exp = reinterpret_cast<TileExp*>(sc.rescore);   // used up before the rescore
 
     sc.bad_blocks = cv.take<int>(kCheckBlocks);
     sc.vmax = cv.take<float>(kCheckBlocks);
 
-    const int64_t vcount = job.n * job.r * (job.real ? 1 : 2);
     // a small solve whose scorer reads neither the roots, nor the largest
     // entry, nor counts into the record leaves the checks to k_tail
     sc.tail = plan.tail;
     sc.prologue = !(plan.tail && plan.form == kFormFp32 && k_special(job.K) != 0 && !(job.real && job.K == 3));
-    if (sc.prologue)
-        hipLaunchKernelGGL(k_prologue, dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K, sc.roots64, sc.roots32,
-                           sc.result, job.V, vcount, sc.bad_blocks, sc.vmax);
-    LRQO_HIP(hipGetLastError());
     return job.real ? dispatch_r<true>(job, sc, st) : dispatch_r<false>(job, sc, st);
 }
 

@@ -28,6 +28,14 @@ struct DevResult {
     unsigned long long flagged_rows;
 };
 
+// Exponents of the largest |V| entry of each column over the rows of a tile of
+// the matrix-core scorer (kZeroColumn: the column is zero there).
+constexpr int kSplitTile = 256;
+constexpr int kZeroColumn = -32768;
+struct TileExp {
+    int16_t e[4];
+};
+
 struct ScoreParams {
     const float* V;
     int64_t n;
@@ -48,6 +56,7 @@ struct ScoreParams {
     uint32_t probe_idx[kMaxProbe]; // positions (0..S-1) of the probed candidates
     const float* vmax;             // [vmax_count] largest |V| entry of each prologue block's share
     int vmax_count;
+    const TileExp* tile_exp;       // [ceil(n / kSplitTile)], matrix-core scorer only
 };
 
 struct RescoreParams {
@@ -122,6 +131,7 @@ struct Scratch {
     int rescore_slices;
     int64_t rescore_rows;
     int* bad_blocks;            // [kCheckBlocks] finiteness flags of the prologue's blocks
+    TileExp* tile_exp;          // the tiles' exponents (matrix-core scorer)
     float* vmax;                // [kCheckBlocks] largest finite |V| entry of each prologue block's share
 };
 

@@ -37,11 +37,19 @@ namespace {
 //              each, looked up by v_perm_b32 (eight-byte tables: sector and
 //              sign select the byte)
 //   s = V^H z  v_mfma_i32_32x32x32_i8 of those planes against V in 30-bit
-//              fixed point (one scale for the whole factor, four balanced
-//              base-256 digits per value: 4C <= 32 rows of the operand).  The
-//              sums are exact integers, so the only error is the rounding of
-//              V to 2^-30 of its largest entry; the digits of a component are
-//              put together once per candidate.
+//              fixed point (four balanced base-256 digits per value: 4C <= 32
+//              rows of the operand).  Column j of a 256-row tile enters in
+//              units of 2^(E_j - 29), E_j at most kSplitSlack above the
+//              exponent e of its largest entry there, so an entry is off by at
+//              most 2^(e - 26), a fraction of what one addition to a running
+//              FP32 sum of that size rounds away, and a few large rows cost
+//              only the rows that share their tile.  The sums are exact
+//              integers; their digits are put together, in FP64, where an E_j
+//              changes and at the end.  (10^6 rows, r = 3 real, K = 3, 2^19
+//              candidates: 59.5 ms for normal rows, 66.8 for row sizes u^-3,
+//              u uniform, where most tiles change an E_j.  One scale for the
+//              whole factor took 57.1 ms, but 300,000 rows of 1e-9 beside one
+//              of 3.9 left f off by 1.8e-4, now 1e-5, FP32 sums 1.2e-5.)
 //
 // Layouts (lane l, h = l / 32): operand rows/columns l % 32, F16 k-slots
 // 8h .. 8h+7, I8 k-slots 16h .. 16h+15; result register i is row
@@ -55,7 +63,7 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 constexpr int kSplitBlock = 512;                           // eight waves of 32 candidates
 constexpr int kSplitCands = kSplitBlock / kWave * 32;      // candidates of a block
-constexpr int kSplitTile = 256;                            // rows staged at a time
+static_assert(kSplitTile * 2 == kSplitBlock, "a thread stages one operand of one row");
 
 // Rows whose I32 sums stay exact: digits of V are at most 128 in size, plane
 // entries 1 (K = 16: 128; its sums are folded after as many rows).
@@ -120,8 +128,15 @@ __device__ __forceinline__ uint32_t signs_hi(float a, float b) {
 
 __device__ __forceinline__ uint32_t signs4(float a, float b, float c, float d) { return signs_lo(a, b) | signs_hi(c, d); }
 
-// Exponent e of the largest |V| entry (prologue's per-block maxima): V enters
-// the I8 operand as round(V 2^(29-e)), below 2^30 in size.
+// A column's exponent E (tile_exp holds those of its largest entries, tile by
+// tile, from the prologue) is kept while the largest entry of the tile is in
+// [2^(E - kSplitSlack), 2^(E + 1)); else it becomes one above that entry's
+// exponent (so that the next larger tile need not change it), at most that of
+// the factor's largest entry.  V enters the I8 operand as round(V 2^(29-E)),
+// at most 2^30 in size.
+constexpr int kSplitSlack = 4;
+
+// Exponent of the largest |V| entry (prologue's per-block maxima).
 __device__ __forceinline__ int split_exponent(const float* vmax, int count) {
     float m = 0.0f;
     for (int k = (int)(threadIdx.x & (kWave - 1)); k < count; k += kWave) m = fmaxf(m, vmax[k]);
@@ -129,6 +144,9 @@ __device__ __forceinline__ int split_exponent(const float* vmax, int count) {
     for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
     return m > 0.0f && isfinite(m) ? ilogbf(m) : 0;
 }
+
+// 2^(E - 29)
+__device__ __forceinline__ double split_unit(int E) { return __hiloint2double((E - 29 + 1023) << 20, 0); }
 
 // Label planes of a K.
 __host__ __device__ constexpr int split_planes(int KS) { return KS == 2 ? 1 : (KS == 8 ? 4 : (KS == 16 ? 6 : 2)); }
@@ -145,7 +163,10 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
     constexpr int NPL = split_planes(KS);
     __shared__ __align__(16) v8h aw[2][NB][NCH][64];     // F16 operand of w: [buffer][block][chunk][lane]
     __shared__ __align__(16) signed char as[2][NB][64][16];   // I8 operand of s: [buffer][block][lane][k-slot]
-    __shared__ long long tot[kSplitTile / kWave][C];
+    // a lane's s so far: in LDS, as 128 registers hold no more than the loop needs (8 components: 80 KB
+    // in all, half of a CU's)
+    constexpr int NG = (R + 1) / 2;
+    __shared__ double sums[2 * NG][kSplitBlock];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int h = lane >> 5;
     const int ev = split_exponent(p.vmax, p.vmax_count);
@@ -212,47 +233,62 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[q][i] = 0;
 
-    // ---- s of the lane's columns j = 2g + h from the accumulators, in units of V's fixed point
-    constexpr int NG = (R + 1) / 2;
-    double sum[NG][2];
+    // ---- s of the lane's columns j = 2g + h from the accumulators, which hold
+    // units of 2^(E_j - 29).  K <= 4: without the terms in sum_i V_ij
+    int E[R];
+    // K <= 4: sums of V over the slice.  Wave w adds up the digits of block w of
+    // every tile: lane l those of operand row l % 32 (digit p of a column's Re
+    // or Im) over its sixteen rows of V.
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    const int dslot = (lane & 31) >> 2, dcol = REAL ? dslot : (dslot & 1) + 2 * (dslot >> 2);
+    int digits = 0;
+    double dsum = 0.0;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) sum[g][0] = sum[g][1] = 0.0;
+    for (int g = 0; g < 2 * NG; ++g) sums[g][tid] = 0.0;
     auto fold = [&]() {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            const int j = 2 * g + h;
+            const double unit = split_unit(h && 2 * g + 1 < R ? E[2 * g + 1 < R ? 2 * g + 1 : 0] : E[2 * g]);
             double zr[2] = {0.0, 0.0}, zi[2] = {0.0, 0.0};   // sums of Re z, Im z times Re V_j and times Im V_j
 #pragma unroll
             for (int q = 0; q < (REAL ? 1 : 2); ++q) {
                 const int i0 = REAL ? 4 * g : 8 * g + 4 * q;
                 auto plane = [&](int k) {
-                    return (((long long)acc[k][i0 + 3] * 256 + acc[k][i0 + 2]) * 256 + acc[k][i0 + 1]) * 256 + acc[k][i0];
+                    return unit * (double)((((long long)acc[k][i0 + 3] * 256 + acc[k][i0 + 2]) * 256 + acc[k][i0 + 1]) * 256 +
+                                           acc[k][i0]);
                 };
                 if constexpr (KS <= 4) {
-                    long long t = 0;
-                    if (j < R) {
-                        for (int w = 0; w < kSplitTile / kWave; ++w) t += tot[w][q * R + j];
-                    }
-                    const long long n0 = -plane(0), n1 = -plane(NPL - 1);   // masks are 0 / -1
+                    const double n0 = -plane(0), n1 = -plane(NPL - 1);   // masks are 0 / -1
                     if constexpr (KS == 2) {             // n0: rows with z = -1
-                        zr[q] = (double)(t - 2 * n0);
+                        zr[q] = -2.0 * n0;
                     } else if constexpr (KS == 3) {      // n0, n1: rows with label 0, 2
-                        zr[q] = 0.5 * (double)(3 * n0 - t);
-                        zi[q] = 0.86602540378443865 * (double)(t - n0 - 2 * n1);
+                        zr[q] = 1.5 * n0;
+                        zi[q] = -0.86602540378443865 * (n0 + 2.0 * n1);
                     } else {                             // n0, n1: rows with negative real, imaginary part
-                        zr[q] = 0.70710678118654752 * (double)(t - 2 * n0);
-                        zi[q] = 0.70710678118654752 * (double)(t - 2 * n1);
+                        zr[q] = -1.4142135623730950 * n0;
+                        zi[q] = -1.4142135623730950 * n1;
                     }
                 } else if constexpr (KS == 8) {
-                    zr[q] = 0.92387953251128676 * (double)plane(0) + 0.38268343236508977 * (double)plane(1);
-                    zi[q] = 0.38268343236508977 * (double)plane(2) + 0.92387953251128676 * (double)plane(3);
+                    zr[q] = 0.92387953251128676 * plane(0) + 0.38268343236508977 * plane(1);
+                    zi[q] = 0.38268343236508977 * plane(2) + 0.92387953251128676 * plane(3);
                 } else {
-                    zr[q] = (((double)plane(2) * 256.0 + (double)plane(1)) * 256.0 + (double)plane(0)) * (1.0 / kRoot16);
-                    zi[q] = (((double)plane(5) * 256.0 + (double)plane(4)) * 256.0 + (double)plane(3)) * (1.0 / kRoot16);
+                    zr[q] = ((plane(2) * 256.0 + plane(1)) * 256.0 + plane(0)) * (1.0 / kRoot16);
+                    zi[q] = ((plane(5) * 256.0 + plane(4)) * 256.0 + plane(3)) * (1.0 / kRoot16);
                 }
             }
-            sum[g][0] += REAL ? zr[0] : zr[0] + zi[1];
-            sum[g][1] += REAL ? zi[0] : zi[0] - zr[1];
+            sums[2 * g][tid] += REAL ? zr[0] : zr[0] + zi[1];
+            sums[2 * g + 1][tid] += REAL ? zi[0] : zi[0] - zr[1];
+        }
+#pragma unroll
+        for (int q = 0; q < NPL; ++q)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[q][i] = 0;
+        if constexpr (KS <= 4) {
+            double unit = 0.0;                           // of this lane's column
+#pragma unroll
+            for (int j = 0; j < R; ++j) unit += dcol == j ? split_unit(E[j]) : 0.0;
+            dsum += unit * (double)((long long)digits << (8 * (lane & 3)));
+            digits = 0;
         }
     };
 
@@ -271,10 +307,19 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
             v[x] = in ? src[k] : 0.0f;
         }
     };
-    long long ts[C];
+    // Exponents for a tile; true if one of them changes.
+    auto exponents = [&](int2 te, const int (&from)[R], int (&to)[R]) {
+        const int w[2] = {__builtin_amdgcn_readfirstlane(te.x), __builtin_amdgcn_readfirstlane(te.y)};
+        bool change = false;
 #pragma unroll
-    for (int k = 0; k < C; ++k) ts[k] = 0;
-    auto stage = [&](int buf) {
+        for (int j = 0; j < R; ++j) {
+            const int e = (w[j / 2] << (16 - 16 * (j & 1))) >> 16;
+            to[j] = e == kZeroColumn || (e <= from[j] && e >= from[j] - kSplitSlack) ? from[j] : min(e + 1, ev);
+            change |= to[j] != from[j];
+        }
+        return change;
+    };
+    auto stage = [&](int buf, const int (&Et)[R]) {
         const int blk = row >> 5, rr = row & 31;
         if (!fixed) {
             float m = fabsf(v[0]);
@@ -300,8 +345,7 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
             const int d = rr >> 3, g = (rr >> 2) & 1, b = rr & 3;
 #pragma unroll
             for (int k = 0; k < C; ++k) {
-                const int q = __float2int_rn(ldexpf(v[k], 29 - ev));
-                if constexpr (KS <= 4) ts[k] += q;
+                const int q = __float2int_rn(ldexpf(v[k], 29 - Et[k % R]));
                 const uint32_t dig = ((uint32_t)q + 0x00808080u) ^ 0x00808080u;   // balanced digits, lowest first
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
@@ -310,17 +354,33 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
         }
     };
 
+    const int2* __restrict__ te = reinterpret_cast<const int2*>(p.tile_exp) + r0 / kSplitTile;   // a slice begins with a tile
+    int2 tn = te[0];
     fetch(r0);
     __syncthreads();                                     // the zeroed operand
-    stage(0);
-    if (r0 + kSplitTile < r1) fetch(r0 + kSplitTile);
+#pragma unroll
+    for (int j = 0; j < R; ++j) E[j] = ev;
+    exponents(tn, E, E);
+    stage(0, E);
+    if (r0 + kSplitTile < r1) {
+        fetch(r0 + kSplitTile);
+        tn = *++te;
+    }
     __syncthreads();
     int buf = 0;
     for (int64_t t0 = r0; t0 < r1; t0 += kSplitTile, buf ^= 1) {
         // the next tile's operands go to the other buffer while this one is used
+        int En[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) En[j] = E[j];
+        bool change = false;
         if (t0 + kSplitTile < r1) {
-            stage(buf ^ 1);
-            if (t0 + 2 * kSplitTile < r1) fetch(t0 + 2 * kSplitTile);
+            change = exponents(tn, E, En);
+            stage(buf ^ 1, En);
+            if (t0 + 2 * kSplitTile < r1) {
+                fetch(t0 + 2 * kSplitTile);
+                tn = *++te;
+            }
         }
         const int nb = (int)min((int64_t)NB, (r1 - t0 + 31) / 32);
 #pragma unroll 2
@@ -417,35 +477,58 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
                 }
             }
         }
-        __syncthreads();
-        if constexpr (KS == 16) {                        // before the sums could pass 31 bits
-            if ((t0 - r0) % split_rows(KS) == split_rows(KS) - kSplitTile && t0 + kSplitTile < r1) {
-                fold();
+        if constexpr (KS <= 4) {
+            if (uwave < nb) {
+                const v4i a8 = *reinterpret_cast<const v4i*>(as[buf][uwave][lane]);
 #pragma unroll
-                for (int q = 0; q < NPL; ++q)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[q][i] = 0;
+                for (int d = 0; d < 4; ++d) digits = __builtin_amdgcn_sdot4(a8[d], 0x01010101, digits, false);
             }
         }
+        // K = 16: also before the sums could pass 31 bits
+        const bool full = KS == 16 && (t0 - r0) % split_rows(KS) == split_rows(KS) - kSplitTile;
+        if (change || full) {
+            fold();
+#pragma unroll
+            for (int j = 0; j < R; ++j) E[j] = En[j];
+        }
+        __syncthreads();
     }
 
-    // ---- sum_i V_i over the slice (exact), then s of each candidate
-#pragma unroll
-    for (int k = 0; k < C; ++k) {
-        long long t = ts[k];
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, kWave);
-        if (fixed && lane == 0) tot[wave - kSplitTile / kWave][k] = t;
-    }
-    __syncthreads();
     fold();
-    const double unit = ldexp(1.0, ev - 29);
+    double sum[NG][2];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) sum[g][u] = sums[2 * g + u][tid];
+    // ---- K <= 4: the terms in sum_i V_i over the slice; then s of each candidate
+    if constexpr (KS <= 4) {
+        double* tot = reinterpret_cast<double*>(aw);     // no longer in use: the loop ends with a barrier
+        tot[tid] = dsum;
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            double t[2] = {0.0, 0.0};                    // sums of Re V_j, Im V_j, j = 2g + h
+#pragma unroll
+            for (int q = 0; q < (REAL ? 1 : 2); ++q) {
+                const int at = 4 * (REAL ? 2 * g + h : 4 * g + 2 * q + h);   // its first digit
+#pragma unroll 1
+                for (int w = 0; w < kSplitBlock / kWave; ++w)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) t[q] += tot[w * kWave + at + d] + tot[w * kWave + 32 + at + d];
+            }
+            // z = a + ib in every row, corrected by the masks
+            constexpr double a = KS == 2 ? 1.0 : (KS == 3 ? -0.5 : 0.70710678118654752);
+            constexpr double b = KS == 2 ? 0.0 : (KS == 3 ? 0.86602540378443865 : 0.70710678118654752);
+            sum[g][0] += a * t[0] + b * t[1];
+            sum[g][1] += b * t[0] - a * t[1];
+        }
+    }
     float f = 0.0f;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
         const int j = 2 * g + h;
         if (j >= R) continue;
-        const float sr = (float)(unit * sum[g][0]), si = (float)(unit * sum[g][1]);
+        const float sr = (float)sum[g][0], si = (float)sum[g][1];
         f = fmaf(sr, sr, fmaf(si, si, f));
         if (gridDim.y > 1 && idx < p.S) {
             float* out = p.partial + ((size_t)blockIdx.y * (2 * R) + 2 * j) * p.S + idx;
