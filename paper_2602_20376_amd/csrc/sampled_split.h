@@ -71,7 +71,9 @@ __host__ __device__ constexpr int64_t split_rows(int KS) { return (int64_t)1 << 
 
 // K = 16 planes.  Entry e of a table: bits 0 and 1 name the sector of the
 // quadrant, bit 2 is the sign; entries hold digit k of round(mag * kRoot16).
-constexpr double kRoot16 = 8200000.0;                      // top digit stays below 128
+// The factor keeps the top digit below 128 and all four roundings below 2^-30,
+// where FP32 roots have up to 2^-25.
+constexpr double kRoot16 = 8312657.375;
 constexpr double root16_mag(int e) {
     return (e & 3) == 3 ? 0.98078528040323043 : (e & 3) == 1 ? 0.83146961230254524 : (e & 3) == 0 ? 0.55557023301960218 : 0.19509032201612826;
 }
@@ -83,6 +85,15 @@ constexpr uint32_t root16_table(int half, int k) {
     return root16_digit(4 * half, k) | root16_digit(4 * half + 1, k) << 8 | root16_digit(4 * half + 2, k) << 16 |
            root16_digit(4 * half + 3, k) << 24;
 }
+
+constexpr bool root16_close() {
+    for (int e = 0; e < 4; ++e) {
+        const double x = root16_mag(e) * kRoot16, d = x - (double)(long long)(x + 0.5);
+        if ((d < 0.0 ? -d : d) > kRoot16 / 1073741824.0) return false;
+    }
+    return true;
+}
+static_assert(root16_close(), "roundings of the K = 16 magnitudes");
 
 template <int R, bool REAL>
 struct SplitShape {
