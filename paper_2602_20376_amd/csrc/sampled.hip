@@ -569,8 +569,15 @@ void launch_score_bf16(const ScoreParams& p, dim3 grid, hipStream_t st) {
 
 template <int R, bool REAL, int KS>
 void launch_score_split(const ScoreParams& p, dim3 grid, hipStream_t st) {
-    if constexpr (R >= 2 && R <= 4 && !(REAL && KS == 2))
-        hipLaunchKernelGGL((k_score_split<R, REAL, KS, false>), grid, dim3(kSplitBlock), 0, st, p);
+    if constexpr (R >= 2 && R <= 4 && !(REAL && KS == 2)) {
+        if constexpr (R == 3 && REAL) {
+            if (p.quick) {
+                hipLaunchKernelGGL((k_score_split<R, REAL, KS, false, true>), grid, dim3(kSplitBlock), 0, st, p);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_score_split<R, REAL, KS, false, false>), grid, dim3(kSplitBlock), 0, st, p);
+    }
 }
 
 template <int R, bool REAL>
@@ -649,6 +656,7 @@ lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
     p.vmax = sc.vmax;
     p.vmax_count = kCheckBlocks;
     p.tile_exp = sc.tile_exp;
+    p.quick = job.precision == 1;
     launch_score_k<R, REAL>(p, dim3((unsigned)cand_blocks, (unsigned)sc.slices), st, sc.form);
     LRQO_HIP(hipGetLastError());
     LRQO_HIP(hipEventRecord(job.ev_score1, st));

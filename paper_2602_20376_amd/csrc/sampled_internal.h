@@ -57,6 +57,7 @@ struct ScoreParams {
     const float* vmax;             // [vmax_count] largest |V| entry of each prologue block's share
     int vmax_count;
     const TileExp* tile_exp;       // [ceil(n / kSplitTile)], matrix-core scorer only
+    int quick;                     // matrix-core scorer: the precision form asked for
 };
 
 struct RescoreParams {

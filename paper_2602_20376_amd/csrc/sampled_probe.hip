@@ -41,8 +41,15 @@ void probe_bf16(const ScoreParams& p, dim3 grid, hipStream_t st) {
 
 template <int R, bool REAL, int KS>
 void probe_split(const ScoreParams& p, dim3 grid, hipStream_t st) {
-    if constexpr (R >= 2 && R <= 4 && !(REAL && KS == 2))
-        hipLaunchKernelGGL((k_score_split<R, REAL, KS, true>), grid, dim3(kSplitBlock), 0, st, p);
+    if constexpr (R >= 2 && R <= 4 && !(REAL && KS == 2)) {
+        if constexpr (R == 3 && REAL) {
+            if (p.quick) {
+                hipLaunchKernelGGL((k_score_split<R, REAL, KS, true, true>), grid, dim3(kSplitBlock), 0, st, p);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_score_split<R, REAL, KS, true, false>), grid, dim3(kSplitBlock), 0, st, p);
+    }
 }
 
 template <int R, bool REAL>
