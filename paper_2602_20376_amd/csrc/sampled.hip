@@ -523,24 +523,26 @@ int cands_per_block(const SampledJob& job, ScoreForm form) {
 }
 
 // The scorer of a call.  k_score_split takes K = 2, 3, 4, 8, 16 and
-// 2 <= r <= 4 in both precisions: it is 1.8 to 3.9 times as fast as the FP32
+// 2 <= r <= 4 in both precisions: it is 1.7 to 3.9 times as fast as the FP32
 // scorer at every n tried (5,000 rows, r = 3 real, K = 3: 0.049 against
-// 0.155 ms for 4,096 candidates; 10^6 rows: 14.7 against 35.0 ms for 131,072;
-// r = 3 complex, K = 16, 200,000 rows: 4.7 against 14.9 ms for 65,536) and its
+// 0.155 ms for 4,096 candidates; 10^6 rows: 17.3 against 30.5 ms for 131,072;
+// r = 3 complex, K = 16, 200,000 rows: 5.0 against 14.9 ms for 65,536) and its
 // scores lie 4 to 70 times closer to FP64.  It is kept to problems whose
-// assignments far outnumber the candidates: where many candidates round to one
-// assignment up to a rotation their objectives are equal, only the rounding of
-// the score orders them, and the scorers that served such sizes before keep
-// doing so.  The count is the order of the arrangement's vertices, n^(2r-1);
-// for real V and K = 4 the quadrants of the turned w depend on Re c and Im c
-// apart (n^(2r-2)), and for real V and K = 2 on Re c alone (few assignments,
-// not taken).
+// assignments far outnumber the candidates of an ordinary call (2^20): where
+// many candidates round to one assignment up to a rotation their objectives are
+// equal, only the rounding of the score orders them, and the scorers that
+// served such sizes before keep doing so.  The count is the order of the
+// arrangement's vertices, n^(2r-1), at least 2^33 from n = 2,048 on; for real V
+// and K = 4 the quadrants of the turned w depend on Re c and Im c apart
+// (n^(2r-2): r = 2 from 2^32 on) and for real V and K = 2 on Re c alone (few
+// assignments, not taken).  The call's own S has no part in it: the pieces of a
+// range of directions are scored as the whole.
 ScoreForm score_form(const SampledJob& job) {
     const ScoreForm plain = job.precision == 1 ? kFormPrecision : kFormFp32;
     if (k_special(job.K) == 0 || job.r < 2 || job.r > 4 || (job.real && job.K == 2)) return plain;
     if (job.n < 2048 || job.n > split_rows(2) || (plain == kFormPrecision && bf16_form() == 1)) return plain;
-    const double vertices = std::pow((double)job.n, job.real && job.K == 4 ? 2 * job.r - 2 : 2 * job.r - 1);
-    return vertices >= 4096.0 * (double)job.S ? kFormSplit : plain;
+    if (job.real && job.K == 4 && job.r == 2 && job.n < 65536) return plain;
+    return kFormSplit;
 }
 
 template <int R, bool REAL, int KS>

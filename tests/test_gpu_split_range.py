@@ -74,3 +74,20 @@ def test_scores_of_uneven_factors(lrqo_mod, kind, n, r, K, real):  # noqa: F811
     for t, pos in enumerate(probe):
         PH.check_labels(V, K, dirs[pos], labels[t], PH.REACH_PRECISION)
     assert out.obj >= np.max(ref["f"]) * (1.0 - 1e-5)
+
+
+def test_pieces_of_a_range_score_as_the_whole(lrqo_mod):  # noqa: F811
+    """The scores of 2^22 directions, in one call and in two (one row slice
+    each), bit for bit: the choice of the scorer does not depend on the length
+    of the range."""
+    torch = pytest.importorskip("torch")
+    n, r, K, S = 2100, 2, 3, 1 << 22
+    V = torch.from_numpy(inputs.random_V(n, r, 5).astype(np.complex64)).cuda()
+    f = torch.empty(S, dtype=torch.float32, device="cuda")
+    g = torch.empty(S, dtype=torch.float32, device="cuda")
+    whole = lrqo_mod.solve_sampled(V, K, S, 3, f_out=f)
+    parts = [lrqo_mod.solve_sampled(V, K, S // 2, 3, first_index=q * (S // 2), f_out=g[q * (S // 2):(q + 1) * (S // 2)])
+             for q in range(2)]
+    assert whole.slices == 1 and all(p.slices == 1 for p in parts)
+    assert torch.equal(f, g)
+    assert max(p.obj for p in parts) == whole.obj
