@@ -48,13 +48,15 @@ namespace {
 // block writes the record while block 0 clears it; k_pick gathers them), and
 // the largest finite |V| entry of the share, into vmax[blockIdx.x] (the real
 // K = 3 scorer sizes its quantiser scale from it).  TILES: also the exponents
-// of the columns' largest entries over each tile of the matrix-core scorer.
+// of the columns' largest entries over each tile of the matrix-core scorer, and
+// whether a caller's list of directions is outside its range.
 template <int R, bool REAL, bool TILES>
 __global__ __launch_bounds__(kBlock) void k_prologue(int K, double2* __restrict__ roots64,
                                                      float2* __restrict__ roots32, DevResult* __restrict__ res,
                                                      const float* __restrict__ V, int64_t n,
                                                      int* __restrict__ bad, float* __restrict__ vmax,
-                                                     TileExp* __restrict__ tile_exp) {
+                                                     TileExp* __restrict__ tile_exp,
+                                                     const float* __restrict__ dirs, uint32_t S) {
     constexpr int RF = Row<R, REAL>::F;
     __shared__ float wmax[kBlock / kWave];
     if (blockIdx.x == 0) {
@@ -68,7 +70,14 @@ __global__ __launch_bounds__(kBlock) void k_prologue(int K, double2* __restrict_
     }
     bool b = false;
     float m = 0.0f;
+    bool wide = false;
     if constexpr (TILES) {
+        for (int64_t q = blockIdx.x * kBlock + threadIdx.x; dirs && q < (int64_t)S; q += (int64_t)gridDim.x * kBlock) {
+            float c[2 * R];
+#pragma unroll
+            for (int j = 0; j < 2 * R; ++j) c[j] = dirs[q * (2 * R) + j];
+            wide |= !direction_in_range<R>(c, K);
+        }
         // a wave takes whole tiles: four rows a lane, and the columns' maxima over the wave
         const int lane = threadIdx.x & (kWave - 1);
         const int64_t tiles = (n + kSplitTile - 1) / kSplitTile;
@@ -115,9 +124,9 @@ __global__ __launch_bounds__(kBlock) void k_prologue(int K, double2* __restrict_
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
     if ((threadIdx.x & (kWave - 1)) == 0) wmax[threadIdx.x / kWave] = m;
-    const int any = __syncthreads_or(b);
+    const int any = __syncthreads_or(b), any_wide = __syncthreads_or(wide);
     if (threadIdx.x == 0) {
-        bad[blockIdx.x] = any;
+        bad[blockIdx.x] = (any ? kFlagNonfinite : 0) | (any_wide ? kFlagWide : 0);
         float mm = 0.0f;
         for (int w = 0; w < kBlock / kWave; ++w) mm = fmaxf(mm, wmax[w]);
         vmax[blockIdx.x] = mm;
@@ -290,7 +299,7 @@ __global__ __launch_bounds__(64 * 2 * R) void k_pick(const double* __restrict__ 
         comp[t][j] = a;
     }
     int b = 0;                                   // the prologue's finiteness flags
-    for (int q = threadIdx.x; q < nbad; q += blockDim.x) b |= bad[q];
+    for (int q = threadIdx.x; q < nbad; q += blockDim.x) b |= bad[q] & kFlagNonfinite;
     const int any_bad = __syncthreads_or(b);
     if (threadIdx.x >= kWave) return;
     const int lane = threadIdx.x;
@@ -420,7 +429,7 @@ __global__ __launch_bounds__(kTailWaves * kWave) void k_tail(TailParams p) {
         b |= !isfinite(x);
     }
     if (p.bad)
-        for (int q = tid; q < p.nbad; q += kTailWaves * kWave) b |= p.bad[q];
+        for (int q = tid; q < p.nbad; q += kTailWaves * kWave) b |= p.bad[q] & kFlagNonfinite;
     // the best 64 keys
     unsigned long long run = 0;
     for (uint32_t g0 = w * kWave; g0 < p.S; g0 += kTailWaves * kWave) {
@@ -624,16 +633,15 @@ lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
         if constexpr (R >= 2 && R <= 4) {
             if (sc.form == kFormSplit)
                 hipLaunchKernelGGL((k_prologue<R, REAL, true>), dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K,
-                                   sc.roots64, sc.roots32, sc.result, job.V, job.n, sc.bad_blocks, sc.vmax, sc.tile_exp);
+                                   sc.roots64, sc.roots32, sc.result, job.V, job.n, sc.bad_blocks, sc.vmax, sc.tile_exp,
+                                   job.dirs, S);
         }
         if (sc.form != kFormSplit)       // V as one column of floats
             hipLaunchKernelGGL((k_prologue<1, true, false>), dim3(kCheckBlocks), dim3(kBlock), 0, st, job.K,
                                sc.roots64, sc.roots32, sc.result, job.V, job.n * Row<R, REAL>::F, sc.bad_blocks,
-                               sc.vmax, nullptr);
+                               sc.vmax, nullptr, nullptr, 0u);
         LRQO_HIP(hipGetLastError());
     }
-    const int cpb = cands_per_block(job, sc.form);
-    const int64_t cand_blocks = ((int64_t)S + cpb - 1) / cpb;
 
     // ---- fused scorer
     ScoreParams p{};
@@ -659,7 +667,18 @@ lrqo_status run_sampled(const SampledJob& job, Scratch& sc, hipStream_t st) {
     p.vmax_count = kCheckBlocks;
     p.tile_exp = sc.tile_exp;
     p.quick = job.precision == 1;
-    launch_score_k<R, REAL>(p, dim3((unsigned)cand_blocks, (unsigned)sc.slices), st, sc.form);
+    const auto launch = [&](ScoreForm form) {
+        const int64_t cpb = cands_per_block(job, form);
+        launch_score_k<R, REAL>(p, dim3((unsigned)((S + cpb - 1) / cpb), (unsigned)sc.slices), st, form);
+    };
+    if (sc.form == kFormSplit && job.dirs) {   // one of the two returns at once (4 us)
+        p.list_flags = sc.bad_blocks;
+        p.list_flag_count = kCheckBlocks;
+        launch(kFormSplit);
+        launch(kFormFp32);
+    } else {
+        launch(sc.form);
+    }
     LRQO_HIP(hipGetLastError());
     LRQO_HIP(hipEventRecord(job.ev_score1, st));
     const int T = sc.topk;

@@ -32,6 +32,11 @@ struct DevResult {
 // the matrix-core scorer (kZeroColumn: the column is zero there).
 constexpr int kSplitTile = 256;
 constexpr int kZeroColumn = -32768;
+
+// Flags of a prologue block.
+constexpr int kFlagNonfinite = 1;   // its share of V holds a NaN or an infinity
+constexpr int kFlagWide = 2;        // its share of the caller's list holds a direction for the FP32 scorer
+
 struct TileExp {
     int16_t e[4];
 };
@@ -58,6 +63,8 @@ struct ScoreParams {
     int vmax_count;
     const TileExp* tile_exp;       // [ceil(n / kSplitTile)], matrix-core scorer only
     int quick;                     // matrix-core scorer: the precision form asked for
+    const int* list_flags;         // a caller's list in the range of the matrix-core scorer: the
+    int list_flag_count;           // prologue's flags (kFlagWide: the FP32 scorer takes the call)
 };
 
 struct RescoreParams {
@@ -131,7 +138,7 @@ struct Scratch {
     double* rescore;
     int rescore_slices;
     int64_t rescore_rows;
-    int* bad_blocks;            // [kCheckBlocks] finiteness flags of the prologue's blocks
+    int* bad_blocks;            // [kCheckBlocks] flags of the prologue's blocks
     TileExp* tile_exp;          // the tiles' exponents (matrix-core scorer)
     float* vmax;                // [kCheckBlocks] largest finite |V| entry of each prologue block's share
 };

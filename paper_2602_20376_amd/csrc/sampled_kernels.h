@@ -40,6 +40,13 @@ __device__ __forceinline__ int root_index(float zr, float zi, int K) {
     return k >= K ? k - K : k;
 }
 
+// Whether the prologue flagged a caller's list for the FP32 scorer (the same in every wave).
+__device__ __forceinline__ bool list_is_wide(const ScoreParams& p) {
+    int b = 0;
+    for (int k = (int)(threadIdx.x & (kWave - 1)); k < p.list_flag_count; k += kWave) b |= p.list_flags[k];
+    return __any(b & kFlagWide);
+}
+
 // Candidate directions of one lane (position idx = base + q * stride) and,
 // when asked, their FP32 values written once (first row slice, first wave),
 // plus the probe slot of each candidate (-1: not probed).
@@ -385,6 +392,7 @@ __global__ __launch_bounds__(kBlock) void k_score_rows(ScoreParams p) {
     __shared__ float red[NW - 1][CPL * 2 * R][kWave];
     constexpr bool Q3 = REAL && KS == 3;   // score_vals' real K = 3 form needs sum_i V_i
     __shared__ float tsum[Q3 ? NW * R : 1];
+    if (p.list_flags && !list_is_wide(p)) return;        // the matrix-core scorer has done it
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid / kWave;

@@ -200,6 +200,37 @@ __device__ __forceinline__ uint32_t signs4(float a, float b, float c, float d) {
 // at most 2^30 in size.
 constexpr int kSplitSlack = 4;
 
+// Whether a direction of a caller's list lies within the range of the F16 parts,
+// which reach down to 2^-39 of a row's and of a direction's largest entry.  The
+// product of the smallest parts of V and the largest of c, and the reverse, is
+// no more than 2^-27 of sum_j |V_ij||c_j| while no component is below 2^-12 of
+// the largest (a row may lie on one column).  K = 2, 3, 4: the same for Re w and
+// Im w as a whole, and no part that decides a sign alone may be lost or a tie
+// (2^-24: real or imaginary c_j; K = 4: their sum and difference).  Of 2^20
+// directions of the sphere the smallest component is near 2^-11 of the largest,
+// and below 2^-16, where a row on that column alone would lose more than in
+// FP32, once in a thousand calls; so only lists, which may hold axes, are looked
+// at.  false for NaN, infinities and zero.
+template <int R>
+__device__ __forceinline__ bool direction_in_range(const float (&c)[2 * R], int K) {
+    float lo = INFINITY, hi = 0.0f, small = INFINITY, re = 0.0f, im = 0.0f;
+    bool finite = true;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const float a = fabsf(c[2 * j]), b = fabsf(c[2 * j + 1]);
+        finite &= isfinite(a) && isfinite(b);
+        lo = fminf(lo, fmaxf(a, b));
+        hi = fmaxf(hi, fmaxf(a, b));
+        const float x = K == 4 ? 0.5f * a + 0.5f * b : a, y = K == 4 ? fabsf(0.5f * a - 0.5f * b) : b;
+        re = fmaxf(re, x);
+        im = fmaxf(im, y);
+        small = fminf(small, K == 2 ? x : fminf(x, y));
+    }
+    const float least = hi * 0x1p-12f;
+    if (!finite || !(lo > 0.0f) || !(lo >= least)) return false;
+    return K > 4 || (small > 0.0f && small >= hi * 0x1p-24f && re >= least && (K == 2 || im >= least));
+}
+
 // Exponent of the largest |V| entry (prologue's per-block maxima).
 __device__ __forceinline__ int split_exponent(const float* vmax, int count) {
     float m = 0.0f;
@@ -232,6 +263,7 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
     // in all, half of a CU's)
     constexpr int NG = (R + 1) / 2;
     __shared__ double sums[2 * NG][kSplitBlock];
+    if (p.list_flags && list_is_wide(p)) return;         // left to the FP32 scorer
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int h = lane >> 5;
     const int ev = split_exponent(p.vmax, p.vmax_count);
