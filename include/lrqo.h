@@ -376,6 +376,11 @@ typedef struct lrqo_rank1_result {
 
 lrqo_status lrqo_solve_rank1(const double* q, int64_t n, int32_t K, uint8_t* z, lrqo_rank1_result* res);
 
+/* Form in which the calling thread's last successful lrqo_solve_rank1 ended
+ * (inspection; the result does not depend on it): 1 buckets sorted in LDS
+ * (n <= 2^24 and points spread over the range), 0 the general sort, -1 none yet. */
+int32_t lrqo_rank1_form(void);
+
 /* --------------------------------------------------------------------------
  * Objective on the graph and greedy local refinement (the step after the
  * low-rank solve: labels scored on the original sparse matrix and improved by

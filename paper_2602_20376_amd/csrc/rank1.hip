@@ -690,6 +690,8 @@ int ceil_log2(int64_t x) {
     return b;
 }
 
+thread_local int t_form = -1;      // form of the thread's last call
+
 // Buckets of 1,024 to 2,048 points; from 256 to 512 points each while that
 // leaves fewer than 256 buckets (a block each) for the chip's 256 CUs.
 int rb_bucket_bits(int64_t n) {
@@ -700,6 +702,8 @@ int rb_bucket_bits(int64_t n) {
 }  // namespace lrqo
 
 extern "C" {
+
+int32_t lrqo_rank1_form(void) { return lrqo::t_form; }
 
 lrqo_status lrqo_solve_rank1(const double* q, int64_t n, int32_t K, uint8_t* z, lrqo_rank1_result* res) {
     using namespace lrqo;
@@ -864,6 +868,7 @@ lrqo_status lrqo_solve_rank1(const double* q, int64_t n, int32_t K, uint8_t* z, 
     }
     float ms = 0.0f;
     LRQO_HIP(hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop));
+    t_form = done ? 1 : 0;
     if (res) {
         std::memset(res, 0, sizeof *res);
         res->obj = sx * sx + sy * sy;

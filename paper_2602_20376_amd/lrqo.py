@@ -27,7 +27,8 @@ EXPORTS = ("lrqo_version", "lrqo_last_error", "lrqo_set_stream", "lrqo_shutdown"
            "lrqo_solve_exact_ex", "lrqo_solve_batched", "lrqo_proposal_param_count",
            "lrqo_proposal_create", "lrqo_proposal_destroy", "lrqo_proposal_get_state",
            "lrqo_proposal_set_state", "lrqo_proposal_train_step", "lrqo_proposal_sample",
-           "lrqo_proposal_frame", "lrqo_solve_nullvec", "lrqo_solve_rank1", "lrqo_graph_objective",
+           "lrqo_proposal_frame", "lrqo_solve_nullvec", "lrqo_solve_rank1", "lrqo_rank1_form",
+           "lrqo_graph_objective",
            "lrqo_refine_greedy", "lrqo_laplacian_factor", "lrqo_phase_sync_factor")
 
 
@@ -473,6 +474,11 @@ def solve_rank1(q, K: int, *, z=None):
         _check(lib.lrqo_solve_rank1(ctypes.c_void_p(qc.data_ptr()), n, int(K), ctypes.c_void_p(z.data_ptr()),
                                     ctypes.byref(res)))
     return z, res
+
+
+def rank1_form() -> int:
+    """Form of this thread's last solve_rank1 (see lrqo_rank1_form)."""
+    return load().lrqo_rank1_form()
 
 
 def _graph(row_ptr, col, w):
