@@ -113,14 +113,16 @@ def _fp64_roofline(flops: float, ms: float, what: str) -> dict:
 I8_MFMA_PEAK_TOPS = 5000.0
 
 
-def _split_roofline(n: int, r: int, K: int, S: int, ms: float) -> dict:
+def _split_roofline(n: int, r: int, K: int, S: int, ms: float, quick: bool = False) -> dict:
     """The matrix-core scorer of a real V (K = 2, 3, 4, 2 <= r <= 4), operations
     as issued per 32 rows x 32 candidates: v_mfma_f32_32x32x16_f16 for Re w and
-    Im w (Re alone for K = 2), one k-chunk for r <= 3 and two for r = 4, and one
-    v_mfma_i32_32x32x32_i8 per label plane (one for K = 2, else two).  The peak
-    is that of this mix: each kind at its own dense rate."""
-    f16 = (1 if K == 2 else 2) * (1 if r <= 3 else 2) * 2 * 32 * 32 * 16 / 1024.0 * n * S
-    i8 = (1 if K == 2 else 2) * 2 * 32 * 32 * 32 / 1024.0 * n * S
+    Im w (one k-chunk each for r = 2, two for r = 4; r = 3: one each, and one
+    more for Re w with K = 3 unless `quick`, the precision form), and one
+    v_mfma_i32_32x32x32_i8 for each of the two label planes.  The peak is that
+    of this mix: each kind at its own dense rate."""
+    chunks = {2: 2, 3: 3 if K == 3 and not quick else 2, 4: 4}[r]
+    f16 = chunks * 2 * 32 * 32 * 16 / 1024.0 * n * S
+    i8 = 2 * 2 * 32 * 32 * 32 / 1024.0 * n * S
     peak = (f16 + i8) / (f16 / BF16_MFMA_PEAK_TFLOPS + i8 / I8_MFMA_PEAK_TOPS)
     achieved = (f16 + i8) / (ms / 1000.0) / 1e12
     return {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": "TOP/s",
@@ -167,9 +169,12 @@ def _time(fn, reps):
 
 
 def form_precision():
-    """The precision form against the FP32 scorer on the 3-block planted
-    partition (n = 1e6, r = 3, K = 3, S = 2^20), same direction stream.  At this
-    size both take the matrix-core scorer from split FP32 values."""
+    """The precision form against the FP32 form on the 3-block planted
+    partition (n = 1e6, r = 3, S = 2^20, same direction stream).  K = 3: both
+    take the matrix-core scorer from split FP32 values, the precision form with
+    one F16 chunk less for Re w.  K = 2 (its Max-Cut, S = 2^17), which that
+    scorer does not take for a real V: the FP32 scorer on the vector ALU and the
+    BF16 scorer."""
     import torch
 
     from paper_2602_20376_amd import inputs, lrqo
@@ -177,10 +182,15 @@ def form_precision():
     inst = inputs.maxcut_ppm()
     V = torch.from_numpy(inputs.as_real_f32(inst.V)).cuda()
     z = torch.empty(inst.n, dtype=torch.uint8, device="cuda")
-    run = lambda prec: lrqo.solve_sampled(V, inst.K, inst.S, inst.seed, real=True, precision=prec, z=z)
-    run(0), run(1)
-    ms32, o32 = _time(lambda: run(0), 3)
-    ms16, o16 = _time(lambda: run(1), 3)
+
+    def both(K, S):
+        run = lambda prec: lrqo.solve_sampled(V, K, S, inst.seed, real=True, precision=prec, z=z)
+        run(0), run(1)
+        return (*_time(lambda: run(0), 3), *_time(lambda: run(1), 3))
+
+    ms32, o32, msp, op = both(inst.K, inst.S)
+    S2 = 1 << 17
+    cut32, c32, cutp, cp = both(2, S2)
     import oracle
 
     oracle.build()
@@ -189,16 +199,19 @@ def form_precision():
     flops = 8 * inst.r * inst.n * inst.S
     return {"workload": "maxcut_ppm", "n": inst.n, "r": inst.r, "K": inst.K, "S": inst.S,
             "roofline_fp32": _split_roofline(inst.n, inst.r, inst.K, inst.S, o32.score_ms),
-            "roofline_bf16": _split_roofline(inst.n, inst.r, inst.K, inst.S, o16.score_ms),
+            "roofline_precision": _split_roofline(inst.n, inst.r, inst.K, inst.S, op.score_ms, quick=True),
             "algorithmic_flops_per_launch": flops,
             "oracle": {"kind": "oracle", "ms": oms, "candidate_rows_per_s": cnt * inst.n / (oms / 1000.0),
                        "cores": ores["threads"],
                        "sample": f"first {cnt} of the {inst.S} directions (FP64, {ores['threads']} threads)"},
-            "fp32_ms": ms32, "bf16_ms": ms16, "bf16_speedup": ms32 / ms16,
-            "fp32_score_ms": o32.score_ms, "bf16_score_ms": o16.score_ms,
-            "obj_fp32": o32.obj, "obj_bf16": o16.obj,
-            "obj_rel_diff": abs(o16.obj - o32.obj) / o32.obj,
-            "flagged_fraction": o16.flagged_rows / float(inst.n * inst.S)}
+            "fp32_ms": ms32, "precision_ms": msp, "precision_speedup": ms32 / msp,
+            "fp32_score_ms": o32.score_ms, "precision_score_ms": op.score_ms,
+            "obj_fp32": o32.obj, "obj_precision": op.obj,
+            "obj_rel_diff": abs(op.obj - o32.obj) / o32.obj,
+            "flagged_fraction": op.flagged_rows / float(inst.n * inst.S),
+            "max_cut_k2": {"S": S2, "fp32_ms": cut32, "bf16_ms": cutp, "bf16_speedup": cut32 / cutp,
+                           "fp32_score_ms": c32.score_ms, "bf16_score_ms": cp.score_ms,
+                           "obj_rel_diff": abs(cp.obj - c32.obj) / c32.obj}}
 
 
 def form_exact():
@@ -375,14 +388,37 @@ def form_rank1_hybrid():
     V = inst.V.real
     q = V[:, 0] / np.linalg.norm(V[:, 0]) + 1j * V[:, 1] / np.linalg.norm(V[:, 1])
     qd = torch.from_numpy(q).cuda()
-    lrqo.solve_rank1(qd, inst.K)
-    runs = []
-    for _ in range(3):
-        torch.cuda.synchronize()
-        t = time.perf_counter()
-        z, res = lrqo.solve_rank1(qd, inst.K)
-        torch.cuda.synchronize()
-        runs.append(((time.perf_counter() - t) * 1000.0, res.device_ms))
+
+    def sweep(qd):
+        """Best wall and device time of three sweeps, the result, and the
+        roofline of the form the sweep ended in."""
+        lrqo.solve_rank1(qd, inst.K)
+        runs = []
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            z, res = lrqo.solve_rank1(qd, inst.K)
+            torch.cuda.synchronize()
+            runs.append(((time.perf_counter() - t) * 1000.0, res.device_ms))
+        ms, dev = min(r[0] for r in runs), min(r[1] for r in runs)
+        # bytes per coordinate.  Both: prep reads q (16) and writes the exact
+        # key, the 32-bit image and the label (13); the cell pass reads the
+        # steps (16); the label pass reads key, label and q (25) and writes z
+        # (1).  Buckets: the split reads image and label (5) and writes the pair
+        # (8); the bucket sort reads that twice, gathers q (16) and writes step
+        # and coordinate (20).  General: four passes over 32-bit pairs (image for
+        # the counts, then pair in and out: 20, the first without positions), the
+        # run check (4), the gather of order, label and q (21) and its steps (16)
+        buckets = lrqo.rank1_form() == 1
+        nbytes = (29 + 16 + 26 + ((13 + 52) if buckets else (76 + 4 + 37))) * float(qd.numel())
+        return z, res, ms, dev, _hbm_roofline(nbytes, dev, "whole sweep: prep, split, bucket sort, cell and label passes"
+                                              if buckets else "whole sweep: prep, four radix passes, run check, "
+                                                              "gather, cell and label passes")
+
+    z, res, ms, dev, roof = sweep(qd)
+    g = np.random.default_rng(3)
+    _, _, spread_ms, spread_dev, spread_roof = sweep(torch.from_numpy(
+        g.standard_normal(inst.n) + 1j * g.standard_normal(inst.n)).cuda())
     i, j = inputs.maxcut_ppm_graph()
     rp, col, _ = inputs.csr_adjacency(inst.n, i, j)
     rpd, cold = torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda()
@@ -394,20 +430,13 @@ def form_rank1_hybrid():
 
     m = 1 << 16
     oms, _ = _timed(lambda: R1.rank1_sweep(q[:m], inst.K))
-    dev = min(r[1] for r in runs)
-    # per coordinate, bucket form: prep reads q (16 B) and writes the exact key,
-    # the 32-bit image and the label (13 B); the split reads image and label
-    # (5 B) and writes the 8 B pair; the bucket sort reads that twice, gathers q
-    # (16 B) and writes step and coordinate in sorted order (20 B); the cell
-    # pass reads the steps (16 B); the label pass reads key, label and q (25 B)
-    # and writes z (1 B)
-    sweep_bytes = (29 + 13 + 52 + 16 + 26) * float(inst.n)
     return {"workload": "maxcut_ppm", "n": inst.n, "K": inst.K, "edges": int(len(i)),
-            "roofline": _hbm_roofline(sweep_bytes, dev, "whole sweep: prep, split, bucket sort, cell and label passes"),
+            "roofline": roof,
+            "spread_q": {"what": "complex normal q of the same n", "rank1_ms": spread_ms, "rank1_device_ms": spread_dev,
+                         "roofline": spread_roof},
             "oracle": {"kind": "oracle", "ms": oms, "ms_scaled_to_n": oms * inst.n / m,
                        "sample": f"Alg. 1 on the first {m} coordinates of the same q (FP64, Python loop)"},
-            "rank1_ms": min(r[0] for r in runs), "rank1_device_ms": min(r[1] for r in runs),
-            "rank1_cells_per_s": (inst.n + 1) / (min(r[1] for r in runs) / 1000.0),
+            "rank1_ms": ms, "rank1_device_ms": dev, "rank1_cells_per_s": (inst.n + 1) / (dev / 1000.0),
             "rank1_obj": res.obj, "rank1_sort_passes": res.sort_passes,
             "cut_rank1": ref.cut_before, "cut_rank1_refined": ref.cut_after,
             "refine_rounds": ref.rounds, "refine_device_ms": ref.device_ms,
@@ -647,7 +676,7 @@ def measure_headline(inst, workload: str, steps: int, warmup: int) -> dict:
     flops_per_rowcand = 8 * r                      # real V: 2r FMA for V c, 2r FMA for V^H z
     flops = flops_per_rowcand * n * S
     avg_score_ms = sum(score_ms) / len(score_ms)
-    kernel = f"k_score_split<{r}, true, {K}, false>"
+    kernel = f"k_score_split<{r}, true, {K}, false, false>"
     roofline = _split_roofline(n, r, K, S, avg_score_ms)
     rows_at_peak = n * S / (avg_score_ms * roofline["frac"] / 1000.0)
     roofline.update({"traffic": load_traffic(kernel, workload), "kernel": kernel,

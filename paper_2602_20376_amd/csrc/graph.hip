@@ -29,8 +29,10 @@
 // launch per remaining round.  The layout checks, the first objective and the
 // first batch are queued together: each kernel returns at once when a check
 // before it failed, and the host reads the verdict with the batch's counts.
-// One thread per vertex; the CSR entries of a vertex are read in order, so
-// every per-vertex sum has a fixed order.
+// The checks, the objective and the gains of weighted graphs or K > 4 take a
+// thread per vertex, which reads its CSR entries in order; unit gains and the
+// moves give a row to sixteen lanes and add whole numbers or compare.  So every
+// per-vertex sum has a fixed order.
 #include <algorithm>
 #include <cmath>
 #include <cstddef>
@@ -546,8 +548,7 @@ lrqo_status read_checks(int flag) {
     return LRQO_OK;
 }
 
-// The report (its first `bytes`) to the host; every edge was seen from both
-// of its ends.
+// The report (its first `bytes`) to the host.
 lrqo_status read_report(const GraphScratch& s, const HostScratch& h, size_t bytes, hipStream_t st) {
     LRQO_HIP(hipMemcpyAsync(h.rep, s.rep, bytes, hipMemcpyDeviceToHost, st));
     LRQO_HIP(hipStreamSynchronize(st));
@@ -602,7 +603,7 @@ lrqo_status lrqo_graph_objective(const lrqo_graph* g, int32_t K, const uint8_t* 
     LRQO_TRY(launch_objective(gd, K, z, s, st));
     LRQO_TRY(read_report(s, h, kReportHead, st));
     LRQO_TRY(read_checks(h.rep->flag));
-    *quad = 0.5 * h.rep->out[0];
+    *quad = 0.5 * h.rep->out[0];          // every edge was seen from both of its ends
     *cut = 0.5 * h.rep->out[1];
     return LRQO_OK;
 }

@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kSymT) void k_w_tiles(PhaseOp o, const double2* __r
 // y_i = sum_k U_ik c_k + sigma (row sums of the items of stripe I + column
 // sums of tiles (I', I), I' <= I); item_first[I] = first item of stripe I.
 __global__ __launch_bounds__(kSymT) void k_w_combine(PhaseOp o, const double2* __restrict__ upart, int unb,
-                                                     const int32_t* __restrict__ item_first, int64_t P,
+                                                     const int32_t* __restrict__ item_first,
                                                      const double2* __restrict__ rowpart,
                                                      const double2* __restrict__ colpart, double2* __restrict__ y) {
     __shared__ double2 c[LRQO_MAX_R];
@@ -349,7 +349,6 @@ __global__ __launch_bounds__(kSymT) void k_w_combine(PhaseOp o, const double2* _
         yi += u.y;
     }
     y[i] = make_double2(yr, yi);
-    (void)P;
 }
 
 // ---------------------------------------------------------------- basis algebra
@@ -1060,7 +1059,7 @@ lrqo_status lanczos_factor(int kind, const LapOp& lap, const PhaseOp& ph, int64_
         if (kind == kOpPhase) {
             hipLaunchKernelGGL(k_w_tiles, dim3((unsigned)items.size()), dim3(kSymT), 0, st, ph, x, d_items, P, chunk,
                                rowpart, colpart);
-            hipLaunchKernelGGL(k_w_combine, dim3((unsigned)P), dim3(kSymT), 0, st, ph, dpart, nbd, d_first, P, rowpart,
+            hipLaunchKernelGGL(k_w_combine, dim3((unsigned)P), dim3(kSymT), 0, st, ph, dpart, nbd, d_first, rowpart,
                                colpart, y);
             LRQO_HIP(hipGetLastError());
         }
