@@ -549,7 +549,7 @@ int cands_per_block(const SampledJob& job, ScoreForm form) {
 ScoreForm score_form(const SampledJob& job) {
     const ScoreForm plain = job.precision == 1 ? kFormPrecision : kFormFp32;
     if (k_special(job.K) == 0 || job.r < 2 || job.r > 4 || (job.real && job.K == 2)) return plain;
-    if (job.n < 2048 || job.n > split_rows(2) || (plain == kFormPrecision && bf16_form() == 1)) return plain;
+    if (job.n < 2048 || job.n > kSplitMaxRows || (plain == kFormPrecision && bf16_form() == 1)) return plain;
     if (job.real && job.K == 4 && job.r == 2 && job.n < 65536) return plain;
     return kFormSplit;
 }

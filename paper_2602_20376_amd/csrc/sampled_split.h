@@ -36,20 +36,22 @@ namespace {
 //              and Im z in 23-bit fixed point, three balanced base-256 digits
 //              each, looked up by v_perm_b32 (eight-byte tables: sector and
 //              sign select the byte)
-//   s = V^H z  v_mfma_i32_32x32x32_i8 of those planes against V in 30-bit
-//              fixed point (four balanced base-256 digits per value: 4C <= 32
-//              rows of the operand).  Column j of a 256-row tile enters in
-//              units of 2^(E_j - 29), E_j at most kSplitSlack above the
-//              exponent e of its largest entry there, so an entry is off by at
-//              most 2^(e - 26), a fraction of what one addition to a running
-//              FP32 sum of that size rounds away, and a few large rows cost
-//              only the rows that share their tile.  The sums are exact
-//              integers; their digits are put together, in FP64, where an E_j
-//              changes and at the end.  (10^6 rows, r = 3 real, K = 3, 2^19
-//              candidates: 59.5 ms for normal rows, 66.8 for row sizes u^-3,
-//              u uniform, where most tiles change an E_j.  One scale for the
-//              whole factor took 57.1 ms, but 300,000 rows of 1e-9 beside one
-//              of 3.9 left f off by 1.8e-4, now 1e-5, FP32 sums 1.2e-5.)
+//   s = V^H z  v_mfma_i32_32x32x32_i8 of those planes against V in fixed point
+//              of 45 bits (balanced base-256 digits: four in units of
+//              2^(E_j - 29) for column j and two of 2^-15 of that, in operand
+//              rows that would be idle; 8 rows a component) or, for more than
+//              four components, 30 (4C <= 32 rows).  E_j is at most 19 or 4
+//              above the exponent e of the column's largest entry in the
+//              256-row tile, so an entry is off by at most 2^(e - 26), a
+//              fraction of what one addition to a running FP32 sum of that size
+//              rounds away, and a few large rows cost only the rows that share
+//              their tile.  The sums are exact integers; their digits are put
+//              together, in FP64, where an E_j changes and at the end.  (10^6 rows, r = 3 real, K = 3, 2^19
+//              candidates: 69.0 ms for normal rows, 70.6 for row sizes u^-3,
+//              u uniform; with 30 bits 67.6 and 74.2, as 88% of the tiles of
+//              such a factor change an E_j.  One scale for the whole factor
+//              took 2.4 ms less, but 300,000 rows of 1e-9 beside one of 3.9
+//              left f off by 1.8e-4, now 1e-5, FP32 sums 1.2e-5.)
 //
 // Layouts (lane l, h = l / 32): operand rows/columns l % 32, F16 k-slots
 // 8h .. 8h+7, I8 k-slots 16h .. 16h+15; result register i is row
@@ -65,9 +67,11 @@ constexpr int kSplitBlock = 512;                           // eight waves of 32 
 constexpr int kSplitCands = kSplitBlock / kWave * 32;      // candidates of a block
 static_assert(kSplitTile * 2 == kSplitBlock, "a thread stages one operand of one row");
 
-// Rows whose I32 sums stay exact: digits of V are at most 128 in size, plane
-// entries 1 (K = 16: 128; its sums are folded after as many rows).
-__host__ __device__ constexpr int64_t split_rows(int KS) { return (int64_t)1 << (KS == 16 ? 16 : 23); }
+// Rows after which the I32 sums are folded: digits of V are at most 128 in size
+// and plane entries 1, or 128 for K = 16, so that the sums stay at 2^30, and for
+// the others a sum plus 256 times the next one as well.
+__host__ __device__ constexpr int64_t split_rows(int KS) { return (int64_t)1 << (KS == 16 ? 16 : 15); }
+constexpr int64_t kSplitMaxRows = (int64_t)1 << 23;
 
 // K = 16 planes.  Entry e of a table: bits 0 and 1 name the sector of the
 // quadrant, bit 2 is the sign; entries hold digit k of round(mag * kRoot16).
@@ -110,7 +114,7 @@ constexpr int kSplitC[8] = {0, 0, 1, 1, 0, 2, 1, 2};
 // Real r = 3 fits one chunk, but for two products V1 c3: K = 4 and the precision
 // form (QUICK; its former BF16 parts left several u) leave it at that, else Re w
 // has a chunk more, for what comes last in size (K = 3 13.3 without it; 10^6
-// rows, 2^19 candidates: 59.5 -> 69.1 ms, FP32 form 122).  Complex r = 3 leaves
+// rows, 2^19 candidates: 59.5 -> 69.0 ms, FP32 scorer 122).  Complex r = 3 leaves
 // out part of V3 c1 and V1 c3, but for K = 2, which has Re w alone.
 template <int R, bool REAL, int KS, bool QUICK>
 struct SplitShape {
@@ -194,11 +198,12 @@ __device__ __forceinline__ uint32_t signs4(float a, float b, float c, float d) {
 
 // A column's exponent E (tile_exp holds those of its largest entries, tile by
 // tile, from the prologue) is kept while the largest entry of the tile is in
-// [2^(E - kSplitSlack), 2^(E + 1)); else it becomes one above that entry's
+// [2^(E - split_slack), 2^(E + 1)); else it becomes one above that entry's
 // exponent (so that the next larger tile need not change it), at most that of
 // the factor's largest entry.  V enters the I8 operand as round(V 2^(29-E)),
 // at most 2^30 in size.
-constexpr int kSplitSlack = 4;
+__host__ __device__ constexpr bool split_low(int C) { return C <= 4; }   // two low digits too
+__host__ __device__ constexpr int split_slack(int C) { return split_low(C) ? 19 : 4; }
 
 // Whether a direction of a caller's list lies within the range of the F16 parts,
 // which reach down to 2^-39 of a row's and of a direction's largest entry.  The
@@ -337,7 +342,8 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
     // every tile: lane l those of operand row l % 32 (digit p of a column's Re
     // or Im) over its sixteen rows of V.
     const int uwave = __builtin_amdgcn_readfirstlane(wave);
-    const int dslot = (lane & 31) >> 2, dcol = REAL ? dslot : (dslot & 1) + 2 * (dslot >> 2);
+    constexpr bool LOW = split_low(C);
+    const int dslot = (lane & 31) >> 2, dcol = LOW ? dslot & (REAL ? 3 : 1) : (dslot & 1) + 2 * (dslot >> 2);
     int digits = 0;
     double dsum = 0.0;
 #pragma unroll
@@ -350,9 +356,13 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
 #pragma unroll
             for (int q = 0; q < (REAL ? 1 : 2); ++q) {
                 const int i0 = REAL ? 4 * g : 8 * g + 4 * q;
+                auto pair = [&](int k, int i) {
+                    return KS == 16 ? fma(256.0, (double)acc[k][i + 1], (double)acc[k][i])
+                                    : (double)(acc[k][i + 1] * 256 + acc[k][i]);
+                };
                 auto plane = [&](int k) {
-                    return unit * (double)((((long long)acc[k][i0 + 3] * 256 + acc[k][i0 + 2]) * 256 + acc[k][i0 + 1]) * 256 +
-                                           acc[k][i0]);
+                    const double v = fma(65536.0, pair(k, i0 + 2), pair(k, i0));
+                    return unit * (LOW ? fma(0x1p-15, pair(k, i0 + (LOW ? 8 : 0)), v) : v);
                 };
                 if constexpr (KS <= 4) {
                     const double n0 = -plane(0), n1 = -plane(NPL - 1);   // masks are 0 / -1
@@ -384,6 +394,7 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
             double unit = 0.0;                           // of this lane's column
 #pragma unroll
             for (int j = 0; j < R; ++j) unit += dcol == j ? split_unit(E[j]) : 0.0;
+            if (LOW && dslot > 3) unit *= 0x1p-15;
             dsum += unit * (double)((long long)digits << (8 * (lane & 3)));
             digits = 0;
         }
@@ -411,7 +422,7 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
 #pragma unroll
         for (int j = 0; j < R; ++j) {
             const int e = (w[j / 2] << (16 - 16 * (j & 1))) >> 16;
-            to[j] = e == kZeroColumn || (e <= from[j] && e >= from[j] - kSplitSlack) ? from[j] : min(e + 1, ev);
+            to[j] = e == kZeroColumn || (e <= from[j] && e >= from[j] - split_slack(C)) ? from[j] : min(e + 1, ev);
             change |= to[j] != from[j];
         }
         return change;
@@ -442,11 +453,19 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
             const int d = rr >> 3, g = (rr >> 2) & 1, b = rr & 3;
 #pragma unroll
             for (int k = 0; k < C; ++k) {
-                const int q = __float2int_rn(ldexpf(v[k], 29 - Et[k % R]));
+                const float x = ldexpf(v[k], 29 - Et[k % R]);
+                const int q = __float2int_rn(x);
                 const uint32_t dig = ((uint32_t)q + 0x00808080u) ^ 0x00808080u;   // balanced digits, lowest first
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
                     as[buf][blk][32 * g + 4 * split_slot<R, REAL>(k) + t][4 * d + b] = (signed char)(dig >> (8 * t));
+                if constexpr (LOW) {                     // the rest, in units of 2^-15
+                    const int ql = __float2int_rn((x - (float)q) * 32768.0f);
+                    const uint32_t low = ((uint32_t)ql + 0x80u) ^ 0x80u;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        as[buf][blk][32 * g + 4 * split_slot<R, REAL>(k) + 16 + t][4 * d + b] = (signed char)(low >> (8 * t));
+                }
             }
         }
     };
@@ -582,8 +601,7 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
                 for (int d = 0; d < 4; ++d) digits = __builtin_amdgcn_sdot4(a8[d], 0x01010101, digits, false);
             }
         }
-        // K = 16: also before the sums could pass 31 bits
-        const bool full = KS == 16 && (t0 - r0) % split_rows(KS) == split_rows(KS) - kSplitTile;
+        const bool full = (t0 - r0) % split_rows(KS) == split_rows(KS) - kSplitTile;
         if (change || full) {
             fold();
 #pragma unroll
@@ -612,7 +630,10 @@ __global__ __launch_bounds__(kSplitBlock, split_waves(KS)) void k_score_split(Sc
 #pragma unroll 1
                 for (int w = 0; w < kSplitBlock / kWave; ++w)
 #pragma unroll
-                    for (int d = 0; d < 4; ++d) t[q] += tot[w * kWave + at + d] + tot[w * kWave + 32 + at + d];
+                    for (int d = 0; d < 4; ++d) {
+                        t[q] += tot[w * kWave + at + d] + tot[w * kWave + 32 + at + d];
+                        if constexpr (LOW) t[q] += tot[w * kWave + 16 + at + d] + tot[w * kWave + 48 + at + d];
+                    }
             }
             // z = a + ib in every row, corrected by the masks
             constexpr double a = KS == 2 ? 1.0 : (KS == 3 ? -0.5 : 0.70710678118654752);
