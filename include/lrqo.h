@@ -87,9 +87,11 @@ lrqo_status lrqo_shutdown(void);
  * r = 2 from n = 65,536 on: on the matrix core from split FP32 values, w to the
  * grade of an FP32 dot product (a caller's list of directions with a component
  * below 2^-12 of the largest, or one that puts whole columns on a tie, takes the
- * FP32 dot products instead), s = V^H z from exact integer sums of V, each column rounded
- * to 2^-26 of its largest entry over runs of 256 rows); the best `rescore_topk` FP32 scores (ties to the lower
- * index) are re-evaluated in FP64 from the same FP32 direction widened to FP64; the FP64 arg-max (ties to the lower index)
+ * FP32 dot products instead), s = V^H z from exact integer sums of V, each
+ * column rounded to 2^-26 of its largest entry over runs of 256 rows); the best
+ * `rescore_topk` FP32 scores (ties to the lower index) are re-evaluated in FP64
+ * from the same FP32 direction widened to FP64; the FP64 arg-max (ties to the
+ * lower index)
  * is the result.  Labels and objective are therefore exactly those of the
  * FP64 decision rule at the returned direction.
  *

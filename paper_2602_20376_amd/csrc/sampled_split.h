@@ -46,12 +46,13 @@ namespace {
 //              fraction of what one addition to a running FP32 sum of that size
 //              rounds away, and a few large rows cost only the rows that share
 //              their tile.  The sums are exact integers; their digits are put
-//              together, in FP64, where an E_j changes and at the end.  (10^6 rows, r = 3 real, K = 3, 2^19
-//              candidates: 69.0 ms for normal rows, 70.6 for row sizes u^-3,
-//              u uniform; with 30 bits 67.6 and 74.2, as 88% of the tiles of
-//              such a factor change an E_j.  One scale for the whole factor
-//              took 2.4 ms less, but 300,000 rows of 1e-9 beside one of 3.9
-//              left f off by 1.8e-4, now 1e-5, FP32 sums 1.2e-5.)
+//              together, in FP64, where an E_j changes and at the end.  (10^6
+//              rows, r = 3 real, K = 3, 2^19 candidates: 69.0 ms for normal
+//              rows, 70.6 for row sizes u^-3, u uniform; with 30 bits 67.6 and
+//              74.2, as 88% of the tiles of such a factor change an E_j.  One
+//              scale for the whole factor took 2.4 ms less, but 300,000 rows
+//              of 1e-9 beside one of 3.9 left f off by 1.8e-4, now 1e-5, FP32
+//              sums 1.2e-5.)
 //
 // Layouts (lane l, h = l / 32): operand rows/columns l % 32, F16 k-slots
 // 8h .. 8h+7, I8 k-slots 16h .. 16h+15; result register i is row
@@ -104,13 +105,16 @@ constexpr int kSplitV[8] = {0, 1, 0, 1, 2, 0, 2, 1};
 constexpr int kSplitC[8] = {0, 0, 1, 1, 0, 2, 1, 2};
 
 // Shape of w's operands: chunks of 16 k-slots, as many as keep the labels at or
-// below the error of FP32 ones.  Wrong labels per 10^9, normal V, this scorer
-// and FP32 (20 10^9 labels each; one standard deviation is 7% at 10 per 10^9):
-//     real r = 2: K = 3 6.2, 9.4; 16 42, 67       complex r = 2: K = 3 6.1, 10.9; 16 41, 77
-//     real r = 3: K = 3 11.0, 10.3 (60 10^9       complex r = 3: K = 2 1.8, 5.7; 3 13.8, 14.7;
-//                 labels, +-0.4); 4 11.7, 19;                    4 16, 23; 8 41, 45; 16 83, 97
-//                 8 31, 36; 16 63, 75
-//     real r = 4: K = 3 6.9, 12.3; 16 44, 84      complex r = 4: K = 3 7.2, 15.3; 16 52, 103
+// below the error of FP32 ones.  Wrong labels per 10^9, normal V, this scorer /
+// the FP32 scorer (20 10^9 labels each, 60 10^9 for real r = 3, K = 3 and
+// complex r = 3, K = 2; one standard deviation is 7% at 10 per 10^9):
+//                K = 2       3           4         8         16
+//     real    2              6.2/9.4     1.0/17              42/67
+//             3              11.0/10.3   12/19     31/36     63/75
+//             4              6.9/12.3                        44/84
+//     complex 2              6.1/10.9                        41/77
+//             3  1.8/5.7     13.8/14.7   16/23     41/45     83/97
+//             4              7.2/15.3                        52/103
 // Real r = 3 fits one chunk, but for two products V1 c3: K = 4 and the precision
 // form (QUICK; its former BF16 parts left several u) leave it at that, else Re w
 // has a chunk more, for what comes last in size (K = 3 13.3 without it; 10^6
@@ -194,24 +198,26 @@ __device__ __forceinline__ uint32_t signs_hi(float a, float b) {
     return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x0b090c0cu);
 }
 
-__device__ __forceinline__ uint32_t signs4(float a, float b, float c, float d) { return signs_lo(a, b) | signs_hi(c, d); }
+__device__ __forceinline__ uint32_t signs4(float a, float b, float c, float d) {
+    return signs_lo(a, b) | signs_hi(c, d);
+}
 
 // A column's exponent E (tile_exp holds those of its largest entries, tile by
 // tile, from the prologue) is kept while the largest entry of the tile is in
 // [2^(E - split_slack), 2^(E + 1)); else it becomes one above that entry's
 // exponent (so that the next larger tile need not change it), at most that of
-// the factor's largest entry.  V enters the I8 operand as round(V 2^(29-E)),
-// at most 2^30 in size.
+// the factor's largest entry.  V enters the I8 operand as round(V 2^(29-E)), at
+// most 2^30 in size, and with low digits the rest of it, rounded to 2^-15.
 __host__ __device__ constexpr bool split_low(int C) { return C <= 4; }   // two low digits too
 __host__ __device__ constexpr int split_slack(int C) { return split_low(C) ? 19 : 4; }
 
 // Whether a direction of a caller's list lies within the range of the F16 parts,
-// which reach down to 2^-39 of a row's and of a direction's largest entry.  The
-// product of the smallest parts of V and the largest of c, and the reverse, is
-// no more than 2^-27 of sum_j |V_ij||c_j| while no component is below 2^-12 of
-// the largest (a row may lie on one column).  K = 2, 3, 4: the same for Re w and
-// Im w as a whole, and no part that decides a sign alone may be lost or a tie
-// (2^-24: real or imaginary c_j; K = 4: their sum and difference).  Of 2^20
+// which reach down to 2^-39 of a row's and of a direction's largest entry.  What
+// they cannot hold is no more than 2^-27 of sum_j |V_ij||c_j| while no component
+// is below 2^-12 of the largest (a row may lie on that column alone).  K = 2, 3,
+// 4: the same for Re w and Im w as a whole, and no part that decides a sign alone
+// may be lost or a tie (2^-24: real or imaginary c_j; K = 4: their sum and
+// difference).  Of 2^20
 // directions of the sphere the smallest component is near 2^-11 of the largest,
 // and below 2^-16, where a row on that column alone would lose more than in
 // FP32, once in a thousand calls; so only lists, which may hold axes, are looked
