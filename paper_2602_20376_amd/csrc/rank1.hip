@@ -651,9 +651,11 @@ __global__ __launch_bounds__(kRbThreads) void k_r1_labels(RbDev p) {
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && tid < 4) p.out->flag[tid] = p.flag[tid];
     if (!p.span && (p.flag[1] | p.flag[2])) return;
-    double f = -1.0;
-    int64_t c = INT64_MAX;
-    int own = -1;
+    // the first bucket's best stands where no value is a number (q near the
+    // largest FP64: the cell before the first point)
+    double f = tid ? -1.0 : p.bbest[0].f;
+    int64_t c = tid ? INT64_MAX : p.bbest[0].cell;
+    int own = tid ? -1 : 0;
     for (int t = tid; t < p.nb; t += kRbThreads)
         if (better(p.bbest[t].f, p.bbest[t].cell, f, c)) {
             f = p.bbest[t].f;
